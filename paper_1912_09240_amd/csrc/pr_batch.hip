@@ -29,13 +29,12 @@
 #include <vector>
 
 #include "pr_coarse_dev.hpp"
+#include "pr_expm.hpp"
 #include "pr_fine_dev.hpp"
 #include "pr_internal.hpp"
 
 namespace pr {
 
-int build_expm(const std::vector<double> &lo, const std::vector<double> &di, const std::vector<double> &up, int n,
-               double tau, double *out, double *w1, double *w2, double *w3, hipStream_t st);
 int make_generator(const pr_sde *sde, const pr_grid *grid, std::vector<double> &lo, std::vector<double> &di,
                    std::vector<double> &up, hipStream_t st);
 
@@ -782,9 +781,15 @@ static int batch_create(int B, const pr_sde *sde, const pr_schedule *sch, const 
     std::vector<CoarseUnit> cu;
     std::vector<ChainInst> chain;
     std::vector<std::tuple<double, double, double, double>> gen_keys;
-    std::vector<std::vector<double>> G_lo, G_di, G_up;
-    struct EReq { int gen; double tau; };
-    std::vector<EReq> ereq;
+    std::vector<Tridiag> gens;
+    std::vector<ExpmReq> ereq;
+    // request of (generator, tau) built on a given base, added where there is none yet
+    auto request = [&ereq](int gen, double tau, int base) {
+        for (size_t t = 0; t < ereq.size(); ++t)
+            if (ereq[t].gen == gen && ereq[t].tau == tau && ereq[t].base == base) return (int)t;
+        ereq.push_back(ExpmReq{gen, tau, base});
+        return (int)ereq.size() - 1;
+    };
     for (int i = 0; i < B; ++i) {
         if (sde[i].a != nullptr) {
             set_error("batched instances serve a = NULL");
@@ -799,23 +804,18 @@ static int batch_create(int B, const pr_sde *sde, const pr_schedule *sch, const 
             gen_keys.push_back(gk);
             std::vector<double> lo, di, up;
             PR_CHECK(make_generator(&sde[i], grid, lo, di, up, st));
-            G_lo.push_back(lo);
-            G_di.push_back(di);
-            G_up.push_back(up);
+            gens.push_back(Tridiag{lo, di, up});
         }
         chain.push_back(ChainInst{b->qrow0[i], sch[i].n_slices, (int)cu.size(), 0});
-        for (int s = 0; s < sch[i].n_slices; ++s) {
-            const int64_t L = slice_begin(sch[i].total_steps, sch[i].n_slices, s + 1) -
-                              slice_begin(sch[i].total_steps, sch[i].n_slices, s);
-            // distinct (generator, tau): tau = L dt of this instance
-            const double tau = (double)L * sch[i].dt;
-            int eid = -1;
-            for (size_t t = 0; t < ereq.size(); ++t)
-                if (ereq[t].gen == gid && ereq[t].tau == tau) eid = (int)t;
-            if (eid < 0) {
-                eid = (int)ereq.size();
-                ereq.push_back(EReq{gid, tau});
-            }
+        // distinct (generator, tau): tau = L dt of this instance, the longer
+        // slices built on the shortest as in a single instance's handle
+        const int K = sch[i].n_slices;
+        auto len = [&](int s) { return slice_begin(sch[i].total_steps, K, s + 1) - slice_begin(sch[i].total_steps, K, s); };
+        int64_t shortest = len(0);
+        for (int s = 1; s < K; ++s) shortest = std::min(shortest, len(s));
+        const int base = request(gid, (double)shortest * sch[i].dt, -1);
+        for (int s = 0; s < K; ++s) {
+            const int eid = len(s) == shortest ? base : request(gid, (double)len(s) * sch[i].dt, base);
             cu.push_back(CoarseUnit{b->qrow0[i] + s, b->qrow0[i] + s + 1, eid, 0});
         }
     }
@@ -825,19 +825,7 @@ static int batch_create(int B, const pr_sde *sde, const pr_schedule *sch, const 
     b->n_e = (int)ereq.size();
     const int64_t nn = (int64_t)I * I;
     PB_ALLOC(b->E, sizeof(double) * nn * b->n_e);
-    {
-        double *w = nullptr;
-        PB_ALLOC(w, sizeof(double) * nn * 3);
-        for (int e = 0; e < b->n_e; ++e) {
-            const int s = build_expm(G_lo[ereq[e].gen], G_di[ereq[e].gen], G_up[ereq[e].gen], I, ereq[e].tau,
-                                     b->E + nn * e, w, w + nn, w + 2 * nn, st);
-            if (s != PR_OK) {
-                (void)hipFree(w);
-                return s;
-            }
-        }
-        (void)hipFree(w);
-    }
+    PR_CHECK(build_expms(gens, ereq, I, b->E, st));
     // sort layout of the states t = 1..K_i of every instance
     int64_t tiles = 0, keys = 0;
     std::vector<int> tile_seg;

@@ -5,79 +5,19 @@
 // piecewise-linear cdf (Sec. 4.4, eq. (discr_cdf)) and the quantile iterator
 // with its monotone repair.
 //
-// A is tridiagonal; E(tau) is dense.  It is built once per distinct slice
-// length on the device by scaling and squaring: X = A tau / 2^s with
-// ||X||_1 <= 1, a degree-24 Taylor polynomial by Horner's rule, then s
-// squarings, all with an LDS-tiled FP64 GEMM.  Applying E is a batched
-// matrix-vector product (FP64 VALU; the matrix stays in L2/MALL).
+// A is tridiagonal; E(tau) is dense and built once per distinct slice length
+// on the device (pr_expm.hip).  Applying E is a batched matrix-vector
+// product (FP64 VALU; the matrix stays in L2/MALL).
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
 #include "pr_chem.hpp"
 #include "pr_coarse_dev.hpp"
+#include "pr_expm.hpp"
 #include "pr_internal.hpp"
 
 namespace pr {
-
-// ---------------------------------------------------------------------------
-// FP64 GEMM C = alpha * A B + diag * I (n x n, row-major), 64x64 tiles.
-// ---------------------------------------------------------------------------
-constexpr int GM_T = 64, GM_K = 16;
-
-__global__ void __launch_bounds__(256) gemm_f64(const double *__restrict__ A, const double *__restrict__ B,
-                                                double *__restrict__ C, int n, double alpha, double diag) {
-    __shared__ double As[GM_K][GM_T + 1];
-    __shared__ double Bs[GM_K][GM_T + 1];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int row0 = blockIdx.y * GM_T, col0 = blockIdx.x * GM_T;
-    double acc[4][4] = {};
-    for (int k0 = 0; k0 < n; k0 += GM_K) {
-        for (int e = threadIdx.x; e < GM_T * GM_K; e += 256) {
-            const int r = e / GM_K, c = e % GM_K;  // A tile: rows row0+r, cols k0+c
-            const int gr = row0 + r, gc = k0 + c;
-            As[c][r] = (gr < n && gc < n) ? A[(int64_t)gr * n + gc] : 0.0;
-            const int br = e / GM_T, bc = e % GM_T;  // B tile: rows k0+br, cols col0+bc
-            const int gbr = k0 + br, gbc = col0 + bc;
-            Bs[br][bc] = (gbr < n && gbc < n) ? B[(int64_t)gbr * n + gbc] : 0.0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < GM_K; ++kk) {
-            double a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = row0 + ty + 16 * i, c = col0 + tx + 16 * j;
-            if (r < n && c < n) C[(int64_t)r * n + c] = alpha * acc[i][j] + (r == c ? diag : 0.0);
-        }
-}
-
-// X = A_tridiag * scale, dense.
-__global__ void tridiag_to_dense(const double *__restrict__ lo, const double *__restrict__ di,
-                                 const double *__restrict__ up, int n, double scale, double *__restrict__ X,
-                                 double add_identity_over) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)n * n) return;
-    const int r = (int)(e / n), c = (int)(e % n);
-    double v = 0.0;
-    if (c == r) v = di[r] * scale;
-    else if (c == r + 1) v = up[r] * scale;
-    else if (c == r - 1) v = lo[r] * scale;
-    if (add_identity_over != 0.0) v = v * add_identity_over + (r == c ? 1.0 : 0.0);
-    X[e] = v;
-}
 
 __global__ void __launch_bounds__(256) knots_to_masses(const double *__restrict__ q, int q_stride,
                                                        double *__restrict__ rho, GridDev g) {
@@ -217,52 +157,6 @@ struct Coarse {
     int device = 0;
 };
 
-int build_expm(const std::vector<double> &lo, const std::vector<double> &di, const std::vector<double> &up,
-                      int n, double tau, double *out, double *w1, double *w2, double *w3, hipStream_t st) {
-    // ||A tau||_1 = max column sum of |entries|
-    double norm = 0.0;
-    for (int c = 0; c < n; ++c) {
-        double s = std::fabs(di[c]);
-        if (c > 0) s += std::fabs(up[c - 1]);
-        if (c + 1 < n) s += std::fabs(lo[c + 1]);
-        norm = std::max(norm, s * tau);
-    }
-    int sq = 0;
-    while (norm / std::ldexp(1.0, sq) > 1.0) ++sq;
-    const double scale = tau / std::ldexp(1.0, sq);
-    constexpr int M = 24;  // ||X|| <= 1: truncation below 1/25! ~ 6e-26
-    double *d_lo, *d_di, *d_up;
-    PR_HIP(hipMalloc(&d_lo, sizeof(double) * n * 3));
-    d_di = d_lo + n;
-    d_up = d_lo + 2 * n;
-    PR_HIP(hipMemcpyAsync(d_lo, lo.data(), sizeof(double) * n, hipMemcpyHostToDevice, st));
-    PR_HIP(hipMemcpyAsync(d_di, di.data(), sizeof(double) * n, hipMemcpyHostToDevice, st));
-    PR_HIP(hipMemcpyAsync(d_up, up.data(), sizeof(double) * n, hipMemcpyHostToDevice, st));
-    const int64_t nn = (int64_t)n * n;
-    const dim3 eg((unsigned)((nn + 255) / 256));
-    // X = A tau / 2^s into w1; R = I + X / M into w2
-    hipLaunchKernelGGL(tridiag_to_dense, eg, dim3(256), 0, st, d_lo, d_di, d_up, n, scale, w1, 0.0);
-    hipLaunchKernelGGL(tridiag_to_dense, eg, dim3(256), 0, st, d_lo, d_di, d_up, n, scale, w2, 1.0 / M);
-    PR_LAUNCHED();
-    const dim3 gg((n + GM_T - 1) / GM_T, (n + GM_T - 1) / GM_T);
-    double *R = w2, *T = w3;
-    for (int k = M - 1; k >= 1; --k) {  // R = I + X R / k
-        hipLaunchKernelGGL(gemm_f64, gg, dim3(256), 0, st, (const double *)w1, (const double *)R, T, n, 1.0 / k, 1.0);
-        PR_LAUNCHED();
-        std::swap(R, T);
-    }
-    for (int i = 0; i < sq; ++i) {
-        double *dst = (i == sq - 1) ? out : T;
-        hipLaunchKernelGGL(gemm_f64, gg, dim3(256), 0, st, (const double *)R, (const double *)R, dst, n, 1.0, 0.0);
-        PR_LAUNCHED();
-        if (dst == T) std::swap(R, T);
-    }
-    if (sq == 0) PR_HIP(hipMemcpyAsync(out, R, sizeof(double) * nn, hipMemcpyDeviceToDevice, st));
-    PR_HIP(hipStreamSynchronize(st));
-    PR_HIP(hipFree(d_lo));
-    return PR_OK;
-}
-
 // Tridiagonal generator of the finite-volume scheme: lo[i] = A[i][i-1],
 // di[i] = A[i][i], up[i] = A[i][i+1].
 int make_generator(const pr_sde *sde, const pr_grid *grid, std::vector<double> &lo, std::vector<double> &di,
@@ -352,19 +246,11 @@ int coarse_create_tridiag(const std::vector<double> &lo, const std::vector<doubl
         set_error("copy of the slice table failed");
         return fail(PR_E_HIP);
     }
-    double *w = nullptr;
-    if (hipMalloc(&w, sizeof(double) * nn * 3) != hipSuccess) {
-        set_error("device allocation of the exponential workspace failed");
-        return fail(PR_E_NOMEM);
-    }
-    for (int t = 0; t < c->n_tau; ++t) {
-        const int s = build_expm(lo, di, up, I, c->taus[t], c->E + nn * t, w, w + nn, w + 2 * nn, st);
-        if (s != PR_OK) {
-            (void)hipFree(w);
-            return fail(s);
-        }
-    }
-    (void)hipFree(w);
+    std::vector<ExpmReq> reqs;
+    const int shortest = (int)(std::min_element(lens.begin(), lens.end()) - lens.begin());
+    for (int t = 0; t < c->n_tau; ++t) reqs.push_back(ExpmReq{0, c->taus[t], t == shortest ? -1 : shortest});
+    const int e = build_expms({Tridiag{lo, di, up}}, reqs, I, c->E, st);
+    if (e != PR_OK) return fail(e);
     (void)hipGetDevice(&c->device);
     *out = c;
     return PR_OK;
