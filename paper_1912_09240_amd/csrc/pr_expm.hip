@@ -107,34 +107,37 @@ __global__ void __launch_bounds__(256) expm_rows(const RowJob *__restrict__ jobs
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // C = A B (n x n, row-major) for the jobs of one step (blockIdx.z), one
-// 32W x 32W tile per block, each of the four waves 16W x 16W of it in
-// 16x16x4 FP64 matrix instructions.  Operand lanes: A[l%16][l/16],
-// B[l/16][l%16]; result register r of lane l: row 4 r + l/16, column l%16.
+// 32W x 32W tile per block of NW waves, each 16W x 16WC of it in 16x16x4
+// FP64 matrix instructions.  Operand lanes: A[l%16][l/16], B[l/16][l%16];
+// result register r of lane l: row 4 r + l/16, column l%16.
 // Matrix rate bound: 64 clocks per instruction and SIMD, 27 us for a full
-// 1024^3 product (256 blocks of W = 2, one per CU); W = 1 keeps 4x as many
-// blocks where W = 2 would leave most CUs idle (200 cells: 49 blocks, 16
-// otherwise).
-template <int W>
-__global__ void __launch_bounds__(256) expm_gemm(const GemmJob *__restrict__ jobs, int n) {
-    constexpr int T = 32 * W, PER = T * EX_K / 256;
+// 1024^3 product (256 blocks of W = 2, one per CU).  Two waves per SIMD hide
+// the LDS reads: 8 waves take 44 us on average over the 8 products of 1024
+// cells (the first two banded), 4 waves of 32x32 took 58 us.  W = 1 keeps 4x
+// as many blocks where W = 2 would leave most CUs idle (200 cells: 49 blocks,
+// 16 otherwise).
+template <int W, int NW>
+__global__ void __launch_bounds__(64 * NW) expm_gemm(const GemmJob *__restrict__ jobs, int n) {
+    constexpr int T = 32 * W, NT = 64 * NW, PER = T * EX_K / NT;
+    constexpr int WC = 4 * W * W / NW / W;  // 16-column tiles per wave (W rows of them)
     __shared__ double As[2][EX_K][T + 2], Bs[2][EX_K][T + 2];
     const GemmJob J = jobs[blockIdx.z];
     const int row0 = (int)blockIdx.y * T, col0 = (int)blockIdx.x * T;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = (wave >> 1) * 16 * W, wc = (wave & 1) * 16 * W, li = lane & 15, lk = lane >> 4;
+    const int wr = (wave / (NW / 2)) * 16 * W, wc = (wave % (NW / 2)) * 16 * WC, li = lane & 15, lk = lane >> 4;
     // k with A[row][k] and B[k][col] both inside their bands
     const int ka = max(0, max(row0 - J.ba, col0 - J.bb)) & ~(EX_K - 1);
     const int kb = min(n, min(row0 + T + J.ba, col0 + T + J.bb));
-    f64x4 acc[W][W];
+    f64x4 acc[W][WC];
 #pragma unroll
     for (int i = 0; i < W; ++i)
 #pragma unroll
-        for (int j = 0; j < W; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int j = 0; j < WC; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
     double ra[PER], rb[PER];
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int e = 0; e < PER; ++e) {
-            const int id = tid + e * 256;
+            const int id = tid + e * NT;
             const int ar = row0 + id / EX_K, ac = k0 + id % EX_K;
             ra[e] = (ar < n && ac < n) ? J.A[(int64_t)ar * n + ac] : 0.0;
             const int br = k0 + id / T, bc = col0 + id % T;
@@ -144,7 +147,7 @@ __global__ void __launch_bounds__(256) expm_gemm(const GemmJob *__restrict__ job
     auto stage = [&](int b) {
 #pragma unroll
         for (int e = 0; e < PER; ++e) {
-            const int id = tid + e * 256;
+            const int id = tid + e * NT;
             As[b][id % EX_K][id / EX_K] = ra[e];
             Bs[b][id / T][id % T] = rb[e];
         }
@@ -159,15 +162,15 @@ __global__ void __launch_bounds__(256) expm_gemm(const GemmJob *__restrict__ job
             if (more) fetch(k0 + EX_K);
 #pragma unroll
             for (int kk = 0; kk < EX_K; kk += 4) {
-                double a[W], v[W];
+                double a[W], v[WC];
 #pragma unroll
                 for (int i = 0; i < W; ++i) a[i] = As[b][kk + lk][wr + 16 * i + li];
 #pragma unroll
-                for (int j = 0; j < W; ++j) v[j] = Bs[b][kk + lk][wc + 16 * j + li];
+                for (int j = 0; j < WC; ++j) v[j] = Bs[b][kk + lk][wc + 16 * j + li];
 #pragma unroll
                 for (int i = 0; i < W; ++i)
 #pragma unroll
-                    for (int j = 0; j < W; ++j)
+                    for (int j = 0; j < WC; ++j)
                         acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], v[j], acc[i][j], 0, 0, 0);
             }
             if (more) stage(b ^ 1);
@@ -176,7 +179,7 @@ __global__ void __launch_bounds__(256) expm_gemm(const GemmJob *__restrict__ job
 #pragma unroll
     for (int i = 0; i < W; ++i)
 #pragma unroll
-        for (int j = 0; j < W; ++j)
+        for (int j = 0; j < WC; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = row0 + wr + 16 * i + 4 * r + lk, col = col0 + wc + 16 * j + li;
@@ -343,9 +346,9 @@ int build_expms(const std::vector<Tridiag> &gens, const std::vector<ExpmReq> &re
                     const GemmJob *jobs = d_gemms + S.g0[i] + z;
                     const unsigned t2 = (unsigned)((n + 63) / 64), t1 = (unsigned)((n + 31) / 32);
                     if ((uint64_t)t2 * t2 * nz >= 128)
-                        hipLaunchKernelGGL(expm_gemm<2>, dim3(t2, t2, nz), dim3(256), 0, st, jobs, n);
+                        hipLaunchKernelGGL((expm_gemm<2, 8>), dim3(t2, t2, nz), dim3(512), 0, st, jobs, n);
                     else
-                        hipLaunchKernelGGL(expm_gemm<1>, dim3(t1, t1, nz), dim3(256), 0, st, jobs, n);
+                        hipLaunchKernelGGL((expm_gemm<1, 4>), dim3(t1, t1, nz), dim3(256), 0, st, jobs, n);
                     PR_LAUNCHED();
                 }
         }
