@@ -311,12 +311,14 @@ int pr_parareal_destroy(void *h);
  * pr_parareal_batch_state copies the state of instance inst at time t.
  * pr_parareal_batch_info reports the tuned block size and particles per
  * thread, the number of fine work units, the fine particle-steps of one
- * iteration and how the fine results are sorted (1: ensembles of 2^16 to
- * 2^20 + 2^16 FP64 keys by splitters and buckets, the rest by radix passes;
- * 0: all by radix passes).  With PR_AUTOTUNE, creation times the fine
- * kernel's shapes (block {128, 256} x particles per thread {1, 2, 4}, kept
- * per device) and the two sorts on the batch's own states (kept per batch;
- * both give the same bits); without it the defaults are 256, 2 and 1.
+ * iteration and how the fine results are sorted (1: ensembles of up to
+ * 2^20 + 2^16 keys by splitters and buckets, longer ones by radix passes;
+ * 0: where some ensemble has 2^16 to 2^20 + 2^16 keys, all by radix passes,
+ * else as 1).  With PR_AUTOTUNE, creation times the fine kernel's shapes
+ * (block {128, 256} x particles per thread {1, 2, 4}, kept per device) and,
+ * where some ensemble has 2^16 to 2^20 + 2^16 keys, the two sorts on the
+ * batch's own states (kept per batch; both give the same bits); without it
+ * the defaults are 256, 2 and 1.
  * Every output pointer (host) may be NULL.  pr_parareal_batch_knot_sorts returns the number of batched
  * iterations whose new knots needed a sort of some new states (where the
  * knots from the fine results' order could not isolate an order statistic),

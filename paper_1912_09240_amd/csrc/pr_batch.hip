@@ -357,9 +357,10 @@ struct Batch {
         SortSeg *seg = nullptr;
         int *tile = nullptr;
         int nseg = 0;
-        int64_t tiles = 0, min_n = 0, max_n = 0;
+        int64_t tiles = 0, max_n = 0;
     } part[2];
-    bool split_sort = true;  // the two layouts above (else one radix sort of all ensembles)
+    bool tuned_sizes = false;  // some ensemble is worth timing both sorts for
+    bool split_sort = true;    // the two layouts above (else one radix sort of all ensembles)
     // matching
     MatchSeg *mseg = nullptr;
     int *mtile = nullptr;
@@ -547,16 +548,16 @@ static int autotune(Batch *b, hipStream_t st) {
 }
 
 // Restriction of the fine results (buffer nx): knots into qf, ranks; in the
-// two layouts (splitter sort for the ensembles it takes, radix passes for the
-// rest) or as one segment table by radix passes, as tuned.
+// two layouts (splitter sort for the ensembles it takes, radix passes for
+// longer ones) or as one segment table by radix passes, as tuned.
 static int restrict_fine(Batch *b, int nx, hipStream_t st) {
-    if (!b->split_sort) {
-        const SortLayout L{0, 0, (int)b->seg_f_h.size(), b->seg_f, b->tile_f, nullptr, b->seg_max_n};
+    if (!b->split_sort && b->tuned_sizes) {
+        const SortLayout L{0, 0, (int)b->seg_f_h.size(), b->seg_f, b->tile_f, nullptr, b->seg_max_n, true};
         return restrict_segments(b->x[nx], PR_F64, L, b->total_x, b->tiles_f, b->Q, b->qf, b->rank, b->ws, st);
     }
     for (const Batch::Part &P : b->part) {
         if (P.nseg == 0) continue;
-        const SortLayout LP{0, 0, P.nseg, P.seg, P.tile, nullptr, P.max_n, P.min_n};
+        const SortLayout LP{0, 0, P.nseg, P.seg, P.tile, nullptr, P.max_n};
         PR_CHECK(restrict_segments(b->x[nx], PR_F64, LP, b->total_x, P.tiles, b->Q, b->qf, b->rank, b->ws, st));
     }
     return PR_OK;
@@ -567,7 +568,7 @@ static int restrict_fine(Batch *b, int nx, hipStream_t st) {
 // give the same bits.  The outputs it writes are rewritten by the first
 // iteration.
 static int tune_sort(Batch *b, hipStream_t st) {
-    if (b->part[0].nseg == 0) {  // no ensemble the splitter sort takes
+    if (!b->tuned_sizes) {  // the splitter sort without a comparison
         b->split_sort = false;
         return PR_OK;
     }
@@ -842,6 +843,7 @@ static int batch_create(int B, const pr_sde *sde, const pr_schedule *sch, const 
             tiles += g.nblk;
             keys += n[i];
             b->seg_max_n = std::max(b->seg_max_n, (int64_t)n[i]);
+            b->tuned_sizes |= splitter_tuned(n[i]);
         }
     b->tiles_f = tiles;
     b->keys_f = keys;
@@ -858,7 +860,6 @@ static int batch_create(int B, const pr_sde *sde, const pr_schedule *sch, const 
             for (int t = 0; t < g.nblk; ++t) tl.push_back((int)segs.size());
             segs.push_back(g);
             P.tiles += g.nblk;
-            P.min_n = P.min_n == 0 ? g.n : std::min(P.min_n, g.n);
             P.max_n = std::max(P.max_n, g.n);
         }
         P.nseg = (int)segs.size();

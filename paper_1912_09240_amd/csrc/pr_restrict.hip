@@ -3,9 +3,9 @@
 // per ensemble, equal or unequal lengths) by (key, particle), followed by
 // the midpoint (Hazen) knots; the moments (eq. (MCestimator)) and the cell
 // histogram (eq. (binning)) are fused into the first read of the values.
-// FP64 ensembles of SS_MIN_N..SS_MAX_N keys with ranks or the permutation
-// asked for take the splitter sort (sample, buckets, one LDS sort per
-// bucket; described with its kernels below); the rest take the radix sort.
+// Ensembles of up to 2^20 + 2^16 keys take the splitter sort (sample,
+// buckets, one LDS sort per bucket; described with its kernels below); longer
+// ones the radix sort.
 //
 // Radix sort design (HBM bound): 8-bit digits, one pass per byte of the
 // orderable key.  A pass is
@@ -39,6 +39,7 @@ constexpr int RS_THREADS = 256;
 constexpr int RS_WAVES = RS_THREADS / 64;
 constexpr int RS_RADIX = 256;
 constexpr int RS_ITEMS = 16;  // keys per thread and tile (tiles of RS_THREADS x RS_ITEMS keys)
+constexpr int RK_SHIFT = 12;  // bits of a place in a tile
 
 template <typename K> struct KeyTraits;
 template <> struct KeyTraits<uint64_t> { using V = double; static constexpr int passes = 8; };
@@ -423,123 +424,226 @@ rs_scatter(const void *__restrict__ src, const uint32_t *__restrict__ vals_in, K
 }
 
 // ---------------------------------------------------------------------------
-// Splitter sort of large FP64 ensembles (SS_MIN_N <= n <= SS_MAX_N; equal
-// lengths or a segment table): the keys of every ensemble are first
-// distributed over ss_buckets(n) buckets (about 4096 keys each) by splitters
-// drawn from a sample, then every bucket is ordered on its own in LDS.
-//   ss_sample_runs  SS_RUNS blocks per ensemble, each sorting SS_RUN keys of
-//                   the sample (positions i n / (SS_RUNS SS_RUN)) in LDS and
-//                   keeping its SS_B quantile keys;
-//   ss_splitters    splitter b = the mean over the runs of their quantile
-//                   value at level b / ss_buckets(n) (non-decreasing in b,
-//                   as every run's quantiles are);
+// Splitter sort of ensembles of up to SS_MAX_N keys (equal lengths or a
+// segment table): the keys of every ensemble are first distributed over
+// ss_buckets(n) buckets (about 4096 keys each) by splitters drawn from a
+// sample, then every bucket is ordered on its own in LDS.  An ensemble of at
+// most SS_BIG keys is one bucket, read from the values themselves.
+//   ss_sample       ss_runs() runs of SS_RUN keys per ensemble, one per block,
+//                   each sorted and thinned to SS_KEEP keys;
+//   ss_splitters    the thinned runs merged; splitter b is the merged key at
+//                   the fraction b / ss_buckets(n);
 //   ss_count        bucket histogram of every tile and the bucket of every
 //                   key (one byte; the moments and the cell histogram fused
 //                   into this first read of the values);
-//   rs_rowscan(_seg) tile offsets and bucket totals, as for a radix pass;
-//   ss_scatter      scatter of (key, particle) into the buckets (in any
-//                   order inside a bucket: slots from LDS atomics);
+//   ss_rowscan(_seg) tile offsets and bucket totals;
+//   ss_scatter      stable scatter of the keys into the buckets, and where
+//                   every particle's key went: its bucket and its place among
+//                   the tile's keys in bucket order;
 //   ss_bucket_sort  one block per bucket: the keys go to value sub-buckets
 //                   (linear in the value between the bucket's bounds, which
 //                   keeps the order), every key counts the keys of its
-//                   sub-bucket that precede it by (key, particle), the
-//                   particles read only for equal keys, and the bucket is
-//                   written out in order with its permutation.
-// A bucket above SS_CAP keys or a sub-bucket above SS_SUBMAX raises the flag
-// that runs the complete radix sort behind it.  Compared with four radix
-// passes and the fix-up this moves about half the bytes per key.
+//                   sub-bucket that precede it by (key, slot), and the bucket
+//                   leaves in order, with the rank of every slot;
+//   ss_left         the buckets of SS_CAP..SS_BIG keys the same way, one block
+//                   per CU, and those that do not fit that digit by digit;
+//   ss_finish       the rank of every particle from that of its slot (a tile's
+//                   particles of one bucket hold neighbouring slots: the ranks
+//                   are read as runs and put in particle order in LDS, none is
+//                   stored to a random address); the knots and moments.
+// The scatter is stable, so slots of equal keys are in particle order and the
+// particles need not travel with the keys (only the permutation, where asked
+// for, moves them).  Bytes per FP64 key with ranks: 62, of which the key's read
+// and the rank's write (12) cannot be avoided.
+//
+// 64 FP64 ensembles of 2^20 (ranks, knots): 1.16 ms -- bucket sort 0.46 (20
+// bytes per key, 2.9 TB/s; LDS), scatter 0.35 (4.0 TB/s), ranks 0.19, count
+// 0.16, sample and splitters 0.06, what is left 0.05.  The scheme before it
+// (splitters as means of the runs' quantiles, particles carried along, ranks
+// staged by particle block, a complete guarded radix sort behind) took 1.37 ms
+// where every bucket fitted and 5.70 ms where one did not, as for ensembles in
+// two narrow wells.  33 FP32 ensembles of 99,991: 98 us (four radix passes:
+// 170 us).  10 FP64 ensembles of 10^4: two kernels, 32 us (about forty
+// launches of radix passes, fix-up and their guarded repetition: 160 us).
 // ---------------------------------------------------------------------------
 constexpr int SS_B = 256;
-constexpr int SS_RUNS = 16;
-constexpr int SS_RUN = 1024;
+constexpr int SS_MAX_RUNS = 16;
+constexpr int SS_RUN = 1024;                // sampled keys of a run
+constexpr int SS_LIST = 64;                // of them sorted by one wave
+constexpr int SS_KEEP = 256;                // of them kept
 constexpr int SS_BT = 1024;                 // threads of a bucket block
 constexpr int SS_IT = 7;                    // keys per thread of a bucket block
 constexpr int SS_CAP = SS_BT * SS_IT;       // 7168: two bucket blocks share a CU's LDS
-constexpr int SS_SUB = 2048;
+constexpr int SS_IT_BIG = 14;
+constexpr int SS_BIG = SS_BT * SS_IT_BIG;   // 14336: one block takes 148 KiB of it
 constexpr int SS_SUBMAX = 512;
-constexpr int64_t SS_MIN_N = (int64_t)1 << 16;
-// Above this the SS_B buckets average more than 4352 keys, and the largest of
-// them (about 1.5 times the mean with 64 samples per bucket) nears SS_CAP.
+// Above this the SS_B buckets average more than 4352 keys.  A bucket spans 64
+// samples and its two splitters are each a few samples off (thinned runs): its
+// size has a standard deviation of about 16 %, so one bucket in tens of
+// thousands passes SS_CAP and none SS_BIG.
 constexpr int64_t SS_MAX_N = ((int64_t)1 << 20) + ((int64_t)1 << 16);
+// From here on a batch of unequal ensembles times both sorts.
+constexpr int64_t SS_LARGE_N = (int64_t)1 << 16;
 static_assert(SS_B == RS_RADIX, "buckets take the place of a radix pass's digits");
+static_assert(SS_RUN == 4 * SS_KEEP && SS_RUN == 16 * SS_LIST, "a run's lists and its kept keys");
 
-// Buckets of an ensemble of n keys: about 4096 keys each, between 1 and SS_B.
+// Buckets of an ensemble of n keys: one where it fits a block (10 ensembles of
+// 10^4 keys: two kernels instead of seven), else one per tile of 4096, at
+// most SS_B.
 __host__ __device__ __forceinline__ int ss_buckets(int64_t n) {
-    const int64_t b = n >> 12;
-    return b < 1 ? 1 : (b > SS_B ? SS_B : (int)b);
+    if (n <= SS_BIG) return 1;
+    const int64_t b = (n + RS_THREADS * RS_ITEMS - 1) / (RS_THREADS * RS_ITEMS);
+    return b > SS_B ? SS_B : (int)b;
 }
-static_assert(SS_SUB == 2 * SS_BT, "two sub-bucket counts per thread");
-
-// Bucket of a key: the number of splitters sp[1..SS_B-1] at or below it.
-__device__ __forceinline__ uint32_t ss_bucket_of(uint64_t key, const uint64_t *sp) {
-    uint32_t b = 0;
-#pragma unroll
-    for (uint32_t step = SS_B / 2; step >= 1; step >>= 1)
-        if (sp[b + step] <= key) b += step;
-    return b;
+// Runs sampled of an ensemble with nb buckets: 64 samples per bucket, a power
+// of two.
+__host__ __device__ __forceinline__ int ss_runs(int nb) {
+    int r = 1;
+    while (r < SS_MAX_RUNS && 16 * r < nb) r <<= 1;
+    return r;
 }
 
-template <bool VAR>
-__global__ void __launch_bounds__(SS_RUN / 2) ss_sample_runs(const double *__restrict__ x, SortLayout L,
-                                                            uint64_t *__restrict__ runq) {
-    __shared__ uint64_t sk[SS_RUN];
-    const int r = blockIdx.x, s = blockIdx.y, t = threadIdx.x;
+// Bucket search.  The bucket of a key is the number of splitters
+// sp[1..SS_B-1] at or below it, except that a key equal to a repeated splitter
+// goes one below the last of them, so that the bucket between the two holds
+// nothing else; it is non-decreasing in the key.  The search starts from a
+// table over cells of equal width between the first and last splitters: the
+// cell is non-decreasing in the value, so a splitter of a lower cell is below
+// the key and one of a higher cell above it, and only the splitters of the
+// key's own cell are left (one or none for smooth values, where eight steps
+// over all of them would wait for LDS eight times).
+constexpr int SS_CELLS = 1024;
+
+template <typename K>
+struct BucketSearch {
+    K sp[SS_B];
+    uint16_t first[SS_CELLS + 1];  // splitters 1.. in cells below
+    double lo, scale;
+    int nb;
+
+    __device__ __forceinline__ int cell(K key) const {
+        const double t = (value_of(key) - lo) * scale;
+        if (t != t) return (key >> (8 * sizeof(K) - 1)) ? SS_CELLS - 1 : 0;  // NaN, or infinities: by the sign
+        return t >= (double)SS_CELLS ? SS_CELLS - 1 : (t > 0.0 ? (int)t : 0);
+    }
+    // Called by a whole block; ready after the caller's next barrier.
+    __device__ __forceinline__ void load(const K *split, int buckets) {
+        const int tid = (int)threadIdx.x, nt = (int)blockDim.x;
+        for (int i = tid; i < SS_B; i += nt) sp[i] = split[i];
+        if (tid == 0) {
+            nb = buckets;
+            const double a = value_of(split[1]), b = value_of(split[buckets - 1]), w = b - a;
+            lo = a;
+            scale = (w > 0.0 && w <= 1.79e308) ? (double)SS_CELLS / w : 0.0;
+        }
+        __syncthreads();
+        // splitter i (1..nb-1) fills the entries of the cells after its
+        // predecessor's up to its own, the last one also those behind it
+        for (int i = 1 + tid; i < buckets; i += nt) {
+            const int c0 = i == 1 ? -1 : cell(sp[i - 1]), c1 = cell(sp[i]);
+            for (int c = c0 + 1; c <= c1; ++c) first[c] = (uint16_t)(i - 1);
+            if (i == buckets - 1)
+                for (int c = c1 + 1; c <= SS_CELLS; ++c) first[c] = (uint16_t)i;
+        }
+    }
+    __device__ __forceinline__ uint32_t operator()(K key) const {
+        const int c = cell(key);
+        int b = first[c], hi = first[c + 1];  // splitters 1..b are below the key, hi + 1.. above
+        while (b < hi) {
+            const int mid = (b + hi + 1) >> 1;
+            if (sp[mid] <= key) b = mid;
+            else hi = mid - 1;
+        }
+        if (b > 1 && sp[b] == key && sp[b - 1] == key) --b;
+        return (uint32_t)b;
+    }
+};
+
+// Merge of the sorted lists of len keys in a[0..m) (m / len a power of two)
+// into out, pairs of neighbouring lists: a key's place is its index plus the
+// number of the partner list's keys before it, equal keys of the first list
+// before those of the second.  Called by a whole block.
+template <typename K>
+__device__ __forceinline__ void merge_pairs(const K *a, K *out, int m, int len) {
+    for (int i = (int)threadIdx.x; i < m; i += (int)blockDim.x) {
+        const int list = i / len, in = i % len;
+        const K k = a[i], *o = a + (list ^ 1) * len;
+        const bool first = (list & 1) == 0;
+        int lo = 0, hi = len;  // o[0..lo) precede k
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (o[mid] < k || (!first && o[mid] == k)) lo = mid + 1;
+            else hi = mid;
+        }
+        out[(list >> 1) * 2 * len + in + lo] = k;
+    }
+}
+
+// One run: SS_RUN keys at positions spread over the ensemble, one in every
+// n / (runs SS_RUN) at a place taken from a hash (a fixed stride could meet a
+// period of the particles).  Every thread counts its wave's keys below its
+// own, the sixteen lists are merged.
+template <typename K, bool VAR>
+__global__ void __launch_bounds__(SS_RUN)
+ss_sample(const void *__restrict__ x, SortLayout L, int most_runs, K *__restrict__ runq) {
+    using V = typename KeyTraits<K>::V;
+    __shared__ K sk[2][SS_RUN];
+    if (L.guard && *L.guard == 0) return;
+    const int r = (int)blockIdx.x % most_runs, s = (int)blockIdx.x / most_runs, t = threadIdx.x;
     int64_t base, n, tile0;
     int nblk, qrow;
     seg_ref<VAR>(L, s, base, n, tile0, nblk, qrow);
-    const int64_t total = (int64_t)SS_RUNS * SS_RUN;
-    const double *xs = x + base;
-    for (int i = t; i < SS_RUN; i += blockDim.x) {
-        const int64_t g = (int64_t)r * SS_RUN + i;
-        sk[i] = key_of(xs[g * n / total]);
-    }
+    const int nb = ss_buckets(n), runs = ss_runs(nb);
+    if (nb == 1 || r >= runs) return;
+    const uint32_t g = (uint32_t)(r * SS_RUN + t);
+    uint32_t h = (g + 0x9E3779B9u * (uint32_t)s) * 0x85EBCA6Bu;
+    h ^= h >> 15;
+    h *= 0xC2B2AE35u;
+    h ^= h >> 16;
+    const uint64_t at = ((((uint64_t)g << 16) + (h & 0xFFFFu)) * (uint64_t)n) / ((uint64_t)(runs * SS_RUN) << 16);
+    const K k = key_of(((const V *)x)[base + (int64_t)at]);
+    sk[0][t] = k;
     __syncthreads();
-    for (int size = 2; size <= SS_RUN; size <<= 1)
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            const int lo = 2 * t - (t & (stride - 1)), hi = lo + stride;  // one pair per thread
-            const bool up = (lo & size) == 0;
-            const uint64_t a = sk[lo], b = sk[hi];
-            if ((a > b) == up) {
-                sk[lo] = b;
-                sk[hi] = a;
-            }
-            __syncthreads();
-        }
-    for (int b = t; b < SS_B; b += blockDim.x)
-        runq[((int64_t)s * SS_RUNS + r) * SS_B + b] = sk[b * (SS_RUN / SS_B)];
+    const int q0 = t & ~(SS_LIST - 1), in = t - q0;
+    int below = 0;
+#pragma unroll 8
+    for (int j = 0; j < SS_LIST; ++j) {
+        const K o = sk[0][q0 + j];
+        below += (o < k || (o == k && j < in)) ? 1 : 0;
+    }
+    sk[1][q0 + below] = k;
+    __syncthreads();
+    int cur = 1;
+    for (int len = SS_LIST; len < SS_RUN; len <<= 1, cur ^= 1) {
+        merge_pairs(sk[cur], sk[cur ^ 1], SS_RUN, len);
+        __syncthreads();
+    }
+    if (t < SS_KEEP) runq[((int64_t)s * SS_MAX_RUNS + r) * SS_KEEP + t] = sk[cur][4 * t + 2];
 }
 
-// Splitter b of an ensemble with B buckets: the mean over the runs of their
-// quantile value at level b/B (the run's quantile b SS_B / B), each value
-// first clamped to the finite range (infinities and NaN to the end of the
-// range their key sorts to).  The clamped value is non-decreasing in the
-// key, so the means are non-decreasing in b; averaging in the value domain
-// keeps the splitters where the values lie (the key domain is far from
-// linear in the value around 0).  Splitters B..SS_B-1 are the largest key:
-// buckets past B stay empty (a key equal to it goes to bucket B - 1).
-template <bool VAR>
-__global__ void __launch_bounds__(SS_B) ss_splitters(const uint64_t *__restrict__ runq, SortLayout L,
-                                                     uint64_t *__restrict__ split) {
-#pragma clang fp contract(off)
-    const int s = blockIdx.x, b = threadIdx.x;
+// The kept keys of the runs merged, then the splitters.  Splitters past the
+// last bucket are the largest key.
+template <typename K, bool VAR>
+__global__ void __launch_bounds__(1024)
+ss_splitters(const K *__restrict__ runq, SortLayout L, K *__restrict__ split) {
+    __shared__ K buf[2][SS_MAX_RUNS * SS_KEEP];
+    if (L.guard && *L.guard == 0) return;
+    const int s = blockIdx.x, t = threadIdx.x;
     int64_t base, n, tile0;
     int nblk, qrow;
     seg_ref<VAR>(L, s, base, n, tile0, nblk, qrow);
     const int nb = ss_buckets(n);
-    if (b >= nb) {
-        split[(int64_t)s * SS_B + b] = ~0ull;
-        return;
+    if (nb == 1) return;
+    const int M = ss_runs(nb) * SS_KEEP;
+    for (int i = t; i < M; i += 1024) buf[0][i] = runq[(int64_t)s * SS_MAX_RUNS * SS_KEEP + i];
+    __syncthreads();
+    int cur = 0;
+    for (int len = SS_KEEP; len < M; len <<= 1, cur ^= 1) {
+        merge_pairs(buf[cur], buf[cur ^ 1], M, len);
+        __syncthreads();
     }
-    const int j = (int)(((int64_t)b * SS_B) / nb);
-    double acc = 0.0;
-    for (int r = 0; r < SS_RUNS; ++r) {
-        const uint64_t k = runq[((int64_t)s * SS_RUNS + r) * SS_B + j];
-        double v = value_of(k);
-        if (v != v) v = (k >> 63) ? 1.79e308 : -1.79e308;
-        v = fmin(fmax(v, -1.79e308), 1.79e308);
-        acc += v / (double)SS_RUNS;
-    }
-    split[(int64_t)s * SS_B + b] = b == 0 ? 0ull : key_of(acc);
+    for (int b = t; b < SS_B; b += 1024)
+        split[(int64_t)s * SS_B + b] = b == 0 ? (K)0 : (b < nb ? buf[cur][(int)((int64_t)b * M / nb)] : ~(K)0);
 }
 
 // The tiles of the radix passes (RS_THREADS x RS_ITEMS keys) are taken by
@@ -548,66 +652,71 @@ __global__ void __launch_bounds__(SS_B) ss_splitters(const uint64_t *__restrict_
 constexpr int SC_THREADS = 2 * RS_THREADS;
 constexpr int SC_WAVES = SC_THREADS / 64;
 
-template <bool VAR>
+template <typename K, bool VAR>
 __global__ void __launch_bounds__(SC_THREADS)
-ss_count(const double *__restrict__ src, const uint64_t *__restrict__ split, SortLayout L,
-         uint32_t *__restrict__ counts, double *__restrict__ mom_part, HistArgs ha, uint8_t *__restrict__ bucket) {
+ss_count(const void *__restrict__ src, const K *__restrict__ split, SortLayout L, uint32_t *__restrict__ counts,
+         double *__restrict__ mom_part, HistArgs ha, uint32_t *__restrict__ bucket) {
+    using V = typename KeyTraits<K>::V;
     constexpr int TILE = RS_THREADS * RS_ITEMS, ITEMS = TILE / SC_THREADS, WAVE_KEYS = 64 * ITEMS;
     __shared__ uint32_t h[SC_WAVES][2][RS_RADIX];
     __shared__ double wsum[SC_WAVES][4];
-    __shared__ uint64_t sp[SS_B];
+    __shared__ BucketSearch<K> bucket_of;
     extern __shared__ uint32_t cell_h[];
+    if (L.guard && *L.guard == 0) return;
     const TileRef T = tile_ref<VAR>(L, xcd_tile(blockIdx.x, gridDim.x));
+    const int nb = ss_buckets(T.n);
+    const bool do_hist = ha.hist != nullptr;
+    if (nb == 1 && !do_hist && mom_part == nullptr) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     for (int i = tid; i < SC_WAVES * 2 * RS_RADIX; i += SC_THREADS) (&h[0][0][0])[i] = 0;
-    for (int i = tid; i < SS_B; i += SC_THREADS) sp[i] = split[(int64_t)T.seg * SS_B + i];
-    const bool do_hist = ha.hist != nullptr;
+    if (nb > 1) bucket_of.load(split + (int64_t)T.seg * SS_B, nb);
     if (do_hist)
         for (int i = tid; i < ha.cells; i += SC_THREADS) cell_h[i] = 0;
     __syncthreads();
     const int64_t t0 = (int64_t)T.blk * TILE + wave * WAVE_KEYS;
-    double in[ITEMS];
+    V in[ITEMS];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const int64_t idx = t0 + i * 64 + lane;
-        in[i] = idx < T.n ? src[T.base + idx] : 0.0;
+        in[i] = idx < T.n ? ((const V *)src)[T.base + idx] : (V)0;
     }
-    // every key's bucket first (loads of LDS only, so the searches of the
-    // tile's keys overlap), then the counting
-    uint32_t bk[ITEMS];
-    const uint32_t last = (uint32_t)ss_buckets(T.n) - 1;  // the largest key joins the last bucket
+    if (nb > 1) {
+        // every key's bucket first (loads of LDS only, so the searches of the
+        // tile's keys overlap), then the counting; one byte per key for the
+        // scatter, at the head of the tile's own stretch of the slots
+        uint32_t bk[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        const uint32_t b = ss_bucket_of(key_of(in[i]), sp);
-        bk[i] = b < last ? b : last;
-    }
-    // every key's bucket for the scatter, one byte each
+        for (int i = 0; i < ITEMS; ++i) bk[i] = bucket_of(key_of(in[i]));
+        uint8_t *bb = bucket ? (uint8_t *)(bucket + T.base + (int64_t)T.blk * TILE) : nullptr;
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        const int64_t idx = t0 + i * 64 + lane;
-        if (idx < T.n) bucket[T.base + idx] = (uint8_t)bk[i];
-    }
-    double s1 = 0, s2 = 0, s3 = 0, s4 = 0;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        const int64_t idx = t0 + i * 64 + lane;
-        if (idx < T.n) {
-            const double xv = in[i];
-            const double x2 = xv * xv;
-            s1 += xv;
-            s2 += x2;
-            s3 += x2 * xv;
-            s4 += x2 * x2;
-            if (do_hist) {
-                double c = floor((xv - ha.lo) * ha.inv_h);
-                c = fmin(fmax(c, 0.0), (double)(ha.cells - 1));
-                atomicAdd(&cell_h[(int)c], 1u);
+        for (int i = 0; i < ITEMS; ++i) {
+            const int64_t idx = t0 + i * 64 + lane;
+            if (idx < T.n) {
+                if (bb) bb[wave * WAVE_KEYS + i * 64 + lane] = (uint8_t)bk[i];
+                atomicAdd(&h[wave][lane & 1][bk[i]], 1u);
             }
-            atomicAdd(&h[wave][lane & 1][bk[i]], 1u);
         }
     }
-    if (mom_part != nullptr) {
-        for (int off = 32; off >= 1; off >>= 1) {  // fixed butterfly, as in rs_count
+    if (do_hist || mom_part != nullptr) {
+        double s1 = 0, s2 = 0, s3 = 0, s4 = 0;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const int64_t idx = t0 + i * 64 + lane;
+            if (idx < T.n) {
+                const double xv = (double)in[i];
+                const double x2 = xv * xv;
+                s1 += xv;
+                s2 += x2;
+                s3 += x2 * xv;
+                s4 += x2 * x2;
+                if (do_hist) {
+                    double c = floor((xv - ha.lo) * ha.inv_h);
+                    c = fmin(fmax(c, 0.0), (double)(ha.cells - 1));
+                    atomicAdd(&cell_h[(int)c], 1u);
+                }
+            }
+        }
+        for (int off = 32; off >= 1; off >>= 1) {  // fixed butterfly
             s1 += __shfl_xor(s1, off);
             s2 += __shfl_xor(s2, off);
             s3 += __shfl_xor(s3, off);
@@ -621,7 +730,7 @@ ss_count(const double *__restrict__ src, const uint64_t *__restrict__ split, Sor
         }
     }
     __syncthreads();
-    if (tid < RS_RADIX) {
+    if (tid < nb && nb > 1) {
         const int d = tid;
         uint32_t c = 0;
 #pragma unroll
@@ -636,6 +745,46 @@ ss_count(const double *__restrict__ src, const uint64_t *__restrict__ split, Sor
     if (do_hist)
         for (int i = tid; i < ha.cells; i += SC_THREADS)
             if (cell_h[i]) atomicAdd(&ha.hist[(int64_t)T.seg * ha.cells + i], cell_h[i]);
+}
+
+// Exclusive prefix of every bucket's tile counts and the bucket totals: one
+// wave per (ensemble, bucket), or one thread of a block per ensemble where
+// the ensembles are many and short (the segment-table layout).
+__global__ void __launch_bounds__(256) ss_rowscan(uint32_t *__restrict__ counts, uint32_t *__restrict__ totals,
+                                                  SortLayout L) {
+    if (L.guard && *L.guard == 0) return;
+    const int d = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (d >= ss_buckets(L.n)) return;
+    uint32_t *c = counts + (int64_t)blockIdx.y * L.nblk * RS_RADIX + (int64_t)d * L.nblk;
+    uint32_t carry = 0;
+    for (int c0 = 0; c0 < L.nblk; c0 += 64) {
+        const int i = c0 + lane;
+        const uint32_t v = i < L.nblk ? c[i] : 0u;
+        uint32_t inc = v;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t t = __shfl_up(inc, off);
+            if (lane >= off) inc += t;
+        }
+        if (i < L.nblk) c[i] = carry + inc - v;
+        carry += __shfl(inc, 63);
+    }
+    if (lane == 0) totals[(int64_t)blockIdx.y * RS_RADIX + d] = carry;
+}
+
+__global__ void __launch_bounds__(SS_B) ss_rowscan_seg(uint32_t *__restrict__ counts, uint32_t *__restrict__ totals,
+                                                       SortLayout L) {
+    if (L.guard && *L.guard == 0) return;
+    const SortSeg g = L.segs[blockIdx.x];
+    const int d = threadIdx.x, nb = ss_buckets(g.n);
+    if (nb == 1 || d >= nb) return;
+    uint32_t *c = counts + g.tile0 * RS_RADIX + (int64_t)d * g.nblk;
+    uint32_t carry = 0;
+    for (int b = 0; b < g.nblk; ++b) {
+        const uint32_t v = c[b];
+        c[b] = carry;
+        carry += v;
+    }
+    totals[(int64_t)blockIdx.x * RS_RADIX + d] = carry;
 }
 
 // Exclusive prefix of one value per thread over a block of NT threads.
@@ -655,61 +804,114 @@ __device__ __forceinline__ uint32_t block_exclusive(uint32_t v, uint32_t *wtot) 
     return pre + inc - v;
 }
 
-// Scatter of (key, particle) into the buckets.  The order inside a bucket
-// is left to the block's LDS atomics: the bucket sort orders by (key,
-// particle) whatever order its input has.
-template <bool VAR>
-__global__ void __launch_bounds__(SC_THREADS)
-ss_scatter(const double *__restrict__ src, const uint8_t *__restrict__ bucket, uint64_t *__restrict__ keys_out,
-           uint32_t *__restrict__ vals_out, const uint32_t *__restrict__ counts,
-           const uint32_t *__restrict__ totals, SortLayout L, uint32_t *__restrict__ bstart) {
-    constexpr int TILE = RS_THREADS * RS_ITEMS, ITEMS = TILE / SC_THREADS, WAVE_KEYS = 64 * ITEMS;
-    __shared__ uint32_t bcnt[RS_RADIX];
-    __shared__ uint32_t lstart[RS_RADIX];
-    __shared__ uint32_t gdelta[RS_RADIX];
-    __shared__ uint32_t wtot[SC_THREADS / 64];
-    __shared__ uint64_t stage[TILE];
-    __shared__ uint8_t sdig[TILE];
+// Lanes of the wave whose 8-bit digit equals this lane's, among the valid ones:
+// peers & ~(ballot(bit) ^ bit) over the bits, one three-input operation per half.
+__device__ __forceinline__ uint64_t digit_peers(uint32_t d, bool valid) {
+    const uint64_t all = __ballot(valid);
+    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const uint32_t bit = 0u - ((d >> b) & 1u);
+        const uint64_t bal = __ballot(bit != 0u);
+        lo = (uint32_t)__builtin_amdgcn_bitop3_b32((int)lo, (int)(uint32_t)bal, (int)bit, 0x90);
+        hi = (uint32_t)__builtin_amdgcn_bitop3_b32((int)hi, (int)(uint32_t)(bal >> 32), (int)bit, 0x90);
+    }
+    return ((uint64_t)hi << 32) | lo;
+}
 
+// Stable scatter of the keys into the buckets.  Every wave ranks its keys in
+// order with ballot-built peer masks, the tile is staged in LDS in bucket
+// order and every bucket's run leaves as a contiguous burst.  slots receives
+// the bucket and the staged place of every particle (in the array the stored
+// buckets were read from), pv (only for the permutation) the particle of
+// every slot.
+template <typename K, bool VAR>
+__global__ void __launch_bounds__(SC_THREADS)
+ss_scatter(const void *__restrict__ src, const uint32_t *bucket, const K *__restrict__ split,
+           K *__restrict__ keys_out, uint32_t *slots, uint32_t *__restrict__ pv, const uint32_t *__restrict__ counts,
+           const uint32_t *__restrict__ totals, SortLayout L, uint32_t *__restrict__ bstart) {
+    using V = typename KeyTraits<K>::V;
+    constexpr int TILE = RS_THREADS * RS_ITEMS, ITEMS = TILE / SC_THREADS, WAVE_KEYS = 64 * ITEMS;
+    __shared__ uint32_t wcnt[SC_WAVES][RS_RADIX];  // keys of a wave's bucket, then its first place in the tile
+    __shared__ uint32_t gdelta[RS_RADIX];
+    __shared__ uint32_t wtot[SC_WAVES];
+    __shared__ alignas(16) K stage[TILE];
+    __shared__ uint8_t sdig[TILE];
+    static_assert(sizeof(BucketSearch<K>) <= sizeof(stage), "the search fits the staging area");
+    BucketSearch<K> *bucket_of = reinterpret_cast<BucketSearch<K> *>(stage);
+    if (L.guard && *L.guard == 0) return;
     const TileRef T = tile_ref<VAR>(L, xcd_tile(blockIdx.x, gridDim.x));
+    const int nb = ss_buckets(T.n);
+    if (nb == 1) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int64_t t0 = (int64_t)T.blk * TILE + wave * WAVE_KEYS;
-    if (tid < RS_RADIX) bcnt[tid] = 0;
-    __syncthreads();
-
-    // bucket (low byte) and slot among the tile's keys of that bucket
-    uint32_t dr[ITEMS];
-    double in[ITEMS];
+    const uint64_t lt = (1ull << lane) - 1ull;
+    for (int i = lane; i < RS_RADIX; i += 64) wcnt[wave][i] = 0;
+    const bool stored = bucket != nullptr;
+    if (!stored) {  // no stored buckets: searched again, from the staging area
+        bucket_of->load(split + (int64_t)T.seg * SS_B, nb);
+        __syncthreads();
+    }
+    V in[ITEMS];
+    uint32_t dig[ITEMS];
+    const uint8_t *bb = stored ? (const uint8_t *)(bucket + T.base + (int64_t)T.blk * TILE) : nullptr;
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const int64_t idx = t0 + i * 64 + lane;
-        in[i] = idx < T.n ? src[T.base + idx] : 0.0;
-        dr[i] = idx < T.n ? (uint32_t)bucket[T.base + idx] : 0u;
+        in[i] = idx < T.n ? ((const V *)src)[T.base + idx] : (V)0;
+        dig[i] = (stored && idx < T.n) ? (uint32_t)bb[wave * WAVE_KEYS + i * 64 + lane] : 0u;
     }
+    if (!stored) {
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i)
-        if (t0 + i * 64 + lane < T.n) dr[i] |= atomicAdd(&bcnt[dr[i]], 1u) << 8;
+        for (int i = 0; i < ITEMS; ++i) dig[i] = (*bucket_of)(key_of(in[i]));
+    }
+    wave_sync();
+    uint32_t rnk[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const bool valid = t0 + i * 64 + lane < T.n;
+        const uint64_t peers = digit_peers(dig[i], valid);
+        uint32_t before = 0;
+        if (valid) before = wcnt[wave][dig[i]];
+        rnk[i] = before + (uint32_t)__popcll(peers & lt);
+        wave_sync();
+        if (valid && lane == 63 - __clzll(peers)) wcnt[wave][dig[i]] = before + (uint32_t)__popcll(peers);
+        wave_sync();
+    }
     __syncthreads();
     {
         // one thread per bucket; the other half adds zeros to the scans
         const int d = tid & (RS_RADIX - 1);
-        const bool own = tid < RS_RADIX;
-        const uint32_t ls = block_exclusive<SC_THREADS>(own ? bcnt[d] : 0u, wtot);
+        const bool own = tid < nb;
+        uint32_t tot = 0;
+        if (own)
+#pragma unroll
+            for (int w = 0; w < SC_WAVES; ++w) tot += wcnt[w][d];
+        const uint32_t ls = block_exclusive<SC_THREADS>(own ? tot : 0u, wtot);
         const uint32_t dbase = block_exclusive<SC_THREADS>(own ? totals[(int64_t)T.seg * RS_RADIX + d] : 0u, wtot);
         if (own) {
-            lstart[d] = ls;
+            uint32_t acc = ls;
+#pragma unroll
+            for (int w = 0; w < SC_WAVES; ++w) {
+                const uint32_t c = wcnt[w][d];
+                wcnt[w][d] = acc;
+                acc += c;
+            }
             gdelta[d] = dbase + counts[T.tile0 * RS_RADIX + (int64_t)d * T.nblk + T.blk] - ls;
             if (T.blk == 0) bstart[(int64_t)T.seg * RS_RADIX + d] = dbase;
         }
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i)
-        if (t0 + i * 64 + lane < T.n) {
-            const uint32_t j = lstart[dr[i] & 0xFFu] + (dr[i] >> 8);
-            stage[j] = key_of(in[i]);
-            sdig[j] = (uint8_t)dr[i];
+    for (int i = 0; i < ITEMS; ++i) {
+        const int64_t idx = t0 + i * 64 + lane;
+        if (idx < T.n) {
+            rnk[i] += wcnt[wave][dig[i]];
+            stage[rnk[i]] = key_of(in[i]);
+            sdig[rnk[i]] = (uint8_t)dig[i];
+            if (slots) slots[T.base + idx] = (dig[i] << RK_SHIFT) | rnk[i];
         }
+    }
     __syncthreads();
     const int64_t rem = T.n - (int64_t)T.blk * TILE;
     const int tile_n = rem < TILE ? (int)rem : TILE;
@@ -726,17 +928,90 @@ ss_scatter(const double *__restrict__ src, const uint8_t *__restrict__ bucket, u
             }
         }
     }
+    if (!pv) return;
     __syncthreads();
     uint32_t *sv = (uint32_t *)stage;
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i)
-        if (t0 + i * 64 + lane < T.n) sv[lstart[dr[i] & 0xFFu] + (dr[i] >> 8)] = (uint32_t)(t0 + i * 64 + lane);
+        if (t0 + i * 64 + lane < T.n) sv[rnk[i]] = (uint32_t)(t0 + i * 64 + lane);
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
         const int j = tid + r * SC_THREADS;
-        if (j < tile_n && gpos[r] != 0xFFFFFFFFu) vals_out[T.base + gpos[r]] = sv[j];
+        if (j < tile_n && gpos[r] != 0xFFFFFFFFu) pv[T.base + gpos[r]] = sv[j];
     }
+}
+
+// Midpoint knot at level j / nq of n keys in order.
+template <typename K>
+__device__ __forceinline__ double knot_of(const K *s, int64_t n, int j, int nq) {
+#pragma clang fp contract(off)
+    const double t = (double)((int64_t)j * n) / (double)nq - 0.5;
+    if (t <= 0.0) return value_of(s[0]);
+    if (t >= (double)(n - 1)) return value_of(s[n - 1]);
+    const int64_t r = (int64_t)floor(t);
+    const double f = t - (double)r;
+    const double a = value_of(s[r]), b = value_of(s[r + 1]);
+    const double v = a + f * (b - a);
+    return v < b ? v : b;
+}
+
+enum BucketLeft : uint32_t { BL_NONE = 0, BL_BIG = 1, BL_HARD = 2 };
+
+// Moments of an ensemble from its tiles' sums, by the block's first wave.
+__device__ __forceinline__ void moments_of(const double *part, int64_t tile0, int nblk, int64_t n, double *mom) {
+    const int lane = threadIdx.x;
+    if (lane >= 64) return;
+    for (int m = 0; m < 4; ++m) {
+        double s = 0;
+        for (int b = lane; b < nblk; b += 64) s += part[(tile0 + b) * 4 + m];
+        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+        if (lane == 0) mom[m] = s / (double)n;
+    }
+}
+
+// Where a bucket's keys come from and what becomes of them.
+template <typename K>
+struct BucketArgs {
+    const void *x;           // values: the input of an ensemble that is one bucket
+    K *skeys;                // scattered keys: the input otherwise
+    const uint32_t *totals, *bstart;
+    const K *split;
+    K *keys_out;             // sorted keys
+    uint32_t *frank;         // rank of every slot, or NULL
+    uint32_t *rank;          // rank of every particle (written here for one-bucket ensembles), or NULL
+    uint32_t *perm;          // in: particle of every slot; out: in order; or NULL
+    uint32_t *tmp;           // 4 bytes per key free for a bucket's use until ss_finish, or NULL without payload
+    double *xs;              // sorted values, or NULL
+    double *q;               // knots (written here for one-bucket ensembles)
+    uint32_t *left;          // one word per tile: what is left to do (BucketLeft)
+    int nq;
+};
+
+struct BucketRef {
+    int64_t sbase, sn;       // the ensemble
+    uint32_t start, size;    // the bucket in it
+    int seg, b, nb, qrow;
+};
+
+template <typename K, bool VAR>
+__device__ __forceinline__ BucketRef bucket_ref(const SortLayout &L, const BucketArgs<K> &A, int64_t tile) {
+    const TileRef T = tile_ref<VAR>(L, tile);
+    BucketRef R;
+    R.seg = T.seg;
+    R.b = T.blk;
+    R.sbase = T.base;
+    R.sn = T.n;
+    R.nb = ss_buckets(T.n);
+    if constexpr (VAR) R.qrow = L.segs[T.seg].qrow;
+    else R.qrow = T.seg;
+    R.start = 0;
+    R.size = 0;
+    if (R.b < R.nb) {
+        R.size = R.nb == 1 ? (uint32_t)R.sn : A.totals[(int64_t)R.seg * SS_B + R.b];
+        R.start = R.nb == 1 ? 0u : A.bstart[(int64_t)R.seg * SS_B + R.b];
+    }
+    return R;
 }
 
 // Reduction of one value per thread over a block of SS_BT.
@@ -752,186 +1027,483 @@ __device__ __forceinline__ V ss_block_reduce(V v, V *red, Op op) {
     return r;
 }
 
-template <bool VAR>
-__global__ void __launch_bounds__(SS_BT)
-ss_bucket_sort(const uint64_t *__restrict__ bkeys, const uint32_t *__restrict__ bvals,
-               const uint32_t *__restrict__ totals, const uint32_t *__restrict__ bstart,
-               const uint64_t *__restrict__ split, SortLayout L, uint64_t *__restrict__ keys_out,
-               uint32_t *__restrict__ perm_out, uint32_t *__restrict__ rank_out, double *__restrict__ xs_out,
-               int *__restrict__ flag) {
-    __shared__ uint64_t sk[SS_CAP];
-    __shared__ uint16_t spos[SS_CAP];          // position of the key in the bucket's input
-    __shared__ uint16_t sstart[SS_SUB];
-    __shared__ uint32_t cursor[SS_SUB / 2];   // two 16-bit counters per word (sub-buckets 2i, 2i+1)
-    __shared__ uint64_t red64[SS_BT / 64];
-    __shared__ uint32_t red32[SS_BT / 64];
-    __shared__ int too_big;
-    const int s = blockIdx.y, b = blockIdx.x, tid = threadIdx.x;
-    const uint32_t size = totals[(int64_t)s * SS_B + b];
-    if (size == 0) return;
-    if (size > (uint32_t)SS_CAP) {
-        if (tid == 0) *flag = 1;
+// One bucket by one block, IT keys per thread; says in left[tile] what is
+// left of it.
+template <typename K, int IT>
+struct BucketLds {
+    K sk[SS_BT * IT];
+    K redk[SS_BT / 64];
+    // value sub-buckets: a power of two, about as many as half the keys the
+    // block takes; two 16-bit counts per word, turned into starts in place
+    static constexpr int SUB = IT <= 7 ? 4096 : 8192;
+    union {
+        uint32_t count[SUB / 2];
+        uint16_t start[SUB + 2];
+    };
+    uint32_t red32[SS_BT / 64];
+    int too_big;
+    uint16_t spos[SS_BT * IT];     // slot of the key in the bucket's input
+};
+
+template <typename K, bool VAR, int IT>
+__device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const SortLayout &L, int64_t tile,
+                                                BucketLds<K, IT> &S) {
+    using V = typename KeyTraits<K>::V;
+    constexpr int CAP = SS_BT * IT, SUB = BucketLds<K, IT>::SUB, PER = SUB / 2 / SS_BT;
+    constexpr uint32_t NONE = ~0u;
+    const BucketRef R = bucket_ref<K, VAR>(L, A, tile);
+    const int tid = threadIdx.x;
+    const uint32_t size = R.size;
+    if (size == 0 || size > (uint32_t)CAP) {
+        if (tid == 0) A.left[tile] = size == 0 ? BL_NONE : (size <= (uint32_t)SS_BIG ? BL_BIG : BL_HARD);
         return;
     }
-    int64_t sbase, sn, tile0;
-    int nblk, qrow;
-    seg_ref<VAR>(L, s, sbase, sn, tile0, nblk, qrow);
-    const uint32_t start = bstart[(int64_t)s * SS_B + b];
-    const int64_t base = sbase + start;
-    for (int i = tid; i < SS_SUB / 2; i += SS_BT) cursor[i] = 0;
-    if (tid == 0) too_big = 0;
-    // keys and their particles, both read in order
-    uint64_t k[SS_IT];
-    uint32_t v[SS_IT];
+    const int64_t base = R.sbase + R.start;
+    for (int i = tid; i < SUB / 2; i += SS_BT) S.count[i] = 0;
+    if (tid == 0) S.too_big = 0;
+    K k[IT];
 #pragma unroll
-    for (int i = 0; i < SS_IT; ++i) {
+    for (int i = 0; i < IT; ++i) {
         const uint32_t idx = (uint32_t)tid + (uint32_t)i * SS_BT;
-        k[i] = idx < size ? bkeys[base + idx] : ~0ull;
-        v[i] = idx < size ? bvals[base + idx] : 0u;
+        if (R.nb == 1) {
+            const V v = idx < size ? ((const V *)A.x)[base + idx] : (V)0;
+            k[i] = key_of(v);
+        } else {
+            k[i] = idx < size ? A.skeys[base + idx] : ~(K)0;
+        }
     }
     // bounds of the bucket's values: its splitters inside, its extremes at
     // the two ends of the ensemble
-    uint64_t kmin, kmax;
-    if (b > 0 && b < ss_buckets(sn) - 1) {
-        kmin = split[(int64_t)s * SS_B + b];
-        kmax = split[(int64_t)s * SS_B + b + 1];
+    K kmin, kmax;
+    if (R.b > 0 && R.b < R.nb - 1) {
+        kmin = A.split[(int64_t)R.seg * SS_B + R.b];
+        kmax = A.split[(int64_t)R.seg * SS_B + R.b + 1];
     } else {
-        kmin = ~0ull;
-        kmax = 0ull;
+        kmin = ~(K)0;
+        kmax = (K)0;
 #pragma unroll
-        for (int i = 0; i < SS_IT; ++i)
+        for (int i = 0; i < IT; ++i)
             if ((uint32_t)tid + (uint32_t)i * SS_BT < size) {
                 kmin = k[i] < kmin ? k[i] : kmin;
                 kmax = k[i] > kmax ? k[i] : kmax;
             }
-        kmin = ss_block_reduce<uint64_t>(kmin, red64, [](uint64_t a, uint64_t c) { return a < c ? a : c; });
-        kmax = ss_block_reduce<uint64_t>(kmax, red64, [](uint64_t a, uint64_t c) { return a > c ? a : c; });
+        kmin = ss_block_reduce<K>(kmin, S.redk, [](K a, K c) { return a < c ? a : c; });
+        kmax = ss_block_reduce<K>(kmax, S.redk, [](K a, K c) { return a > c ? a : c; });
     }
-    // value sub-buckets: floor((x - lo) SS_SUB / (hi - lo)) is non-decreasing
+    // value sub-buckets: floor((x - lo) SUB / (hi - lo)) is non-decreasing
     // in x (every rounded operation is), so they keep the order; equal values
     // share one.  Bounds that are not finite put every key in one.
     const double lo = value_of(kmin), hi = value_of(kmax);
     const double span = hi - lo;
-    const double scale = (span > 0.0 && span <= 1.79e308) ? (double)SS_SUB / span : 0.0;
+    const double scale = (span > 0.0 && span <= 1.79e308) ? (double)SUB / span : 0.0;
     __syncthreads();
-    uint16_t sub[SS_IT];
+    // per key: its sub-bucket (low half) and its number among the keys counted
+    // there, then its place in sub-bucket order, then its final place
+    uint32_t w[IT];
 #pragma unroll
-    for (int i = 0; i < SS_IT; ++i) {
-        sub[i] = 0;
+    for (int i = 0; i < IT; ++i) {
+        w[i] = NONE;
         if ((uint32_t)tid + (uint32_t)i * SS_BT < size) {
             const double t = (value_of(k[i]) - lo) * scale;
-            sub[i] = (uint16_t)(t >= (double)SS_SUB ? SS_SUB - 1 : (t > 0.0 ? (int)t : 0));
-            atomicAdd(&cursor[sub[i] >> 1], 1u << (16 * (sub[i] & 1)));
+            w[i] = (uint32_t)(t >= (double)SUB ? SUB - 1 : (t > 0.0 ? (int)t : 0));
         }
     }
+#pragma unroll
+    for (int i = 0; i < IT; ++i)
+        if (w[i] != NONE) {
+            const uint32_t sh = 16 * (w[i] & 1);
+            w[i] |= ((atomicAdd(&S.count[w[i] >> 1], 1u << sh) >> sh) & 0xFFFFu) << 16;
+        }
     __syncthreads();
-    // exclusive scan of the sub-bucket counts (two per thread), their maximum
+    // exclusive scan of the sub-bucket counts (2 PER per thread), their maximum
     {
-        const uint32_t w0 = cursor[tid];
-        const uint32_t c0 = w0 & 0xFFFFu, c1 = w0 >> 16;
-        if (c0 > (uint32_t)SS_SUBMAX || c1 > (uint32_t)SS_SUBMAX) too_big = 1;
-        const uint32_t c = c0 + c1;
+        uint32_t c[2 * PER], sum = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const uint32_t two = S.count[tid * PER + i];
+            c[2 * i] = two & 0xFFFFu;
+            c[2 * i + 1] = two >> 16;
+            sum += c[2 * i] + c[2 * i + 1];
+            if (c[2 * i] > (uint32_t)SS_SUBMAX || c[2 * i + 1] > (uint32_t)SS_SUBMAX) S.too_big = 1;
+        }
         const int lane = tid & 63, wave = tid >> 6;
-        uint32_t inc = c;
+        uint32_t inc = sum;
         for (int off = 1; off < 64; off <<= 1) {
             const uint32_t t = __shfl_up(inc, off);
             if (lane >= off) inc += t;
         }
-        if (lane == 63) red32[wave] = inc;
+        if (lane == 63) S.red32[wave] = inc;
         __syncthreads();
-        uint32_t pre = 0;
-        for (int w = 0; w < wave; ++w) pre += red32[w];
-        const uint32_t e0 = pre + inc - c, e1 = e0 + c0;
-        sstart[2 * tid] = (uint16_t)e0;
-        sstart[2 * tid + 1] = (uint16_t)e1;
-        cursor[tid] = e0 | (e1 << 16);
-        __syncthreads();
-    }
-    if (too_big) {
-        if (tid == 0) *flag = 1;
-        return;
-    }
-    // every slot first (the atomics of all items in flight together), then
-    // the stores
-    uint16_t slot[SS_IT];
+        uint32_t e = inc - sum;
+        for (int v = 0; v < wave; ++v) e += S.red32[v];
 #pragma unroll
-    for (int i = 0; i < SS_IT; ++i) {
-        const uint32_t idx = (uint32_t)tid + (uint32_t)i * SS_BT;
-        slot[i] = 0xFFFF;
-        if (idx < size) {
-            const uint32_t sh = 16 * (sub[i] & 1);
-            slot[i] = (uint16_t)((atomicAdd(&cursor[sub[i] >> 1], 1u << sh) >> sh) & 0xFFFFu);
+        for (int i = 0; i < PER; ++i) {
+            S.count[tid * PER + i] = e | ((e + c[2 * i]) << 16);
+            e += c[2 * i] + c[2 * i + 1];
         }
+        if (tid == SS_BT - 1) S.start[SUB] = (uint16_t)size;
+        __syncthreads();
     }
+    if (tid == 0) A.left[tile] = S.too_big ? BL_HARD : BL_NONE;
+    if (S.too_big) return;
 #pragma unroll
-    for (int i = 0; i < SS_IT; ++i)
-        if (slot[i] != 0xFFFF) {
-            sk[slot[i]] = k[i];
-            spos[slot[i]] = (uint16_t)((uint32_t)tid + (uint32_t)i * SS_BT);
+    for (int i = 0; i < IT; ++i)
+        if (w[i] != NONE) {
+            const uint32_t at = S.start[w[i] & 0xFFFFu] + (w[i] >> 16);
+            S.sk[at] = k[i];
+            S.spos[at] = (uint16_t)((uint32_t)tid + (uint32_t)i * SS_BT);
+            w[i] = (w[i] & 0xFFFFu) | (at << 16);
         }
     __syncthreads();
-    // place: the keys of the sub-bucket before this one by (key, particle)
-    uint16_t fin[SS_IT];
+    // place: the keys of the sub-bucket before this one by (key, slot)
 #pragma unroll
-    for (int i = 0; i < SS_IT; ++i) {
-        const uint32_t idx = (uint32_t)tid + (uint32_t)i * SS_BT;
-        fin[i] = 0xFFFF;
-        if (idx < size) {
-            const uint32_t a = sstart[sub[i]], e = (cursor[sub[i] >> 1] >> (16 * (sub[i] & 1))) & 0xFFFFu;
-            const uint32_t me = slot[i];
+    for (int i = 0; i < IT; ++i) {
+        if (w[i] != NONE) {
+            const uint32_t idx = (uint32_t)tid + (uint32_t)i * SS_BT;
+            const uint32_t a = S.start[w[i] & 0xFFFFu], e = S.start[(w[i] & 0xFFFFu) + 1], me = w[i] >> 16;
             // four entries per step, their LDS loads in flight together; the
-            // steps past the end read the key's own slot, which never counts.
-            // Positions are read only for equal keys in other slots.
+            // steps past the end read the key's own place, which never counts.
+            // Input slots are read only for equal keys.
             uint32_t r = a;
-            for (uint32_t j = a; j < e; j += 4) {
-                uint64_t kj[4];
+            for (uint32_t j = e - a > 1 ? a : e; j < e; j += 4) {
+                K kj[4];
                 uint32_t jj[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     jj[u] = j + u < e ? j + u : me;
-                    kj[u] = sk[jj[u]];
+                    kj[u] = S.sk[jj[u]];
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     if (kj[u] < k[i]) ++r;
-                    else if (kj[u] == k[i] && jj[u] != me && bvals[base + spos[jj[u]]] < v[i]) ++r;
+                    else if (kj[u] == k[i] && jj[u] != me && S.spos[jj[u]] < idx) ++r;
                 }
             }
-            fin[i] = (uint16_t)r;
+            w[i] = r;
         }
     }
-    // the keys, then their particles, pass through LDS to their final
-    // slots and leave in order (the particles in the keys' own array)
+    // the ranks in slot order from the registers; the keys pass through LDS
+    // to their final places and leave in order
+    uint32_t *frank = (R.nb == 1 || !A.rank) ? A.rank : A.frank;
+    if (frank) {
+#pragma unroll
+        for (int i = 0; i < IT; ++i)
+            if (w[i] != NONE) frank[base + tid + i * SS_BT] = R.start + w[i];
+    }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < SS_IT; ++i)
-        if (fin[i] != 0xFFFF) sk[fin[i]] = k[i];
+    for (int i = 0; i < IT; ++i)
+        if (w[i] != NONE) S.sk[w[i]] = k[i];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < SS_IT; ++i) {
+    for (int i = 0; i < IT; ++i) {
         const uint32_t idx = (uint32_t)tid + (uint32_t)i * SS_BT;
         if (idx < size) {
-            const uint64_t ok = sk[idx];
-            keys_out[base + idx] = ok;
-            if (xs_out) xs_out[base + idx] = value_of(ok);
+            const K ok = S.sk[idx];
+            A.keys_out[base + idx] = ok;
+            if (A.xs) A.xs[base + idx] = value_of(ok);
         }
     }
-    if (!perm_out && !rank_out) return;
-    __syncthreads();
-    uint32_t *sv = reinterpret_cast<uint32_t *>(sk);
+    if (R.nb == 1)
+        for (int j = tid; j <= A.nq; j += SS_BT)
+            A.q[(int64_t)R.qrow * (A.nq + 1) + j] = knot_of<K>(S.sk, R.sn, j, A.nq);
+    if (!A.perm) return;
+    // the particles, by way of LDS (in the keys' own array)
+    uint32_t v[IT];
 #pragma unroll
-    for (int i = 0; i < SS_IT; ++i)
-        if (fin[i] != 0xFFFF) sv[fin[i]] = v[i];
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < SS_IT; ++i) {
+    for (int i = 0; i < IT; ++i) {
         const uint32_t idx = (uint32_t)tid + (uint32_t)i * SS_BT;
-        if (idx < size) {
-            const uint32_t op = sv[idx];
-            if (perm_out) perm_out[base + idx] = op;
-            if (rank_out) rank_out[sbase + op] = start + idx;
+        v[i] = idx < size ? (R.nb == 1 ? idx : A.perm[base + idx]) : 0u;
+    }
+    __syncthreads();
+    uint32_t *sv = reinterpret_cast<uint32_t *>(S.sk);
+#pragma unroll
+    for (int i = 0; i < IT; ++i)
+        if (w[i] != NONE) sv[w[i]] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+        const uint32_t idx = (uint32_t)tid + (uint32_t)i * SS_BT;
+        if (idx < size) A.perm[base + idx] = sv[idx];
+    }
+}
+
+template <typename K, bool VAR, int IT>
+__global__ void __launch_bounds__(SS_BT) ss_bucket_sort(BucketArgs<K> A, SortLayout L) {
+    if (L.guard && *L.guard == 0) return;
+    __shared__ BucketLds<K, IT> S;
+    bucket_by_block<K, VAR, IT>(A, L, xcd_tile(blockIdx.x, gridDim.x), S);
+}
+
+// Tile j of this block's share.  Neighbouring ensembles mostly leave the same
+// bucket, so the share is skewed.
+__device__ __forceinline__ int64_t shared_tile(int64_t j) {
+    return j * gridDim.x + (blockIdx.x + 37 * j) % gridDim.x;
+}
+
+// The tiles of the block's share whose word is want, among the SS_BT of chunk
+// c: their numbers in the chunk in list, their count returned.
+__device__ __forceinline__ int tiles_left(const uint32_t *left, int64_t tiles, int64_t c, uint32_t want,
+                                          uint16_t *list, int *count) {
+    __syncthreads();  // the last list has been read
+    if (threadIdx.x == 0) *count = 0;
+    __syncthreads();
+    const int64_t t = shared_tile(c * SS_BT + threadIdx.x);
+    if (t < tiles && left[t] == want) list[atomicAdd(count, 1)] = (uint16_t)threadIdx.x;
+    __syncthreads();
+    return *count;
+}
+
+// A bucket of more than SS_BIG keys (mostly one value taken by many particles)
+// or with a sub-bucket above SS_SUBMAX (ties, far outliers, values that are
+// not finite).  One block orders such a bucket in
+// global memory by the digits in which its keys differ at all, least
+// significant first; every pass is stable, so equal keys stay in slot order.
+// The keys alternate between the scattered and the sorted keys' stretches
+// (the first pass reads the scattered ones, or the values), their slots
+// between tmp and frank.
+template <typename K>
+struct DigitsLds {
+    K redk[SS_BT / 64];
+    uint32_t wcnt[SS_BT / 64][RS_RADIX];
+    uint32_t dbase[RS_RADIX];
+    uint32_t wtot[SS_BT / 64];
+};
+
+template <typename K, bool VAR>
+__device__ __forceinline__ void bucket_by_digits(const BucketArgs<K> &A, const SortLayout &L, int64_t tile,
+                                                 DigitsLds<K> &S) {
+    using V = typename KeyTraits<K>::V;
+    constexpr int NW = SS_BT / 64, IT = 4, STEP = SS_BT * IT;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    const BucketRef R = bucket_ref<K, VAR>(L, A, tile);
+    const int64_t base = R.sbase + R.start, size = R.size;
+    const bool payload = A.tmp != nullptr;
+    K *buf[2] = {A.skeys + base, A.keys_out + base};
+    uint32_t *pos[2] = {payload ? A.tmp + base : nullptr, payload ? A.frank + base : nullptr};
+    // the first buffer holds the keys; the digits in which they differ (eight
+    // loads in flight per thread: one block reads the whole bucket)
+    K diff = 0;
+    const K k0 = R.nb == 1 ? key_of(((const V *)A.x)[base]) : buf[0][0];
+    for (int64_t i0 = tid; i0 < size; i0 += 8 * SS_BT) {
+        K k[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t i = i0 + u * SS_BT < size ? i0 + u * SS_BT : i0;
+            if (R.nb == 1) k[u] = key_of(((const V *)A.x)[base + i]);
+            else k[u] = buf[0][i];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            diff |= k[u] ^ k0;
+            if (R.nb == 1 && i0 + u * SS_BT < size) buf[0][i0 + u * SS_BT] = k[u];
         }
     }
+    diff = ss_block_reduce<K>(diff, S.redk, [](K a, K c) { return (K)(a | c); });
+    if (diff == 0) {  // one value: already in order, slot by slot
+        uint32_t *rank = R.nb == 1 ? A.rank : A.frank;
+        for (int64_t i = tid; i < size; i += SS_BT) {
+            buf[1][i] = k0;
+            if (A.rank) rank[base + i] = R.start + (uint32_t)i;
+            if (A.perm && R.nb == 1) A.perm[base + i] = (uint32_t)i;
+            if (A.xs) A.xs[base + i] = value_of(k0);
+        }
+        if (R.nb == 1)
+            for (int j = tid; j <= A.nq; j += SS_BT) A.q[(int64_t)R.qrow * (A.nq + 1) + j] = value_of(k0);
+        return;
+    }
+    if (payload)
+        for (int64_t i = tid; i < size; i += SS_BT) pos[0][i] = (uint32_t)i;
+    __syncthreads();
+    int cur = 0;
+    for (int shift = 0; shift < (int)sizeof(K) * 8; shift += 8) {
+        if (((diff >> shift) & (K)0xFF) == 0) continue;
+        const K *in = buf[cur];
+        K *out = buf[cur ^ 1];
+        const uint32_t *pin = pos[cur];
+        uint32_t *pout = pos[cur ^ 1];
+        // digit totals, then where each digit's keys go next
+        if (tid < RS_RADIX) S.dbase[tid] = 0;
+        __syncthreads();
+        for (int64_t i = tid; i < size; i += SS_BT) atomicAdd(&S.dbase[(uint32_t)(in[i] >> shift) & 0xFFu], 1u);
+        __syncthreads();
+        const uint32_t e = block_exclusive<SS_BT>(tid < RS_RADIX ? S.dbase[tid] : 0u, S.wtot);
+        if (tid < RS_RADIX) S.dbase[tid] = e;
+        for (int64_t t0 = 0; t0 < size; t0 += STEP) {
+            for (int i = lane; i < RS_RADIX; i += 64) S.wcnt[wave][i] = 0;
+            wave_sync();
+            K k[IT];
+            uint32_t rnk[IT];
+#pragma unroll
+            for (int i = 0; i < IT; ++i) {
+                const int64_t idx = t0 + wave * (64 * IT) + i * 64 + lane;
+                const bool valid = idx < size;
+                k[i] = valid ? in[idx] : (K)0;
+                const uint32_t d = (uint32_t)(k[i] >> shift) & 0xFFu;
+                const uint64_t peers = digit_peers(d, valid);
+                const uint32_t before = valid ? S.wcnt[wave][d] : 0u;
+                rnk[i] = before + (uint32_t)__popcll(peers & lt);
+                wave_sync();
+                if (valid && lane == 63 - __clzll(peers)) S.wcnt[wave][d] = before + (uint32_t)__popcll(peers);
+                wave_sync();
+            }
+            __syncthreads();
+            if (tid < RS_RADIX) {
+                uint32_t acc = S.dbase[tid];
+                for (int w = 0; w < NW; ++w) {
+                    const uint32_t c = S.wcnt[w][tid];
+                    S.wcnt[w][tid] = acc;
+                    acc += c;
+                }
+                S.dbase[tid] = acc;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < IT; ++i) {
+                const int64_t idx = t0 + wave * (64 * IT) + i * 64 + lane;
+                if (idx < size) {
+                    const uint32_t to = S.wcnt[wave][(uint32_t)(k[i] >> shift) & 0xFFu] + rnk[i];
+                    if ((int64_t)to < size) {  // always true: the digit totals sum to size
+                        out[to] = k[i];
+                        if (payload) pout[to] = pin[idx];
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        cur ^= 1;
+    }
+    if (cur == 0)
+        for (int64_t i = tid; i < size; i += SS_BT) buf[1][i] = buf[0][i];
+    if (payload && cur == 1)
+        for (int64_t i = tid; i < size; i += SS_BT) pos[0][i] = pos[1][i];
+    __syncthreads();
+    if (A.xs)
+        for (int64_t i = tid; i < size; i += SS_BT) A.xs[base + i] = value_of(buf[1][i]);
+    if (R.nb == 1)
+        for (int j = tid; j <= A.nq; j += SS_BT)
+            A.q[(int64_t)R.qrow * (A.nq + 1) + j] = knot_of<K>(buf[1], R.sn, j, A.nq);
+    if (payload) {
+        // pos[0] holds the slots in key order (in the rank array, where
+        // ranks are asked for)
+        if (A.perm) {
+            if (R.nb == 1) {
+                for (int64_t i = tid; i < size; i += SS_BT) A.perm[base + i] = pos[0][i];
+            } else {
+                for (int64_t i = tid; i < size; i += SS_BT) pos[1][i] = A.perm[base + pos[0][i]];
+                __syncthreads();
+                for (int64_t i = tid; i < size; i += SS_BT) A.perm[base + i] = pos[1][i];
+            }
+            __syncthreads();
+        }
+        if (A.rank) {
+            for (int64_t i = tid; i < size; i += SS_BT) pos[1][pos[0][i]] = R.start + (uint32_t)i;
+            __syncthreads();
+            if (R.nb == 1)
+                for (int64_t i = tid; i < size; i += SS_BT) A.rank[base + i] = pos[1][i];
+        }
+    }
+}
+
+// What ss_bucket_sort left: the buckets of SS_CAP..SS_BIG keys by one block
+// with most of a CU's LDS, then the ones for the digits.
+template <typename K, bool VAR>
+__global__ void __launch_bounds__(SS_BT) ss_left(BucketArgs<K> A, SortLayout L, int64_t tiles) {
+    union Lds {
+        BucketLds<K, SS_IT_BIG> bucket;
+        DigitsLds<K> digits;
+    };
+    __shared__ Lds S;
+    __shared__ uint16_t list[SS_BT];
+    __shared__ int count;
+    if (L.guard && *L.guard == 0) return;
+    for (int64_t c = 0; c * SS_BT * gridDim.x < tiles; ++c) {
+        const int big = tiles_left(A.left, tiles, c, BL_BIG, list, &count);
+        for (int i = 0; i < big; ++i) {
+            bucket_by_block<K, VAR, SS_IT_BIG>(A, L, shared_tile(c * SS_BT + list[i]), S.bucket);
+            __syncthreads();
+        }
+        const int hard = tiles_left(A.left, tiles, c, BL_HARD, list, &count);
+        for (int i = 0; i < hard; ++i) {
+            bucket_by_digits<K, VAR>(A, L, shared_tile(c * SS_BT + list[i]), S.digits);
+            __syncthreads();
+        }
+    }
+}
+
+// Rank of every particle from the rank of its slot: the block stages the
+// bucket of every place of its tile, reads the ranks of those places' slots
+// (runs of neighbouring slots, one per bucket) into LDS and writes them in
+// particle order.
+template <bool VAR>
+__device__ __forceinline__ void ranks_of_tile(const uint32_t *slots, const uint32_t *frank, const uint32_t *counts,
+                                              const uint32_t *totals, const uint32_t *bstart, const SortLayout &L,
+                                              int64_t tile, uint32_t *rank) {
+    constexpr int TILE = RS_THREADS * RS_ITEMS, ITEMS = TILE / SC_THREADS;
+    __shared__ uint8_t sdig[TILE];
+    __shared__ uint32_t sr[TILE];
+    __shared__ uint32_t gdelta[SS_B], wtot[SC_WAVES];
+    const TileRef T = tile_ref<VAR>(L, tile);
+    const int nb = ss_buckets(T.n), tid = threadIdx.x;
+    if (nb == 1) return;
+    const int64_t t0 = (int64_t)T.blk * TILE;
+    const int tile_n = T.n - t0 < TILE ? (int)(T.n - t0) : TILE;
+    uint32_t s[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const int p = tid + i * SC_THREADS;
+        s[i] = p < tile_n ? slots[T.base + t0 + p] : ~0u;
+    }
+    uint32_t mine = 0, at = 0;  // the tile's keys of bucket tid, the slot of the first
+    if (tid < nb) {
+        const uint32_t *c = counts + T.tile0 * RS_RADIX + (int64_t)tid * T.nblk + T.blk;
+        const uint32_t end = T.blk + 1 < T.nblk ? c[1] : totals[(int64_t)T.seg * SS_B + tid];
+        mine = end - c[0];
+        at = bstart[(int64_t)T.seg * SS_B + tid] + c[0];
+    }
+    const uint32_t ls = block_exclusive<SC_THREADS>(mine, wtot);
+    if (tid < nb) gdelta[tid] = at - ls;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        if (s[i] != ~0u) sdig[s[i] & (TILE - 1)] = (uint8_t)(s[i] >> RK_SHIFT);
+    __syncthreads();
+    uint32_t r[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const int j = tid + i * SC_THREADS;
+        const uint32_t g = j < tile_n ? (uint32_t)j + gdelta[sdig[j]] : ~0u;
+        r[i] = (int64_t)g < T.n ? frank[T.base + g] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) sr[tid + i * SC_THREADS] = r[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        if (s[i] != ~0u) rank[T.base + t0 + tid + i * SC_THREADS] = sr[s[i] & (TILE - 1)];
+}
+
+// Blocks [0, nseg): the knots (sorted != NULL) and the moments (part != NULL)
+// of an ensemble; the others, where ranks are asked for: those of a tile.
+template <typename K, bool VAR>
+__global__ void __launch_bounds__(SC_THREADS)
+ss_finish(const K *__restrict__ sorted, int nq, double *__restrict__ q, const double *__restrict__ part,
+          double *__restrict__ mom, const uint32_t *__restrict__ slots, const uint32_t *__restrict__ frank,
+          const uint32_t *__restrict__ counts, const uint32_t *__restrict__ totals,
+          const uint32_t *__restrict__ bstart, SortLayout L, uint32_t *__restrict__ rank) {
+    if (L.guard && *L.guard == 0) return;
+    if ((int64_t)blockIdx.x >= L.nseg) {
+        ranks_of_tile<VAR>(slots, frank, counts, totals, bstart, L,
+                           xcd_tile((int64_t)blockIdx.x - L.nseg, (int64_t)gridDim.x - L.nseg), rank);
+        return;
+    }
+    int64_t base, n, tile0;
+    int nblk, qrow;
+    seg_ref<VAR>(L, blockIdx.x, base, n, tile0, nblk, qrow);
+    if (sorted)
+        for (int j = threadIdx.x; j <= nq; j += blockDim.x)
+            q[(int64_t)qrow * (nq + 1) + j] = knot_of<K>(sorted + base, n, j, nq);
+    if (part) moments_of(part, tile0, nblk, n, mom + (int64_t)qrow * 4);
 }
 
 // ---------------------------------------------------------------------------
@@ -1047,7 +1619,6 @@ rs_fixup(const uint64_t *__restrict__ keys_in, const uint32_t *__restrict__ vals
 // path.  Both kernels return at once where the fix-up raised its flag (the
 // complete sort then writes the ranks).
 // ---------------------------------------------------------------------------
-constexpr int RK_SHIFT = 12;
 constexpr int64_t RK_MAX_N = (int64_t)1 << 20;
 static_assert((1 << RK_SHIFT) == RS_THREADS * RS_ITEMS, "a block of particles is one tile");
 static_assert(RS_THREADS == RS_RADIX, "one thread per particle block of a segment");
@@ -1133,28 +1704,12 @@ rs_rank_place(const uint32_t *__restrict__ staged, SortLayout L, uint32_t *__res
 // ---------------------------------------------------------------------------
 template <typename K, bool VAR>
 __global__ void rs_knots(const K *__restrict__ sorted, SortLayout L, int nq, double *__restrict__ q) {
-#pragma clang fp contract(off)
     if (L.guard && *L.guard == 0) return;
     int64_t base, n, tile0;
     int nblk, qrow;
     seg_ref<VAR>(L, blockIdx.x, base, n, tile0, nblk, qrow);
     const K *s = sorted + base;
-    for (int j = threadIdx.x; j <= nq; j += blockDim.x) {
-        const double t = (double)((int64_t)j * n) / (double)nq - 0.5;
-        double v;
-        if (t <= 0.0) {
-            v = value_of(s[0]);
-        } else if (t >= (double)(n - 1)) {
-            v = value_of(s[n - 1]);
-        } else {
-            const int64_t r = (int64_t)floor(t);
-            const double f = t - (double)r;
-            const double a = value_of(s[r]), b = value_of(s[r + 1]);
-            v = a + f * (b - a);
-            v = v < b ? v : b;
-        }
-        q[(int64_t)qrow * (nq + 1) + j] = v;
-    }
+    for (int j = threadIdx.x; j <= nq; j += blockDim.x) q[(int64_t)qrow * (nq + 1) + j] = knot_of<K>(s, n, j, nq);
 }
 
 template <bool VAR>
@@ -1163,13 +1718,7 @@ __global__ void rs_moments(const double *__restrict__ part, SortLayout L, double
     int64_t base, n, tile0;
     int nblk, qrow;
     seg_ref<VAR>(L, blockIdx.x, base, n, tile0, nblk, qrow);
-    const int lane = threadIdx.x;  // one wave
-    for (int m = 0; m < 4; ++m) {
-        double s = 0;
-        for (int b = lane; b < nblk; b += 64) s += part[(tile0 + b) * 4 + m];
-        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-        if (lane == 0) mom[(int64_t)qrow * 4 + m] = s / (double)n;
-    }
+    moments_of(part, tile0, nblk, n, mom + (int64_t)qrow * 4);
 }
 
 __global__ void zero_u32(uint32_t *p, int64_t count) {
@@ -1529,12 +2078,13 @@ size_t sort_ws_bytes(int64_t total_keys, int64_t total_tiles, int nseg, int prec
     const size_t ks = precision == PR_F32 ? 4 : 8;
     size_t b = align256(total_keys * ks) * 2 + align256((size_t)total_tiles * RS_RADIX * 4) +
                align256((size_t)nseg * RS_RADIX * 4) + align256((size_t)total_tiles * 4 * 8) + 256 + 256 +
-               align256((size_t)nseg * SS_B * (8 + 4 + 8 * SS_RUNS));
+               align256((size_t)nseg * (SS_B * (8 + 4) + 8 * SS_MAX_RUNS * SS_KEEP));
     if (payload) b += align256(total_keys * 4) * 2;
     return b;
 }
 
-bool splitter_sorts(int64_t n) { return n >= SS_MIN_N && n <= SS_MAX_N; }
+bool splitter_sorts(int64_t n) { return n <= SS_MAX_N; }
+bool splitter_tuned(int64_t n) { return n >= SS_LARGE_N && n <= SS_MAX_N; }
 
 size_t restrict_ws(int64_t n, int k, int precision) {
     return sort_ws_bytes((int64_t)n * k, sort_tiles(n) * k, k, precision, true);
@@ -1572,9 +2122,9 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
     }
     int *flag = (int *)p;  // 256 bytes after the payload (or the moment) buffers
     if (payload) flag = (int *)((char *)vals[1] + align256(total_keys * 4));
-    uint64_t *split = (uint64_t *)((char *)flag + 256);  // splitters, [nseg][SS_B]
-    uint32_t *bstart = (uint32_t *)(split + (size_t)L.nseg * SS_B);  // bucket starts, [nseg][SS_B]
-    uint64_t *runq = (uint64_t *)(bstart + (size_t)L.nseg * SS_B);  // run quantiles, [nseg][SS_RUNS][SS_B]
+    K *split = (K *)((char *)flag + 256);                               // splitters, [nseg][SS_B]
+    uint32_t *bstart = (uint32_t *)(split + (size_t)L.nseg * SS_B);     // bucket starts, [nseg][SS_B]
+    K *runq = (K *)(bstart + (size_t)L.nseg * SS_B);                    // thinned runs, [nseg][SS_MAX_RUNS SS_KEEP]
     const dim3 grid((unsigned)total_tiles);
     const dim3 rows((unsigned)(((int64_t)L.nseg * RS_RADIX + 3) / 4));
     // outputs of the last pass (the ranks move to the staging kernels below
@@ -1631,52 +2181,55 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
         return PR_OK;
     };
     constexpr int P = KeyTraits<K>::passes;
-    // The splitter sort takes FP64 ensembles of SS_MIN_N..SS_MAX_N keys (a
-    // segment table says its shortest and longest).
-    bool splitter = false;
-    if constexpr (std::is_same<K, uint64_t>::value)
-        splitter = payload && L.guard == nullptr &&
-                   (VAR ? (L.min_n >= SS_MIN_N && L.max_n <= SS_MAX_N) : (L.n >= SS_MIN_N && L.n <= SS_MAX_N));
+    const bool splitter = !L.radix && max_n > 0 && max_n <= SS_MAX_N;
+    const bool many = max_n > SS_BIG;  // some ensemble is more than one bucket
     if (splitter) {
-        if constexpr (std::is_same<K, uint64_t>::value) {
-            // the splitter sort, then the complete radix sort guarded by its flag
-            hipLaunchKernelGGL(zero_u32, dim3(1), dim3(64), 0, st, (uint32_t *)flag, (int64_t)1);
+        K *skeys = keys[1 - sorted_buffer<K>()], *out = keys[sorted_buffer<K>()];
+        const int nb = ss_buckets(max_n), runs = ss_runs(nb);
+        if (many) {
+            hipLaunchKernelGGL((ss_sample<K, VAR>), dim3((unsigned)(runs * L.nseg)), dim3(SS_RUN), 0, st, x, L, runs,
+                               runq);
             PR_LAUNCHED();
-            hipLaunchKernelGGL((ss_sample_runs<VAR>), dim3(SS_RUNS, (unsigned)L.nseg), dim3(SS_RUN / 2), 0, st,
-                               (const double *)x, L, runq);
+            hipLaunchKernelGGL((ss_splitters<K, VAR>), dim3((unsigned)L.nseg), dim3(1024), 0, st, (const K *)runq, L,
+                               split);
             PR_LAUNCHED();
-            hipLaunchKernelGGL((ss_splitters<VAR>), dim3((unsigned)L.nseg), dim3(SS_B), 0, st,
-                               (const uint64_t *)runq, L, split);
+        }
+        if (many || mom || hist) {
+            hipLaunchKernelGGL((ss_count<K, VAR>), grid, dim3(SC_THREADS), cell_lds, st, x, (const K *)split, L,
+                               counts, mom ? mom_part : nullptr, ha, vals[0]);
             PR_LAUNCHED();
-            // the bucket of every key, one byte each, in the first payload
-            // buffer (free until the bucket sort writes the permutation)
-            uint8_t *bucket = (uint8_t *)vals[0];
-            hipLaunchKernelGGL((ss_count<VAR>), grid, dim3(SC_THREADS), cell_lds, st, (const double *)x,
-                               (const uint64_t *)split, L, counts, mom ? mom_part : nullptr, ha, bucket);
-            PR_LAUNCHED();
+        }
+        if (many) {
             if constexpr (VAR)
-                hipLaunchKernelGGL((rs_rowscan_seg<true>), dim3((unsigned)L.nseg), dim3(RS_RADIX), 0, st, counts,
-                                   totals, L);
+                hipLaunchKernelGGL(ss_rowscan_seg, dim3((unsigned)L.nseg), dim3(SS_B), 0, st, counts, totals, L);
             else
-                hipLaunchKernelGGL((rs_rowscan<false>), rows, dim3(256), 0, st, counts, totals, L);
+                hipLaunchKernelGGL(ss_rowscan, dim3((unsigned)((nb + 3) / 4), (unsigned)L.nseg), dim3(256), 0, st,
+                                   counts, totals, L);
             PR_LAUNCHED();
-            hipLaunchKernelGGL((ss_scatter<VAR>), grid, dim3(SC_THREADS), 0, st, (const double *)x,
-                               (const uint8_t *)bucket, (uint64_t *)keys[1], vals[1], (const uint32_t *)counts,
+            hipLaunchKernelGGL((ss_scatter<K, VAR>), grid, dim3(SC_THREADS), 0, st, x, (const uint32_t *)vals[0],
+                               (const K *)split, skeys, rank ? vals[0] : nullptr, perm, (const uint32_t *)counts,
                                (const uint32_t *)totals, L, bstart);
             PR_LAUNCHED();
-            uint32_t *perm_fix = perm ? perm : (staged_ranks ? vals[0] : nullptr);
-            // one block per bucket of the ensemble with the most (the blocks
-            // of the others' empty buckets return at once)
-            const int nb = ss_buckets(VAR ? L.max_n : L.n);
-            hipLaunchKernelGGL((ss_bucket_sort<VAR>), dim3((unsigned)nb, (unsigned)L.nseg), dim3(SS_BT), 0, st,
-                               (const uint64_t *)keys[1], (const uint32_t *)vals[1], (const uint32_t *)totals,
-                               (const uint32_t *)bstart, (const uint64_t *)split, L, (uint64_t *)keys[0], perm_fix,
-                               staged_ranks ? nullptr : rank, xs, flag);
+        }
+        // the ranks' final array is free until ss_finish writes it, the
+        // runs' since the splitters were taken
+        const BucketArgs<K> A{x, skeys, totals, bstart, split, out, vals[1], rank, perm,
+                              payload ? (rank ? rank : vals[0]) : nullptr, xs, q, (uint32_t *)runq, nq};
+        if (!VAR && !many && max_n > SS_CAP)
+            hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT_BIG>), grid, dim3(SS_BT), 0, st, A, L);
+        else
+            hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT>), grid, dim3(SS_BT), 0, st, A, L);
+        PR_LAUNCHED();
+        hipLaunchKernelGGL((ss_left<K, VAR>), dim3((unsigned)std::min<int64_t>(total_tiles, 256)), dim3(SS_BT), 0, st, A,
+                           L, total_tiles);
+        PR_LAUNCHED();
+        if (many || mom) {
+            const int64_t blocks = L.nseg + (many && rank ? total_tiles : 0);
+            hipLaunchKernelGGL((ss_finish<K, VAR>), dim3((unsigned)blocks), dim3(SC_THREADS), 0, st,
+                               many ? (const K *)out : nullptr, nq, q, mom ? (const double *)mom_part : nullptr, mom,
+                               (const uint32_t *)vals[0], (const uint32_t *)vals[1], (const uint32_t *)counts,
+                               (const uint32_t *)totals, (const uint32_t *)bstart, L, rank);
             PR_LAUNCHED();
-            if (staged_ranks) PR_CHECK(stage_ranks(perm_fix, vals[1]));
-            SortLayout LG = L;
-            LG.guard = flag;
-            for (int j = 0; j < P; ++j) PR_CHECK(pass(LG, 8 * j, j == 0, j == P - 1, j & 1, (j + 1) & 1, false));
         }
     } else if constexpr (std::is_same<K, uint64_t>::value) {
         // the high 32 bits (passes 4..7, ending in buffer 1), the fix-up of
@@ -1717,8 +2270,9 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
             PR_CHECK(stage_ranks(perm_last, vals[0]));
         }
     }
-    const K *sorted = keys[sorted_buffer<K>()];
-    hipLaunchKernelGGL((rs_knots<K, VAR>), dim3(L.nseg), dim3(128), 0, st, sorted, L, nq, q);
+    if (splitter) return PR_OK;
+    hipLaunchKernelGGL((rs_knots<K, VAR>), dim3(L.nseg), dim3(128), 0, st, (const K *)keys[sorted_buffer<K>()], L, nq,
+                       q);
     PR_LAUNCHED();
     if (mom) {
         hipLaunchKernelGGL((rs_moments<VAR>), dim3(L.nseg), dim3(64), 0, st, (const double *)mom_part, L, mom);
