@@ -141,11 +141,6 @@ __global__ void __launch_bounds__(256) k2m_units(const double *__restrict__ q, c
 }
 
 // E rho for 4 rows of one unit per block, one wave per row.
-__device__ __forceinline__ double row_dot(const double *row, const double *v, int n, int lane) {
-    double acc = lane_row_dot(row, v, n, lane);
-    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
-    return acc;
-}
 
 __global__ void __launch_bounds__(256) apply_units(const double *__restrict__ E, const CoarseUnit *__restrict__ cu,
                                                    const double *__restrict__ rin, double *__restrict__ rout, int n) {
@@ -157,7 +152,7 @@ __global__ void __launch_bounds__(256) apply_units(const double *__restrict__ E,
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r = blockIdx.x * 4 + wave;
     if (r >= n) return;
-    const double acc = row_dot(Es + (int64_t)r * n, rv, n, lane);
+    const double acc = wave_sum(lane_row_dot(Es + (int64_t)r * n, rv, n, lane));
     if (lane == 0) rout[(int64_t)u * n + r] = acc > 0.0 ? acc : 0.0;
 }
 
@@ -173,73 +168,26 @@ __global__ void __launch_bounds__(256) m2k_units(const double *__restrict__ rho,
 
 // Serial chain of one instance per block: q_{k+1}^{n+1} = J(C_n(q_{k+1}^n),
 // q_f^{n+1}, q_c^{*,n+1}); without qf it is the plain coarse pass of the
-// zeroth iteration, q^{n+1} = C_n(q^n).  qn row 0 is copied from q.  A block
-// of CHAIN_THREADS: the product E rho of a link is spread over all its waves,
-// each taking CHAIN_ROWS rows at a time with their loads in flight together,
-// every row summed in the order of the single-instance coarse step.
-constexpr int CHAIN_THREADS = 1024;
-constexpr int CHAIN_ROWS = 4;
-
+// zeroth iteration, q^{n+1} = C_n(q^n).  qn row 0 is copied from q.
 __global__ void __launch_bounds__(CHAIN_THREADS) chain_kernel(const ChainInst *__restrict__ ci, int inst0,
                                                     const CoarseUnit *__restrict__ cu, const double *__restrict__ E,
                                                     const double *__restrict__ q, const double *__restrict__ qf,
                                                     const double *__restrict__ qcs, double *__restrict__ qn,
                                                     GridDev g) {
-#pragma clang fp contract(off)
     extern __shared__ double sh[];
     const int Q1 = g.nq + 1;
-    double *qc = sh;               // Q1: current knots
-    double *c = qc + Q1;           // cells + 1
-    double *rho = c + g.cells + 1;  // cells
-    double *rho2 = rho + g.cells;   // cells
-    double *C = rho2 + g.cells;     // cells + 1
-    double *S = C + g.cells + 1;    // Q1
-    int *SC = (int *)(S + Q1);      // Q1
-    int *vio = SC + Q1;             // Q1
     const ChainInst I = ci[inst0 + blockIdx.x];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int j = threadIdx.x; j < Q1; j += blockDim.x) {
         const double v = q[(int64_t)I.qrow0 * Q1 + j];
-        qc[j] = v;
+        sh[j] = v;
         qn[(int64_t)I.qrow0 * Q1 + j] = v;
     }
     __syncthreads();
     for (int s = 0; s < I.K; ++s) {
         const CoarseUnit U = cu[I.u0 + s];
-        for (int i = 1 + threadIdx.x; i < g.cells; i += blockDim.x) c[i] = cdf_knots(qc, g.nq, edge_at(g, i));
-        __syncthreads();
-        for (int i = threadIdx.x; i < g.cells; i += blockDim.x)
-            rho[i] = (i == 0) ? c[1] : (i == g.cells - 1) ? 1.0 - c[g.cells - 1] : c[i + 1] - c[i];
-        __syncthreads();
-        const double *Es = E + (int64_t)U.e_id * g.cells * g.cells;
-        const int nw = (int)(blockDim.x >> 6);
-        for (int r0 = wave; r0 < g.cells; r0 += nw * CHAIN_ROWS) {
-            const double *rows[CHAIN_ROWS];
-            double acc[CHAIN_ROWS];
-#pragma unroll
-            for (int k = 0; k < CHAIN_ROWS; ++k) {
-                const int r = r0 + k * nw;
-                rows[k] = Es + (int64_t)(r < g.cells ? r : r0) * g.cells;
-            }
-            lane_rows_dot<CHAIN_ROWS, 4>(rows, rho, g.cells, lane, acc);
-#pragma unroll
-            for (int k = 0; k < CHAIN_ROWS; ++k) {
-                double a = acc[k];
-                for (int off = 32; off >= 1; off >>= 1) a += __shfl_xor(a, off);
-                const int r = r0 + k * nw;
-                if (lane == 0 && r < g.cells) rho2[r] = a > 0.0 ? a : 0.0;
-            }
-        }
-        __syncthreads();
-        masses_to_knots_block(rho2, C, g, qc);
-        __syncthreads();
         const int64_t orow = (int64_t)U.out_row * Q1;
-        if (qf) {
-            for (int j = threadIdx.x; j < Q1; j += blockDim.x) qc[j] = qf[orow + j] + (qc[j] - qcs[orow + j]);
-            __syncthreads();
-            pava_block(qc, Q1, S, SC, vio);
-        }
-        for (int j = threadIdx.x; j < Q1; j += blockDim.x) qn[orow + j] = qc[j];
+        chain_link(E + (int64_t)U.e_id * g.cells * g.cells, qf ? qf + orow : nullptr, qf ? qcs + orow : nullptr, g, sh);
+        for (int j = threadIdx.x; j < Q1; j += blockDim.x) qn[orow + j] = sh[j];
         __syncthreads();
     }
 }
@@ -420,10 +368,6 @@ static int upload(T *&dev, const std::vector<T> &h, hipStream_t st) {
     PB_ALLOC(dev, sizeof(T) * std::max<size_t>(1, h.size()));
     if (!h.empty()) PR_HIP(hipMemcpyAsync(dev, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice, st));
     return PR_OK;
-}
-
-static size_t lds_chain(const GridDev &g) {
-    return sizeof(double) * (2 * (g.nq + 1) + 4 * g.cells + 2) + 2 * sizeof(int) * (g.nq + 1);
 }
 
 // Fine units of a given tile size, in decreasing cost.
@@ -654,7 +598,7 @@ static int iterate_once(Batch *b, int mode, hipStream_t st) {
         hipLaunchKernelGGL(m2k_units, dim3(b->total_slices), dim3(256), sizeof(double) * (2 * g.cells + 1), st,
                            (const double *)b->rho_b, (const CoarseUnit *)b->cu, b->qcs, g);
         PR_LAUNCHED();
-        hipLaunchKernelGGL(chain_kernel, dim3(b->B), dim3(CHAIN_THREADS), lds_chain(g), st, (const ChainInst *)b->chain, 0,
+        hipLaunchKernelGGL(chain_kernel, dim3(b->B), dim3(CHAIN_THREADS), chain_lds(g), st, (const ChainInst *)b->chain, 0,
                            (const CoarseUnit *)b->cu, (const double *)b->E, (const double *)b->q,
                            (const double *)b->qf, (const double *)b->qcs, b->qn, g);
         PR_LAUNCHED();
@@ -696,7 +640,7 @@ static int iterate_once(Batch *b, int mode, hipStream_t st) {
             hipLaunchKernelGGL(m2k_units, dim3(K), dim3(256), sizeof(double) * (2 * g.cells + 1), st,
                                (const double *)b->rho_b, cu, b->qcs, g);
             PR_LAUNCHED();
-            hipLaunchKernelGGL(chain_kernel, dim3(1), dim3(CHAIN_THREADS), lds_chain(g), st, (const ChainInst *)b->chain, i,
+            hipLaunchKernelGGL(chain_kernel, dim3(1), dim3(CHAIN_THREADS), chain_lds(g), st, (const ChainInst *)b->chain, i,
                                (const CoarseUnit *)b->cu, (const double *)b->E, (const double *)b->q,
                                (const double *)b->qf, (const double *)b->qcs, b->qn, g);
             PR_LAUNCHED();
@@ -784,11 +728,10 @@ static int batch_create(int B, const pr_sde *sde, const pr_schedule *sch, const 
     std::vector<std::tuple<double, double, double, double>> gen_keys;
     std::vector<Tridiag> gens;
     std::vector<ExpmReq> ereq;
-    // request of (generator, tau) built on a given base, added where there is none yet
-    auto request = [&ereq](int gen, double tau, int base) {
+    auto request = [&ereq](int gen, double tau) {  // added where there is none yet
         for (size_t t = 0; t < ereq.size(); ++t)
-            if (ereq[t].gen == gen && ereq[t].tau == tau && ereq[t].base == base) return (int)t;
-        ereq.push_back(ExpmReq{gen, tau, base});
+            if (ereq[t].gen == gen && ereq[t].tau == tau) return (int)t;
+        ereq.push_back(ExpmReq{gen, tau});
         return (int)ereq.size() - 1;
     };
     for (int i = 0; i < B; ++i) {
@@ -808,16 +751,11 @@ static int batch_create(int B, const pr_sde *sde, const pr_schedule *sch, const 
             gens.push_back(Tridiag{lo, di, up});
         }
         chain.push_back(ChainInst{b->qrow0[i], sch[i].n_slices, (int)cu.size(), 0});
-        // distinct (generator, tau): tau = L dt of this instance, the longer
-        // slices built on the shortest as in a single instance's handle
-        const int K = sch[i].n_slices;
-        auto len = [&](int s) { return slice_begin(sch[i].total_steps, K, s + 1) - slice_begin(sch[i].total_steps, K, s); };
-        int64_t shortest = len(0);
-        for (int s = 1; s < K; ++s) shortest = std::min(shortest, len(s));
-        const int base = request(gid, (double)shortest * sch[i].dt, -1);
-        for (int s = 0; s < K; ++s) {
-            const int eid = len(s) == shortest ? base : request(gid, (double)len(s) * sch[i].dt, base);
-            cu.push_back(CoarseUnit{b->qrow0[i] + s, b->qrow0[i] + s + 1, eid, 0});
+        for (int s = 0; s < sch[i].n_slices; ++s) {
+            const int64_t L = slice_begin(sch[i].total_steps, sch[i].n_slices, s + 1) -
+                              slice_begin(sch[i].total_steps, sch[i].n_slices, s);
+            // distinct (generator, tau): tau = L dt of this instance
+            cu.push_back(CoarseUnit{b->qrow0[i] + s, b->qrow0[i] + s + 1, request(gid, (double)L * sch[i].dt), 0});
         }
     }
     b->chain_h = chain;
@@ -930,7 +868,7 @@ static int batch_create(int B, const pr_sde *sde, const pr_schedule *sch, const 
         PR_CHECK(init_ensemble(&sde[i], seed, b->inst_id[i], ni, b->x[0] + xo_i, b->y[0] + xo_i, st));
         PR_CHECK(restrict_quantiles(b->x[0] + xo_i, PR_F64, ni, 1, b->Q, nullptr, b->q + (int64_t)r0 * (b->Q + 1),
                                     b->rank + xo_i, nullptr, nullptr, nullptr, nullptr, b->ws, st));
-        hipLaunchKernelGGL(chain_kernel, dim3(1), dim3(CHAIN_THREADS), lds_chain(b->g), st, (const ChainInst *)b->chain, i,
+        hipLaunchKernelGGL(chain_kernel, dim3(1), dim3(CHAIN_THREADS), chain_lds(b->g), st, (const ChainInst *)b->chain, i,
                            (const CoarseUnit *)b->cu, (const double *)b->E, (const double *)b->q, nullptr, nullptr,
                            b->q, b->g);
         PR_LAUNCHED();

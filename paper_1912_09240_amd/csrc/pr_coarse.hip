@@ -8,7 +8,6 @@
 // A is tridiagonal; E(tau) is dense and built once per distinct slice length
 // on the device (pr_expm.hip).  Applying E is a batched matrix-vector
 // product (FP64 VALU; the matrix stays in L2/MALL).
-#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -64,8 +63,7 @@ __global__ void __launch_bounds__(256) apply_expm_knots(const double *__restrict
     const int r = blockIdx.x * 4 + wave;
     if (r >= n) return;
     const double *row = Es + (int64_t)r * n;
-    double acc = lane_row_dot(row, rv, n, lane);
-    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+    const double acc = wave_sum(lane_row_dot(row, rv, n, lane));
     if (lane == 0) rout[r] = acc > 0.0 ? acc : 0.0;
 }
 
@@ -82,8 +80,7 @@ __global__ void __launch_bounds__(256) apply_expm(const double *__restrict__ E, 
     const int r = blockIdx.x * 4 + wave;
     if (r >= n) return;
     const double *row = Es + (int64_t)r * n;
-    double acc = lane_row_dot(row, rv, n, lane);
-    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+    const double acc = wave_sum(lane_row_dot(row, rv, n, lane));
     if (lane == 0) rout[(int64_t)s * n + r] = acc > 0.0 ? acc : 0.0;
 }
 
@@ -102,7 +99,7 @@ __global__ void __launch_bounds__(256) masses_to_knots(const double *__restrict_
 // Fused with the Qf of the coarse result: rho is C applied to q_new^n.
 __global__ void __launch_bounds__(256) qf_and_jump(const double *__restrict__ rho, const double *__restrict__ qf,
                                                    const double *__restrict__ qcs, double *__restrict__ q_out,
-                                                   double *__restrict__ qc_out, GridDev g) {
+                                                   GridDev g) {
 #pragma clang fp contract(off)
     extern __shared__ double sh[];
     double *r = sh;
@@ -116,12 +113,33 @@ __global__ void __launch_bounds__(256) qf_and_jump(const double *__restrict__ rh
     masses_to_knots_block(r, C, g, qc);
     __syncthreads();
     for (int j = threadIdx.x; j <= g.nq; j += blockDim.x) {
-        if (qc_out) qc_out[j] = qc[j];
         qc[j] = qf[j] + (qc[j] - qcs[j]);
     }
     __syncthreads();
     pava_block(qc, g.nq + 1, S, SC, vio);
     for (int j = threadIdx.x; j <= g.nq; j += blockDim.x) q_out[j] = qc[j];
+}
+
+// The whole serial chain of K links in one block: qn row 0 is q, row s + 1 the
+// link of slice s (a plain coarse pass without qf, qcs, whose rows 1..K belong
+// to the links).
+__global__ void __launch_bounds__(CHAIN_THREADS) chain_block(const double *__restrict__ E,
+                                                             const int *__restrict__ tau_id, int K,
+                                                             const double *q, const double *__restrict__ qf,
+                                                             const double *__restrict__ qcs, double *qn, GridDev g) {
+    extern __shared__ double sh[];
+    const int Q1 = g.nq + 1;
+    for (int j = threadIdx.x; j < Q1; j += blockDim.x) {
+        sh[j] = q[j];
+        qn[j] = sh[j];
+    }
+    __syncthreads();
+    for (int s = 0; s < K; ++s) {
+        const int64_t row = (int64_t)(s + 1) * Q1;
+        chain_link(E + (int64_t)tau_id[s] * g.cells * g.cells, qf ? qf + row : nullptr, qf ? qcs + row : nullptr, g, sh);
+        for (int j = threadIdx.x; j < Q1; j += blockDim.x) qn[row + j] = sh[j];
+        __syncthreads();
+    }
 }
 
 // The quantile iterator alone on k independent rows of L = Q + 1 knots:
@@ -247,8 +265,7 @@ int coarse_create_tridiag(const std::vector<double> &lo, const std::vector<doubl
         return fail(PR_E_HIP);
     }
     std::vector<ExpmReq> reqs;
-    const int shortest = (int)(std::min_element(lens.begin(), lens.end()) - lens.begin());
-    for (int t = 0; t < c->n_tau; ++t) reqs.push_back(ExpmReq{0, c->taus[t], t == shortest ? -1 : shortest});
+    for (double tau : c->taus) reqs.push_back(ExpmReq{0, tau});
     const int e = build_expms({Tridiag{lo, di, up}}, reqs, I, c->E, st);
     if (e != PR_OK) return fail(e);
     (void)hipGetDevice(&c->device);
@@ -279,17 +296,39 @@ int coarse_step(const Coarse *c, int first, int count, const double *q_in, int i
     return PR_OK;
 }
 
-// One link of the serial chain: q_next = J(C_n(q_cur), q_f, q_cs).
-int coarse_jump(const Coarse *c, int n, const double *q_cur, const double *qf, const double *qcs, double *q_next,
-                double *qc_out, hipStream_t st) {
+// The serial chain of all slices: qn[0] = q, qn[s+1] = J(C_s(qn[s]), qf[s+1],
+// qcs[s+1]), or C_s(qn[s]) without qf (rows of n_q + 1 knots).  One block for
+// the whole chain while one CU reads E of a slice in about the time of two
+// launches: a link of 200 cells takes 12 us (7 of them the product, at 45 GB/s
+// from L2) against 18 us in two launches, one of 256 cells 13 us; 320 cells
+// take 18 us.  Beyond, two launches per link, the product spread over the chip.
+constexpr int CHAIN_CELLS = 256;
+
+int coarse_chain(const Coarse *c, const double *q, const double *qf, const double *qcs, double *qn, hipStream_t st) {
     const GridDev &g = c->g;
-    hipLaunchKernelGGL(apply_expm_knots, dim3((g.cells + 3) / 4), dim3(256),
-                       sizeof(double) * (g.nq + 1 + 2 * g.cells + 1), st, (const double *)c->E,
-                       (const int *)c->tau_id, n, q_cur, c->rho_b, g);
-    PR_LAUNCHED();
-    hipLaunchKernelGGL(qf_and_jump, dim3(1), dim3(256), lds_qf_jump(g), st, (const double *)c->rho_b, qf, qcs, q_next,
-                       qc_out, g);
-    PR_LAUNCHED();
+    const int64_t Q1 = g.nq + 1;
+    if (g.cells <= CHAIN_CELLS && chain_lds(g) <= 65536) {
+        hipLaunchKernelGGL(chain_block, dim3(1), dim3(CHAIN_THREADS), chain_lds(g), st, (const double *)c->E,
+                           (const int *)c->tau_id, c->n_slices, q, qf, qcs, qn, g);
+        PR_LAUNCHED();
+        return PR_OK;
+    }
+    if (q != qn) PR_HIP(hipMemcpyAsync(qn, q, sizeof(double) * Q1, hipMemcpyDeviceToDevice, st));
+    for (int s = 0; s < c->n_slices; ++s) {
+        const double *cur = qn + s * Q1;
+        double *next = qn + (s + 1) * Q1;
+        if (!qf) {
+            PR_CHECK(coarse_step(c, s, 1, cur, (int)Q1, next, (int)Q1, nullptr, st));
+            continue;
+        }
+        hipLaunchKernelGGL(apply_expm_knots, dim3((g.cells + 3) / 4), dim3(256),
+                           sizeof(double) * (g.nq + 1 + 2 * g.cells + 1), st, (const double *)c->E,
+                           (const int *)c->tau_id, s, cur, c->rho_b, g);
+        PR_LAUNCHED();
+        hipLaunchKernelGGL(qf_and_jump, dim3(1), dim3(256), lds_qf_jump(g), st, (const double *)c->rho_b,
+                           qf + (s + 1) * Q1, qcs + (s + 1) * Q1, next, g);
+        PR_LAUNCHED();
+    }
     return PR_OK;
 }
 

@@ -8,27 +8,13 @@
 
 namespace pr {
 
-// One lane's share of a row-vector product (elements lane, lane + 64, ...):
-// the loads of the row run eight ahead of the multiply-adds, whose order stays
-// the element order, so the sum is that of the plain loop.
-__device__ __forceinline__ double lane_row_dot(const double *__restrict__ row, const double *v, int n, int lane) {
-    double acc = 0.0;
-    int j = lane;
-    for (; j + 7 * 64 < n; j += 8 * 64) {
-        double e[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) e[u] = row[j + u * 64];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc = fma(e[u], v[j + u * 64], acc);
-    }
-    for (; j < n; j += 64) acc = fma(row[j], v[j], acc);
-    return acc;
-}
-
-// The lane's shares of R rows at once (row k at rows[k]): every row's
-// multiply-adds run in the element order of lane_row_dot, so each sum has
-// its bits; the loads of U elements of all R rows are issued before any of
-// them is used, R U loads in flight per lane.
+// Row-vector products.  A lane takes the elements lane, lane + 64, ..., in
+// that order.  Elements past the end are read at the last one and not used:
+// a load behind a condition would wait for the one before.
+//
+// The lane's shares of R rows at once (row k at rows[k]); the loads of U
+// elements of all R rows are issued before any of them is used.  The sums do
+// not depend on R and U.
 template <int R, int U>
 __device__ __forceinline__ void lane_rows_dot(const double *const *rows, const double *v, int n, int lane,
                                               double *acc) {
@@ -39,20 +25,64 @@ __device__ __forceinline__ void lane_rows_dot(const double *const *rows, const d
 #pragma unroll
         for (int k = 0; k < R; ++k)
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int j = j0 + u * 64;
-                e[k][u] = j < n ? rows[k][j] : 0.0;
-            }
+            for (int u = 0; u < U; ++u) e[k][u] = rows[k][min(j0 + u * 64, n - 1)];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int j = j0 + u * 64;
-            if (j < n) {
-                const double vj = v[j];
+            const double vj = v[min(j, n - 1)];
 #pragma unroll
-                for (int k = 0; k < R; ++k) acc[k] = fma(e[k][u], vj, acc[k]);
+            for (int k = 0; k < R; ++k) {
+                const double t = fma(e[k][u], vj, acc[k]);
+                acc[k] = j < n ? t : acc[k];
             }
         }
     }
+}
+
+// The lane's share of one row.
+__device__ __forceinline__ double lane_row_dot(const double *__restrict__ row, const double *v, int n, int lane) {
+    const double *rows[1] = {row};
+    double acc[1];
+    lane_rows_dot<1, 8>(rows, v, n, lane, acc);
+    return acc[0];
+}
+
+// One 32-bit word from the lane that a DPP control selects.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)b, CTRL, 0xF, 0xF, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Sum over the wave, the same additions as the butterfly v += v[lane ^ off] for
+// off = 32, 16, 8, 4, 2, 1, in every lane: the first two by swapping halves and
+// rows between two copies, the others by rotations inside rows of 16 (after
+// the step for 8 the row has period 8, and so on, so a rotation by off reads
+// the value of lane ^ off).  No LDS: the butterfly's twelve ds_bpermute per
+// row took most of a link's product E rho.
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma clang fp contract(off)
+    {
+        const long long b = __double_as_longlong(v);
+        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+        v = __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+            __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+    }
+    {
+        const long long b = __double_as_longlong(v);
+        const auto l = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+        v = __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+            __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+    }
+    v += dpp_f64<0x128>(v);  // row_ror:8
+    v += dpp_f64<0x124>(v);
+    v += dpp_f64<0x122>(v);
+    v += dpp_f64<0x121>(v);
+    return v;
 }
 
 // ---------------------------------------------------------------------------
@@ -85,43 +115,66 @@ __device__ inline double cdf_knots(const double *q, int nq, double x) {
     return ((double)lo + t) / (double)nq;
 }
 
+// The value of v in lane l (uniform l) of the wave.
+__device__ __forceinline__ double lane_value(double v, int l) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, l);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // Cell masses -> knots (Qf) of the piecewise-linear cdf with cumulative
 // masses C_i (left to right); level p_j C_I.  A level hit on a flat stretch
 // gives its midpoint; the end knots are the grid ends.  Runs inside one
 // block; C must hold cells + 1 doubles of LDS.
 __device__ inline void masses_to_knots_block(const double *rho, double *C, const GridDev &g, double *q) {
 #pragma clang fp contract(off)
-    // C_{i+1} = C_i + rho_i strictly left to right (the same additions as a
-    // serial loop), done by one wave: each lane holds 16 consecutive masses
-    // in registers and the running sum is handed from lane to lane.
+    // Cumulative masses by one wave, in three nested levels: every lane sums its
+    // own run of consecutive masses, the runs' totals are summed along groups
+    // of 8 lanes, the groups' totals along the wave, and C_{i+1} = start of the
+    // group + (start of the run in it + sum inside the run).  The start of the
+    // next run or group is the last value of this one and every sum is
+    // non-decreasing, so C is, and constant over cells without mass, as a
+    // single running sum would be (the searches below rely on both); 16 + 7 + 8
+    // dependent additions per 1024 cells instead of 1024.
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         if (lane == 0) C[0] = 0.0;
         double carry = 0.0;
         for (int base = 0; base < g.cells; base += 1024) {
-            double v[16];
+            const int m = min(1024, g.cells - base), per = (m + 63) >> 6;
+            double v[16], run = 0.0;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int idx = base + lane * 16 + i;
-                v[i] = idx < g.cells ? rho[idx] : 0.0;
+                const int idx = lane * per + i;
+                v[i] = (i < per && idx < m) ? rho[base + idx] : 0.0;
             }
-            double mine = 0.0;
-            for (int l = 0; l < 64; ++l) {
-                if (lane == l) {
-                    double acc = carry;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        if (base + lane * 16 + i < g.cells) acc = acc + v[i];
-                        v[i] = acc;
-                    }
-                    mine = acc;
+            for (int i = 0; i < 16; ++i)
+                if (i < per) {
+                    run = run + v[i];
+                    v[i] = run;
                 }
-                carry = __shfl(mine, l);
+            // inclusive sums of the totals along the group: lane l commits in
+            // step l mod 8, when the lane before it is final
+            double inc = run;
+#pragma unroll
+            for (int l = 1; l < 8; ++l) {
+                const double t = dpp_f64<0x111>(inc) + run;  // row_shr:1
+                inc = (lane & 7) == l ? t : inc;
+            }
+            const double before = dpp_f64<0x111>(inc);
+            const double in_group = (lane & 7) == 0 ? 0.0 : before;
+            double start = carry;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {
+                carry = carry + lane_value(inc, 8 * w + 7);
+                start = (lane >> 3) > w ? carry : start;
             }
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int idx = base + lane * 16 + i;
-                if (idx < g.cells) C[idx + 1] = v[i];
+                const int idx = lane * per + i;
+                if (i < per && idx < m) C[base + idx + 1] = start + (in_group + v[i]);
             }
         }
     }
@@ -160,14 +213,6 @@ __device__ inline void masses_to_knots_block(const double *rho, double *C, const
         }
         q[j] = v;
     }
-}
-
-// The value of v in lane l (uniform l) of the wave.
-__device__ __forceinline__ double lane_value(double v, int l) {
-    const long long b = __double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, l);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
 // Whether the rounded mean a/ca exceeds the rounded mean b/cb (counts >= 1).
@@ -628,6 +673,68 @@ __device__ inline void pava_block(double *v, int L, double *S, int *SC, int *vio
         for (int t = lane; t < cq; t += wl) v[st + t] = mean;
     }
     __syncthreads();
+}
+
+// ---------------------------------------------------------------------------
+// One link of a serial chain by one block: qc (LDS, the knots q^n) becomes
+// J(C_n(q^n), q_f, q_c^*), or C_n(q^n) without qf.  Es: E of the slice.  The
+// product E rho is spread over all the block's waves, each taking CHAIN_ROWS
+// rows at a time with their loads in flight together.  lds: chain_lds() bytes.  Every thread of the
+// block calls it; the result is complete when it returns.
+// ---------------------------------------------------------------------------
+constexpr int CHAIN_THREADS = 1024;
+constexpr int CHAIN_ROWS = 4;
+
+inline size_t chain_lds(const GridDev &g) {
+    return sizeof(double) * (2 * (g.nq + 1) + 4 * g.cells + 2) + 2 * sizeof(int) * (g.nq + 1);
+}
+
+__device__ inline void chain_link(const double *__restrict__ Es, const double *__restrict__ qf,
+                                  const double *__restrict__ qcs, const GridDev &g, double *lds) {
+#pragma clang fp contract(off)
+    const int Q1 = g.nq + 1;
+    double *qc = lds;               // Q1: current knots
+    double *c = qc + Q1;            // cells + 1
+    double *rho = c + g.cells + 1;  // cells
+    double *rho2 = rho + g.cells;   // cells
+    double *C = rho2 + g.cells;     // cells + 1
+    double *S = C + g.cells + 1;    // Q1
+    int *SC = (int *)(S + Q1);      // Q1
+    int *vio = SC + Q1;             // Q1
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = (int)(blockDim.x >> 6);
+    // the link's other inputs, wanted at its end, on their way from the start
+    const int j0 = threadIdx.x;
+    const double f0 = qf && j0 < Q1 ? qf[j0] : 0.0, s0 = qf && j0 < Q1 ? qcs[j0] : 0.0;
+    for (int i = 1 + threadIdx.x; i < g.cells; i += blockDim.x) c[i] = cdf_knots(qc, g.nq, edge_at(g, i));
+    __syncthreads();
+    for (int i = threadIdx.x; i < g.cells; i += blockDim.x)
+        rho[i] = (i == 0) ? c[1] : (i == g.cells - 1) ? 1.0 - c[g.cells - 1] : c[i + 1] - c[i];
+    __syncthreads();
+    for (int r0 = wave; r0 < g.cells; r0 += nw * CHAIN_ROWS) {
+        const double *rows[CHAIN_ROWS];
+        double acc[CHAIN_ROWS];
+#pragma unroll
+        for (int k = 0; k < CHAIN_ROWS; ++k) {
+            const int r = r0 + k * nw;
+            rows[k] = Es + (int64_t)(r < g.cells ? r : r0) * g.cells;
+        }
+        lane_rows_dot<CHAIN_ROWS, 4>(rows, rho, g.cells, lane, acc);
+#pragma unroll
+        for (int k = 0; k < CHAIN_ROWS; ++k) {
+            const double a = wave_sum(acc[k]);
+            const int r = r0 + k * nw;
+            if (lane == 0 && r < g.cells) rho2[r] = a > 0.0 ? a : 0.0;
+        }
+    }
+    __syncthreads();
+    masses_to_knots_block(rho2, C, g, qc);
+    __syncthreads();
+    if (qf) {
+        if (j0 < Q1) qc[j0] = f0 + (qc[j0] - s0);
+        for (int j = j0 + blockDim.x; j < Q1; j += blockDim.x) qc[j] = qf[j] + (qc[j] - qcs[j]);
+        __syncthreads();
+        pava_block(qc, Q1, S, SC, vio);
+    }
 }
 
 }  // namespace pr

@@ -17,7 +17,6 @@ struct Tridiag {
 struct ExpmReq {
     int gen;     // index of the generator
     double tau;  // time, >= 0
-    int base;    // another request of this generator with a slightly shorter time (and no base of its own), or -1
 };
 
 // out[e] (device, [reqs][n][n] row-major) = exp(gens[reqs[e].gen] reqs[e].tau).

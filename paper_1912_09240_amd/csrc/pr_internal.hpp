@@ -288,8 +288,7 @@ struct Coarse;
 int coarse_create(const pr_sde *sde, const pr_schedule *sch, const pr_grid *grid, hipStream_t st, Coarse **out);
 int coarse_step(const Coarse *c, int first, int count, const double *q_in, int in_stride, double *q_out,
                 int out_stride, double *rho_out, hipStream_t st);
-int coarse_jump(const Coarse *c, int n, const double *q_cur, const double *qf, const double *qcs, double *q_next,
-                double *qc_out, hipStream_t st);
+int coarse_chain(const Coarse *c, const double *q, const double *qf, const double *qcs, double *qn, hipStream_t st);
 int coarse_apply(const Coarse *c, int first, int count, const double *rho_in, double *rho_out, hipStream_t st);
 void coarse_free(Coarse *c);
 

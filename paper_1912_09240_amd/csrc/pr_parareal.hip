@@ -13,6 +13,7 @@
 //   5. matching of every Xbar^{n+1} to q_{k+1}^{n+1} (in place);
 //   6. knots of the new states (next coarse input and the error to a
 //      reference).
+#include <algorithm>
 #include <vector>
 
 #include "pr_internal.hpp"
@@ -89,6 +90,23 @@ __global__ void knot_error(const double *__restrict__ qR, const double *__restri
     }
 }
 
+// Row 0 (words 4-byte words) of a into row 0 of b and rows 1..rows of a.
+__global__ void spread_row(uint32_t *a, uint32_t *__restrict__ b, int64_t words, int rows) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t v = a[i];
+        b[i] = v;
+        for (int r = 1; r <= rows; ++r) a[r * words + i] = v;
+    }
+}
+
+static int spread(char *a, char *b, size_t bytes, int rows, hipStream_t st) {
+    const int64_t words = (int64_t)(bytes / 4);
+    hipLaunchKernelGGL(spread_row, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 4096)), dim3(256), 0, st,
+                       (uint32_t *)a, (uint32_t *)b, words, rows);
+    PR_LAUNCHED();
+    return PR_OK;
+}
+
 #define PR_ALLOC(ptr, bytes)                                                  \
     do {                                                                      \
         if (hipMalloc((void **)&(ptr), (bytes)) != hipSuccess) {              \
@@ -159,21 +177,16 @@ int parareal_create(const pr_sde *sde_in, const pr_schedule *sch, const pr_grid 
 
     // initial ensemble in slot 0 of both buffers
     PR_TRY(init_ensemble(&h->sde, seed, inst, n, h->xs(0, 0), h->ys(0, 0), st));
-    PR_TRY(hipMemcpyAsync(h->xs(1, 0), h->xs(0, 0), (size_t)n * h->esz, hipMemcpyDeviceToDevice, st) == hipSuccess
-               ? PR_OK : PR_E_HIP);
-    PR_TRY(hipMemcpyAsync(h->ys(1, 0), h->ys(0, 0), (size_t)D * n * h->esz, hipMemcpyDeviceToDevice, st) == hipSuccess
-               ? PR_OK : PR_E_HIP);
+    // initial x in both, initial y (which matching leaves alone) also at every later time
+    PR_TRY(spread(h->xs(0, 0), h->xs(1, 0), (size_t)n * h->esz, 0, st));
+    PR_TRY(spread(h->ys(0, 0), h->ys(1, 0), (size_t)D * n * h->esz, K, st));
     // zeroth iteration: q_0^0 = R(X0) (with X0's ranks), q_0^{n+1} = C_n(q_0^n)
     PR_TRY(restrict_quantiles(h->xs(0, 0), h->sde.precision, n, 1, Q, nullptr, h->q, h->rank, nullptr, nullptr,
                               nullptr, nullptr, h->ws, st));
-    for (int s = 0; s < K; ++s)
-        PR_TRY(coarse_step(h->coarse, s, 1, h->qrow(h->q, s), Q + 1, h->qrow(h->q, s + 1), Q + 1, nullptr, st));
-    // X_0^n = M(q_0^n; X0) for n = 1..K; fast variables copied from X0
+    PR_TRY(coarse_chain(h->coarse, h->q, nullptr, nullptr, h->q, st));
+    // X_0^n = M(q_0^n; X0) for n = 1..K
     MatchArgs ma{h->qrow(h->q, 1), Q + 1, h->q, 0, h->rank, 0, h->xs(0, 0), 0, h->xs(0, 1), n};
     PR_TRY(match_strided(ma, n, K, Q, h->sde.precision, st));
-    for (int t = 1; t <= K; ++t)
-        PR_TRY(hipMemcpyAsync(h->ys(0, t), h->ys(0, 0), (size_t)D * n * h->esz, hipMemcpyDeviceToDevice, st) ==
-                       hipSuccess ? PR_OK : PR_E_HIP);
     PR_TRY(restrict_states(h, 0, 0, K + 1, st));
     if (hipStreamSynchronize(st) != hipSuccess) {
         set_error("zeroth iteration failed on the device");
@@ -217,10 +230,7 @@ int parareal_iterate(Parareal *h, int n_iter, const double *q_ref, double *err_o
         PR_CHECK(coarse_step(h->coarse, 0, K, cin, Q + 1, h->qrow(h->qcs, 1), Q + 1, nullptr, st));
         PR_CHECK(mark(3));
         // 4. serial chain
-        PR_HIP(hipMemcpyAsync(h->qn, h->q, sizeof(double) * (Q + 1), hipMemcpyDeviceToDevice, st));
-        for (int s = 0; s < K; ++s)
-            PR_CHECK(coarse_jump(h->coarse, s, h->qrow(h->qn, s), h->qrow(h->qf, s + 1), h->qrow(h->qcs, s + 1),
-                                 h->qrow(h->qn, s + 1), nullptr, st));
+        PR_CHECK(coarse_chain(h->coarse, h->q, h->qf, h->qcs, h->qn, st));
         PR_CHECK(mark(4));
         // 5. matching of the fine results, in place
         MatchArgs ma{h->qrow(h->qn, 1), Q + 1, h->qrow(h->qf, 1), Q + 1, h->rank, n, h->xs(nx, 1), n,
