@@ -213,28 +213,23 @@ __device__ inline double quantile_hist(const double *rho, const double *c, const
     return quantile_hist_ab(rho, c, g, p, lower_bound_d(c, I + 1, p), upper_bound_d(c, I + 1, p) - 1);
 }
 
-// Quantiles at non-decreasing levels by one thread: the edge indices of
-// quantile_hist found once by binary search, then advanced.
-struct QuantileWalk {
-    int a = -1, u = 0;  // first edge with c >= p, first edge with c > p
-    __device__ inline double at(const double *rho, const double *c, const HGrid &g, double p) {
-        const int E = g.cells + 1;
-        p = fmin(fmax(p, 0.0), c[E - 1]);
-        if (a < 0) {
-            a = lower_bound_d(c, E, p);
-            u = upper_bound_d(c, E, p);
-        } else {
-            while (a < E && c[a] < p) ++a;
-            while (u < E && c[u] <= p) ++u;
-        }
-        return quantile_hist_ab(rho, c, g, p, a, u - 1);
-    }
-};
+// Quantile at a level of the union of several histograms' cdfs, of which a
+// edges lie below it and b + 1 not above: levels above the total mass are
+// taken at it.
+__device__ inline double quantile_level(const double *rho, const double *c, const HGrid &g, double p, int a, int b) {
+    const int I = g.cells;
+    if (p > c[I]) return quantile_hist(rho, c, g, p);
+    return quantile_hist_ab(rho, c, g, p, min(max(a, 0), I), min(max(b, 0), I));  // in range for NaN masses, too
+}
 
-// Left-to-right running sums by one wave (lanes of wave 0 call it):
-// out[0] = 0, out[i+1] = out[i] + v(i) for i < n; returns the total to lane 0
-// .. 63.  v is read through a functor so that sums of derived values need no
-// scratch.
+// Left-to-right running sums by one wave: out[0] = 0, out[i+1] = out[i] + v(i)
+// for i < n; returns the total to all lanes.  v (>= 0) is read through a
+// functor so that sums of derived values need no scratch.  Every lane holds
+// 16 consecutive values and adds them when the sum of the lanes before it
+// reaches it; values past the end are 0, which changes no sum, so the
+// additions of a turn follow each other without a test (170 clocks a turn;
+// with a test per addition and the sum handed on through LDS, and turns for
+// lanes without values, 400).
 template <class F>
 __device__ inline double wave_running_sum(F v, int n, double *out) {
 #pragma clang fp contract(off)
@@ -248,18 +243,14 @@ __device__ inline double wave_running_sum(F v, int n, double *out) {
             const int idx = base + lane * 16 + i;
             r[i] = idx < n ? v(idx) : 0.0;
         }
-        double mine = 0.0;
-        for (int l = 0; l < 64; ++l) {
+        const int turns = min(64, (n - base + 15) >> 4);
+        for (int l = 0; l < turns; ++l) {
             if (lane == l) {
-                double acc = carry;
+                r[0] = carry + r[0];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    if (base + lane * 16 + i < n) acc = acc + r[i];
-                    r[i] = acc;
-                }
-                mine = acc;
+                for (int i = 1; i < 16; ++i) r[i] = r[i - 1] + r[i];
             }
-            carry = __shfl(mine, l);
+            carry = lane_value(r[15], l);
         }
         if (out) {
 #pragma unroll
@@ -288,8 +279,16 @@ __global__ void __launch_bounds__(HB_THREADS) hist_count(const double *__restric
     for (int i = threadIdx.x; i < g.cells; i += blockDim.x) hc[i] = 0;
     __syncthreads();
     const double *xs = x + (int64_t)s * stride;
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x)
-        atomicAdd(&hc[hcell(g, xs[p])], 1u);
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    // eight loads in flight per thread (values past the end: the last one, not counted)
+    for (int64_t p0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p0 < n; p0 += 8 * step) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = xs[p0 + u * step < n ? p0 + u * step : n - 1];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (p0 + u * step < n) atomicAdd(&hc[hcell(g, v[u])], 1u);
+    }
     __syncthreads();
     for (int i = threadIdx.x; i < g.cells; i += blockDim.x)
         if (hc[i]) atomicAdd((unsigned long long *)&cnt[(int64_t)s * g.cells + i], (unsigned long long)hc[i]);
@@ -356,7 +355,10 @@ int hist_restrict(const double *x, const double *w, int64_t n, int64_t stride, i
     hipLaunchKernelGGL(zero_u64, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 1024)), dim3(256), 0, st, acc,
                        words);
     PR_LAUNCHED();
-    const int per = (int)std::min<int64_t>(std::max<int64_t>((n + 16383) / 16384, 1), 32);
+    // a block counts at least 4096 particles (16384 with weights): two of its
+    // threads' batches of loads against the cells it adds to the ensemble's
+    const int64_t share = w ? 16384 : 4096;
+    const int per = (int)std::min<int64_t>(std::max<int64_t>((n + share - 1) / share, 1), 32);
     const dim3 grid((unsigned)per, (unsigned)k);
     if (w) {
         hipLaunchKernelGGL(hist_weighted, grid, dim3(HB_THREADS), sizeof(uint64_t) * 4 * g.cells, st, x, w, n, stride,
@@ -456,76 +458,102 @@ __global__ void __launch_bounds__(KIND == PR_J_QUANTILE ? JQ_THREADS : HB_THREAD
         double *lev = (double *)(pC + 2 * T3);          // [3E]
         (void)scratch;
         __shared__ int nU, bad;
+        const int top = 1 << (31 - __clz(E));  // largest step of a search over E edges
         const int wave = threadIdx.x >> 6;
         if (wave == 0) wave_running_sum([&](int i) { return rc[i]; }, I, cc);
         if (wave == 1) wave_running_sum([&](int i) { return rf[i]; }, I, cf);
         if (wave == 2) wave_running_sum([&](int i) { return rcs[i]; }, I, ccs);
         __syncthreads();
-        // stable merge by rank: (value, array, index).  Every thread takes a
-        // contiguous run of one array's (non-decreasing) values; the ranks in
-        // the other two arrays come from one binary search each, then advance.
-        {
-            const int per = (T3 + JQ_THREADS - 1) / JQ_THREADS;
-            const int e0 = threadIdx.x * per, e1 = min(e0 + per, T3);
-            int cur = -1, r1 = 0, r2 = 0;
-            for (int e = e0; e < e1; ++e) {
-                const int arr = e / E, idx = e % E;
-                const double *A = arr == 0 ? cc : arr == 1 ? cf : ccs;
-                const double *B1 = arr == 0 ? cf : cc;   // first other array
-                const double *B2 = arr == 2 ? cf : ccs;  // second other array
-                const double v = A[idx];
-                // ties: an earlier array's equal values come first
-                const bool strict1 = arr == 0;  // B1 later than A: count B1 < v; else B1 <= v
-                const bool strict2 = arr != 2;  // B2 later than A: count B2 < v; else B2 <= v
-                if (arr != cur) {
-                    cur = arr;
-                    r1 = strict1 ? lower_bound_d(B1, E, v) : upper_bound_d(B1, E, v);
-                    r2 = strict2 ? lower_bound_d(B2, E, v) : upper_bound_d(B2, E, v);
-                } else {
-                    if (strict1) while (r1 < E && B1[r1] < v) ++r1;
-                    else while (r1 < E && B1[r1] <= v) ++r1;
-                    if (strict2) while (r2 < E && B2[r2] < v) ++r2;
-                    else while (r2 < E && B2[r2] <= v) ++r2;
-                }
-                merged[idx + r1 + r2] = v;
+        // stable merge by rank: (value, array, index), every value searched for
+        // in the other two arrays (long runs of equal levels, the empty tails,
+        // rule out walking along them); the array of every merged place
+        int *tag = pC + T3;  // [3E], dead once the levels are unique
+        for (int e = threadIdx.x; e < T3; e += JQ_THREADS) {
+            const int arr = e / E, idx = e % E;
+            const double *A = arr == 0 ? cc : arr == 1 ? cf : ccs;
+            const double *B1 = arr == 0 ? cf : cc;   // first other array
+            const double *B2 = arr == 2 ? cf : ccs;  // second other array
+            const double v = A[idx];
+            // ties: an earlier array's equal values come first (of an array
+            // later than A the values below v precede it, else those up to v)
+            const bool strict1 = arr == 0, strict2 = arr != 2;
+            int r1 = 0, r2 = 0;
+            for (int step = top; step > 0; step >>= 1) {
+                const int m1 = min(r1 + step, E), m2 = min(r2 + step, E);
+                const double b1 = B1[m1 - 1], b2 = B2[m2 - 1];
+                if (r1 + step <= E && (b1 < v || (!strict1 && b1 == v))) r1 += step;
+                if (r2 + step <= E && (b2 < v || (!strict2 && b2 == v))) r2 += step;
             }
+            merged[idx + r1 + r2] = v;
+            tag[idx + r1 + r2] = arr;
         }
         __syncthreads();
         // unique levels: compaction of the first of every run of equal values,
-        // every thread owning a contiguous chunk of the merged levels
+        // every thread owning a contiguous chunk of the merged levels.  With
+        // each level, how many edges of every array lie below it: the tags
+        // before its place, counted along.
+        int *below01 = pC, *below2 = tag;
         {
+            constexpr int MOST = (3 * (HB_MAX_CELLS + 1) + JQ_THREADS - 1) / JQ_THREADS;
             const int per = (T3 + JQ_THREADS - 1) / JQ_THREADS;
-            const int i0 = threadIdx.x * per, i1 = min(i0 + per, T3);
-            int cnt = 0;
-            for (int i = i0; i < i1; ++i) cnt += (i == 0 || merged[i] != merged[i - 1]) ? 1 : 0;
-            __shared__ int wsum[JQ_THREADS / 64];
+            const int i0 = min((int)threadIdx.x * per, T3), i1 = min(i0 + per, T3);
+            // counts in 12-bit fields: unique levels, tags 0, tags 1
+            uint64_t cnt = 0;
+            double v[MOST];
+            int tg[MOST];
+#pragma unroll
+            for (int t = 0; t < MOST; ++t) {
+                const int i = i0 + t;
+                if (i < i1) {
+                    v[t] = merged[i];
+                    tg[t] = tag[i];
+                    const bool first = i == 0 || v[t] != merged[i - 1];
+                    cnt += (first ? 1ull : 0ull) + (tg[t] == 0 ? 1ull << 12 : tg[t] == 1 ? 1ull << 24 : 0ull);
+                    if (!first) tg[t] |= 4;
+                }
+            }
+            __shared__ uint64_t wsum[JQ_THREADS / 64];
             const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-            int inc = cnt;
+            uint64_t inc = cnt;
             for (int off = 1; off < 64; off <<= 1) {
-                const int t = __shfl_up(inc, off);
+                const uint64_t t = __shfl_up((unsigned long long)inc, off);
                 if (lane >= off) inc += t;
             }
             if (lane == 63) wsum[w] = inc;
-            __syncthreads();
-            int base = inc - cnt;
-            for (int k2 = 0; k2 < w; ++k2) base += wsum[k2];
-            for (int i = i0; i < i1; ++i)
-                if (i == 0 || merged[i] != merged[i - 1]) lev[base++] = merged[i];
-            if (threadIdx.x == JQ_THREADS - 1) nU = base;
+            __syncthreads();  // every tag has been read, too
+            uint64_t at = inc - cnt;
+            for (int k2 = 0; k2 < w; ++k2) at += wsum[k2];
+            int j = (int)(at & 0xFFF), n0 = (int)((at >> 12) & 0xFFF), n1 = (int)((at >> 24) & 0xFFF);
+#pragma unroll
+            for (int t = 0; t < MOST; ++t) {
+                const int i = i0 + t;
+                if (i < i1) {
+                    if (!(tg[t] & 4)) {
+                        lev[j] = v[t];
+                        below01[j] = n0 | (n1 << 16);
+                        below2[j] = i - n0 - n1;
+                        ++j;
+                    }
+                    n0 += (tg[t] & 3) == 0 ? 1 : 0;
+                    n1 += (tg[t] & 3) == 1 ? 1 : 0;
+                }
+            }
+            if (threadIdx.x == JQ_THREADS - 1) nU = j;
         }
         __syncthreads();
         const int U = nU;
-        {  // every thread a contiguous run of the (increasing) levels
-            const int per = (U + JQ_THREADS - 1) / JQ_THREADS;
-            const int j0 = threadIdx.x * per, j1 = min(j0 + per, U);
-            QuantileWalk wf, wc, wcs;
-            for (int j = j0; j < j1; ++j) {
-                const double p = lev[j];
-                const double qf = wf.at(rf, cf, g, p);
-                const double qc = wc.at(rc, cc, g, p);
-                const double qcs = wcs.at(rcs, ccs, g, p);
-                qt[j] = qf + (qc - qcs);
-            }
+        // the three quantiles at every level: of each array the first edge with
+        // cdf >= the level is the number of edges below it, the last edge with
+        // cdf <= the level one less than the number below the next level
+        for (int j = threadIdx.x; j < U; j += JQ_THREADS) {
+            const double p = lev[j];
+            const int a01 = below01[j], a2 = below2[j];
+            const bool end = j == U - 1;
+            const int b01 = end ? (E | (E << 16)) : below01[j + 1], b2 = end ? E : below2[j + 1];
+            const double qf = quantile_level(rf, cf, g, p, a01 >> 16, (b01 >> 16) - 1);
+            const double qc = quantile_level(rc, cc, g, p, a01 & 0xFFFF, (b01 & 0xFFFF) - 1);
+            const double qcs = quantile_level(rcs, ccs, g, p, a2, b2 - 1);
+            qt[j] = qf + (qc - qcs);
         }
         __syncthreads();
         // violations qt[j] > qt[j+1], in increasing j, compacted into vio
@@ -558,10 +586,7 @@ __global__ void __launch_bounds__(KIND == PR_J_QUANTILE ? JQ_THREADS : HB_THREAD
         __syncthreads();
         // cdf at the edges: inf{p : q(p) >= x_i} on the piecewise-linear q
         double *ct = jq;  // [E], over the pool sums
-        const int iper = (E + JQ_THREADS - 1) / JQ_THREADS;
-        const int i0 = threadIdx.x * iper, i1 = min(i0 + iper, E);
-        int jw = -1;  // first level with qt >= x, advanced along the thread's edges
-        for (int i = i0; i < i1; ++i) {
+        for (int i = threadIdx.x; i < E; i += JQ_THREADS) {
             double v;
             if (i == 0) {
                 v = 0.0;
@@ -569,9 +594,7 @@ __global__ void __launch_bounds__(KIND == PR_J_QUANTILE ? JQ_THREADS : HB_THREAD
                 v = lev[U - 1];
             } else {
                 const double x = hedge(g, i);
-                if (jw < 0) jw = lower_bound_d(qt, U, x);
-                else while (jw < U && qt[jw] < x) ++jw;
-                const int j = jw;
+                const int j = lower_bound_d(qt, U, x);  // first level with qt >= x
                 if (j == 0) v = 0.0;
                 else if (j == U) v = lev[U - 1];
                 else {
@@ -617,6 +640,20 @@ int hist_jump_launch(int kind, const double *rc, const double *rf, const double 
 // ---------------------------------------------------------------------------
 // Matchings.
 // ---------------------------------------------------------------------------
+// r + share tg[a] + share tg[a + 1] + ... (up to b, in that order), eight loads
+// in flight.
+__device__ inline double gap_sum(double r, const double *tg, int a, int b, double share) {
+#pragma clang fp contract(off)
+    for (int i = a; i < b; i += 8) {
+        double m[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) m[u] = tg[i + u < b ? i + u : a];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) r = i + u < b ? r + share * m[u] : r;
+    }
+    return r;
+}
+
 // Per slice tables: cdf of the prior and of the target at the edges, and the
 // reweighting ratios rho'_i / rhobar_i (H9 of the design notes).
 __global__ void __launch_bounds__(HB_THREADS) match_tables(const double *__restrict__ rt, int64_t t_stride,
@@ -633,42 +670,35 @@ __global__ void __launch_bounds__(HB_THREADS) match_tables(const double *__restr
     if (wave == 0) wave_running_sum([&](int i) { return rp[i]; }, I, cp);
     if (wave == 1) wave_running_sum([&](int i) { return rt[i]; }, I, ctg);
     if (want_ratio) {
-        // the target mass of cells without prior particles goes to the
-        // nearest supported cells, half to each side, in increasing cell order
-        __shared__ double r[HB_MAX_CELLS], tg[HB_MAX_CELLS];
-        __shared__ int sup[HB_MAX_CELLS], nxt[HB_MAX_CELLS + 1];
-        for (int i = threadIdx.x; i < I; i += blockDim.x) {
-            sup[i] = rp[i] > 0.0 ? 1 : 0;
-            tg[i] = rt[i];
-            r[i] = sup[i] ? tg[i] : 0.0;
+        // the target mass of cells without prior particles goes to the nearest
+        // supported cells, half to each side: every supported cell adds up
+        // what it receives in increasing cell order, from the gap on its left,
+        // then from the one on its right
+        __shared__ double tg[HB_MAX_CELLS];
+        __shared__ uint64_t sup[HB_MAX_CELLS / 64];
+        for (int i0 = wave * 64; i0 < I; i0 += HB_THREADS) {
+            const int i = i0 + ((int)threadIdx.x & 63);
+            const uint64_t m = __ballot(i < I && rp[i < I ? i : I - 1] > 0.0);
+            if ((threadIdx.x & 63) == 0) sup[i0 >> 6] = m;
+            if (i < I) tg[i] = rt[i];
         }
         __syncthreads();
-        if (threadIdx.x == 128) {
-            // nxt[i]: first supported cell at or after i (I if none)
-            nxt[I] = I;
-            for (int i = I - 1; i >= 0; --i) nxt[i] = sup[i] ? i : nxt[i + 1];
-            int left = -1;
-            for (int i = 0; i < I; ++i) {
-                if (sup[i]) {
-                    left = i;
-                    continue;
-                }
-                const double m = tg[i];
-                if (m == 0.0) continue;
-                const int right = nxt[i + 1];
-                if (left >= 0 && right < I) {
-                    const double half = 0.5 * m;
-                    r[left] = r[left] + half;
-                    r[right] = r[right] + half;
-                } else if (left >= 0) {
-                    r[left] = r[left] + m;
-                } else if (right < I) {
-                    r[right] = r[right] + m;
-                }
+        const int words = (I + 63) >> 6;
+        for (int c = threadIdx.x; c < I; c += blockDim.x) {
+            const int wc = c >> 6, bc = c & 63;
+            double r = 0.0;
+            if ((sup[wc] >> bc) & 1ull) {
+                int lw = wc, rw = wc;  // the supported cells around c (-1, I: none)
+                uint64_t lm = sup[wc] & ((1ull << bc) - 1ull), rm = bc == 63 ? 0ull : sup[wc] & (~0ull << (bc + 1));
+                while (lm == 0 && --lw >= 0) lm = sup[lw];
+                while (rm == 0 && ++rw < words) rm = sup[rw];
+                const int left = lm ? (lw << 6) + 63 - __clzll(lm) : -1;
+                const int right = rm ? (rw << 6) + __ffsll((unsigned long long)rm) - 1 : I;
+                r = gap_sum(tg[c], tg, left + 1, c, left >= 0 ? 0.5 : 1.0);
+                r = gap_sum(r, tg, c + 1, right, right < I ? 0.5 : 1.0);
             }
+            ratio[c] = (sup[wc] >> bc) & 1ull ? r / rp[c] : 0.0;
         }
-        __syncthreads();
-        for (int i = threadIdx.x; i < I; i += blockDim.x) ratio[i] = sup[i] ? r[i] / rp[i] : 0.0;
     }
 }
 
