@@ -1,6 +1,6 @@
 // Fine propagator: initial ensemble and Euler-Maruyama over all slices at once
-// (Sec. 2.1.3 eq. (EMx)/(EMy), Sec. 3.2.1).  One thread owns PPT particles of
-// one slice and keeps their state in registers for the whole slice; the
+// (Sec. 2.1.3 eq. (EMx)/(EMy), Sec. 3.2.1).  One thread owns one particle of
+// one slice and keeps its state in registers for the whole slice; the
 // normal increments come from the counter-based generator, so no random
 // state is stored and a slice recomputed later sees the same numbers.
 #include "pr_fine_dev.hpp"
@@ -12,12 +12,12 @@ namespace pr {
 // (one wave per SIMD); asking for 3 blocks per CU makes the compiler fit it
 // in 168 with a few spilled values, which runs 1.5x faster (FP32: 4 blocks,
 // 128 VGPRs, 2 % faster than its own 142).
-template <int D, typename T, int PPT>
+template <int D, typename T>
 __global__ void __launch_bounds__(256, (D >= 32 ? (sizeof(T) == 4 ? 4 : 3) : 1)) fine_kernel(const T *xin, const T *yin, T *xout, T *yout, int64_t n,
                                                    int slice_first, int64_t S, int N,
                                                    EmCoef<T> c, const double *__restrict__ a_dev,
                                                    Key key, uint32_t inst) {
-    __shared__ NoiseTab tab;
+    __shared__ typename TabOf<T>::type tab;
     load_noise_tab(tab);
     const int s = blockIdx.y;
     const int sl = slice_first + s;
@@ -29,37 +29,20 @@ __global__ void __launch_bounds__(256, (D >= 32 ? (sizeof(T) == 4 ? 4 : 3) : 1))
 #pragma unroll
     for (int i = 0; i < D; ++i) a[i] = a_dev ? (T)a_dev[i] : (T)1;
 
-    const int64_t base = (int64_t)blockIdx.x * blockDim.x * PPT + threadIdx.x;
-    T xv[PPT];
-    T yv[PPT][D];
-    bool live[PPT];
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n) return;
+    T x = xin[(int64_t)s * n + p], y[D];
 #pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        const int64_t p = base + (int64_t)q * blockDim.x;
-        live[q] = p < n;
-        const int64_t pc = live[q] ? p : 0;
-        xv[q] = xin[(int64_t)s * n + pc];
-#pragma unroll
-        for (int i = 0; i < D; ++i) yv[q][i] = yin[((int64_t)s * D + i) * n + pc];
-    }
+    for (int i = 0; i < D; ++i) y[i] = yin[((int64_t)s * D + i) * n + p];
     // 32-bit step counter (the generator's counter word is 32 bits wide);
     // unrolled twice where the registers allow (a large fast part would spill)
     constexpr int UNROLL = D <= 4 ? 2 : 1;
     const uint32_t mb = (uint32_t)m0, steps = (uint32_t)(m1 - m0);
 #pragma unroll UNROLL
-    for (uint32_t i = 0; i < steps; ++i) {
+    for (uint32_t i = 0; i < steps; ++i) em_step<D, T>(x, y, a, c, tab, key, inst, mb + i, (uint32_t)p);
+    xout[(int64_t)s * n + p] = x;
 #pragma unroll
-        for (int q = 0; q < PPT; ++q)
-            em_step<D, T>(xv[q], yv[q], a, c, tab, key, inst, mb + i, (uint32_t)(base + (int64_t)q * blockDim.x));
-    }
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        if (!live[q]) continue;
-        const int64_t p = base + (int64_t)q * blockDim.x;
-        xout[(int64_t)s * n + p] = xv[q];
-#pragma unroll
-        for (int i = 0; i < D; ++i) yout[((int64_t)s * D + i) * n + p] = yv[q][i];
-    }
+    for (int i = 0; i < D; ++i) yout[((int64_t)s * D + i) * n + p] = y[i];
 }
 
 // Few particles (d = 1, FP64): 64 per block, their normals generated ahead by
@@ -144,10 +127,8 @@ static int launch_fine(const pr_sde *sde, const pr_schedule *sch, uint64_t seed,
     // One particle per thread: two take the same time where the chip is full
     // (64 x 2^20 particles: 221.8 ms both) and up to 1.8 times as long where it
     // is not (40,000 particles: 45 us, one 25 us; 100,000: 45.5 and 37.7).
-    constexpr int PPT = 1;
-    const int64_t per_block = 256 * PPT;
-    dim3 grid((unsigned)((n + per_block - 1) / per_block), (unsigned)slice_count);
-    hipLaunchKernelGGL((fine_kernel<D, T, PPT>), grid, dim3(256), 0, st, (const T *)xi, (const T *)yi, (T *)x,
+    dim3 grid((unsigned)((n + 255) / 256), (unsigned)slice_count);
+    hipLaunchKernelGGL((fine_kernel<D, T>), grid, dim3(256), 0, st, (const T *)xi, (const T *)yi, (T *)x,
                        (T *)y, n, slice_first,
                        sch->total_steps, sch->n_slices, make_coef<T>(sde, sch->dt), sde->a,
                        make_key(seed), inst);

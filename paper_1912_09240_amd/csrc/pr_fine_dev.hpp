@@ -18,21 +18,15 @@ struct EmCoef {
     T sy;          // sqrt(2 dt / (beta eps))
 };
 
+// The normals' tables in LDS, by precision.
 template <typename T>
-__device__ __forceinline__ void normal_pair(const NoiseTab &tab, Key key, uint32_t inst, uint32_t tag,
-                                            uint32_t m, uint32_t p, uint32_t j, T &z0, T &z1);
-
+struct TabOf {
+    using type = NoiseTab;
+};
 template <>
-__device__ __forceinline__ void normal_pair<double>(const NoiseTab &tab, Key key, uint32_t inst, uint32_t tag,
-                                                    uint32_t m, uint32_t p, uint32_t j, double &z0,
-                                                    double &z1) {
-    box_muller(noise_block(key, inst, tag, m, p, j), tab, z0, z1);
-}
-template <>
-__device__ __forceinline__ void normal_pair<float>(const NoiseTab &, Key key, uint32_t inst, uint32_t tag,
-                                                   uint32_t m, uint32_t p, uint32_t j, float &z0, float &z1) {
-    box_muller_f32(noise_block(key, inst, tag, m, p, j), z0, z1);
-}
+struct TabOf<float> {
+    using type = NoiseTabF;
+};
 
 __device__ __forceinline__ double fmaf_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float fmaf_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
@@ -72,11 +66,13 @@ __device__ __forceinline__ void em_update(T &x, T (&y)[D], const T (&a)[D], cons
 // One step of one particle with its normals generated in place.
 template <int D, typename T>
 __device__ __forceinline__ void em_step(T &x, T (&y)[D], const T (&a)[D], const EmCoef<T> &c,
-                                        const NoiseTab &tab, Key key, uint32_t inst, uint32_t m, uint32_t p) {
+                                        const typename TabOf<T>::type &tab, Key key, uint32_t inst, uint32_t m,
+                                        uint32_t p) {
     constexpr int NP = (D + 2) / 2;  // pairs of normals for 1 + D components
     T z[2 * NP];
 #pragma unroll
-    for (int j = 0; j < NP; ++j) normal_pair<T>(tab, key, inst, 0u, m, p, (uint32_t)j, z[2 * j], z[2 * j + 1]);
+    for (int j = 0; j < NP; ++j)
+        box_muller(noise_block(key, inst, 0u, m, p, (uint32_t)j), tab, z[2 * j], z[2 * j + 1]);
     em_update<D, T>(x, y, a, c, z);
 }
 

@@ -144,16 +144,8 @@ __device__ __forceinline__ void box_muller(const Block &b, const NoiseTab &tab, 
     normal_pair_of_words(b.w0, b.w1, b.w2, b.w3, tab, z0, z1);
 }
 
-// FP32 variant with the same bits at single precision: u from the top 24
-// bits of w0, the angle from bits 4..31 of w2 (no tables).
-__device__ __forceinline__ void box_muller_f32(const Block &b, float &z0, float &z1) {
-    const float u1 = ((float)(b.w0 >> 8) + 0.5f) * 0x1p-24f;
-    const float t = ((float)((b.w2 >> 4) & 255u) + (float)(b.w2 >> 12) * 0x1p-20f) * 0x1p-7f;
-    const float r = sqrtf(-2.0f * logf(u1));
-    float s, c;
-    sincospif(t, &s, &c);
-    z0 = r * c;
-    z1 = r * s;
+__device__ __forceinline__ void box_muller(const Block &b, const NoiseTabF &tab, float &z0, float &z1) {
+    normal_pair_of_words_f32(b.w0, b.w2, tab, z0, z1);
 }
 
 // Orderable 64-bit key of a double: unsigned order == numeric order,

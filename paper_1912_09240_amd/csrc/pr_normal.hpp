@@ -122,4 +122,45 @@ __device__ __forceinline__ void load_noise_tab(NoiseTab &tab) {
     __syncthreads();
 }
 
+// FP32 pair with the same bits at single precision: u from the top 24 bits of
+// w0 (rounded to single), the angle from bits 4..31 of w2, by the table of
+// 256 pairs above in single precision.
+//   -2 ln u: the hardware's base-2 logarithm (1 ulp, also next to u = 1) times
+//   -2 ln 2 in two parts; 2^-100 keeps the root's seed finite at u = 1.
+//   sin(h b) to b^3 and cos(h b) - 1 to b^2 (truncation below 1e-9), b exact.
+// 26 vector operations and two transcendental ones per pair, against 44 for
+// logf, sqrtf and sincospif, whose angle is also rounded (t to 24 bits).
+struct alignas(8) TabPairF {
+    float a, b;
+};
+struct NoiseTabF {
+    TabPairF sc[256];
+};
+
+__device__ __forceinline__ void load_noise_tab(NoiseTabF &tab) {
+    float *d = reinterpret_cast<float *>(&tab);
+    for (int i = (int)threadIdx.x; i < 512; i += (int)blockDim.x) d[i] = (float)kNoiseTabDev[i];
+    __syncthreads();
+}
+
+__device__ __forceinline__ void normal_pair_of_words_f32(uint32_t w0, uint32_t w2, const NoiseTabF &tab, float &z0,
+                                                         float &z1) {
+#pragma clang fp contract(off)
+    constexpr float M2LN2 = -0x1.62e43p+0f, M2LN2_LO = (float)(kMinus2Ln2 - (double)M2LN2);
+    const float u = __builtin_fmaf((float)(w0 >> 8), 0x1p-24f, 0x1p-25f);
+    const float l2 = __builtin_amdgcn_logf(u);
+    const float L = __builtin_fmaf(l2, M2LN2, __builtin_fmaf(l2, M2LN2_LO, 0x1p-100f));
+    const float y = __builtin_amdgcn_rsqf(L);
+    float r = L * y;
+    r = __builtin_fmaf(__builtin_fmaf(-r, r, L), 0.5f * y, r);
+    const TabPairF t = tab.sc[(w2 >> 4) & 255u];
+    const float b = __builtin_fmaf((float)(w2 >> 12), 0x1p-20f, -0.5f);
+    const float b2 = b * b;
+    const float sb = b * __builtin_fmaf((float)kSinP3, b2, (float)kSinP1);
+    const float cm1 = (float)kCosQ2 * b2;
+    const float ds = __builtin_fmaf(t.b, sb, t.a * cm1), dc = __builtin_fmaf(-t.a, sb, t.b * cm1);
+    z0 = __builtin_fmaf(r, dc, r * t.b);
+    z1 = __builtin_fmaf(r, ds, r * t.a);
+}
+
 }  // namespace pr
