@@ -428,7 +428,8 @@ rs_scatter(const void *__restrict__ src, const uint32_t *__restrict__ vals_in, K
 // segment table): the keys of every ensemble are first distributed over
 // ss_buckets(n) buckets (about 4096 keys each) by splitters drawn from a
 // sample, then every bucket is ordered on its own in LDS.  An ensemble of at
-// most SS_BIG keys is one bucket, read from the values themselves.
+// most SS_BIG keys (segment table: SS_CAP) is one bucket, read from the values
+// themselves.
 //   ss_sample       ss_runs() runs of SS_RUN keys per ensemble, one per block,
 //                   each sorted and thinned to SS_KEEP keys;
 //   ss_splitters    the thinned runs merged; splitter b is the merged key at
@@ -487,11 +488,15 @@ constexpr int64_t SS_LARGE_N = (int64_t)1 << 16;
 static_assert(SS_B == RS_RADIX, "buckets take the place of a radix pass's digits");
 static_assert(SS_RUN == 4 * SS_KEEP && SS_RUN == 16 * SS_LIST, "a run's lists and its kept keys");
 
-// Buckets of an ensemble of n keys: one where it fits a block (10 ensembles of
-// 10^4 keys: two kernels instead of seven), else one per tile of 4096, at
-// most SS_B.
+// Buckets of an ensemble of n keys: one where it fits a block, else one per
+// tile of 4096, at most SS_B.  Equal ensembles are one bucket up to SS_BIG keys
+// (10 of 10^4 keys: two kernels instead of seven), those of a segment table up
+// to SS_CAP: the others' distribution is launched in any case, and above SS_CAP
+// they would wait for one of 256 blocks in ss_left (637 segments of 2^12 to
+// 2^15 keys: that took 156 us, now 10).
+template <bool VAR>
 __host__ __device__ __forceinline__ int ss_buckets(int64_t n) {
-    if (n <= SS_BIG) return 1;
+    if (n <= (VAR ? SS_CAP : SS_BIG)) return 1;
     const int64_t b = (n + RS_THREADS * RS_ITEMS - 1) / (RS_THREADS * RS_ITEMS);
     return b > SS_B ? SS_B : (int)b;
 }
@@ -593,7 +598,7 @@ ss_sample(const void *__restrict__ x, SortLayout L, int most_runs, K *__restrict
     int64_t base, n, tile0;
     int nblk, qrow;
     seg_ref<VAR>(L, s, base, n, tile0, nblk, qrow);
-    const int nb = ss_buckets(n), runs = ss_runs(nb);
+    const int nb = ss_buckets<VAR>(n), runs = ss_runs(nb);
     if (nb == 1 || r >= runs) return;
     const uint32_t g = (uint32_t)(r * SS_RUN + t);
     uint32_t h = (g + 0x9E3779B9u * (uint32_t)s) * 0x85EBCA6Bu;
@@ -632,7 +637,7 @@ ss_splitters(const K *__restrict__ runq, SortLayout L, K *__restrict__ split) {
     int64_t base, n, tile0;
     int nblk, qrow;
     seg_ref<VAR>(L, s, base, n, tile0, nblk, qrow);
-    const int nb = ss_buckets(n);
+    const int nb = ss_buckets<VAR>(n);
     if (nb == 1) return;
     const int M = ss_runs(nb) * SS_KEEP;
     for (int i = t; i < M; i += 1024) buf[0][i] = runq[(int64_t)s * SS_MAX_RUNS * SS_KEEP + i];
@@ -664,7 +669,7 @@ ss_count(const void *__restrict__ src, const K *__restrict__ split, SortLayout L
     extern __shared__ uint32_t cell_h[];
     if (L.guard && *L.guard == 0) return;
     const TileRef T = tile_ref<VAR>(L, xcd_tile(blockIdx.x, gridDim.x));
-    const int nb = ss_buckets(T.n);
+    const int nb = ss_buckets<VAR>(T.n);
     const bool do_hist = ha.hist != nullptr;
     if (nb == 1 && !do_hist && mom_part == nullptr) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -754,7 +759,7 @@ __global__ void __launch_bounds__(256) ss_rowscan(uint32_t *__restrict__ counts,
                                                   SortLayout L) {
     if (L.guard && *L.guard == 0) return;
     const int d = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (d >= ss_buckets(L.n)) return;
+    if (d >= ss_buckets<false>(L.n)) return;
     uint32_t *c = counts + (int64_t)blockIdx.y * L.nblk * RS_RADIX + (int64_t)d * L.nblk;
     uint32_t carry = 0;
     for (int c0 = 0; c0 < L.nblk; c0 += 64) {
@@ -775,7 +780,7 @@ __global__ void __launch_bounds__(SS_B) ss_rowscan_seg(uint32_t *__restrict__ co
                                                        SortLayout L) {
     if (L.guard && *L.guard == 0) return;
     const SortSeg g = L.segs[blockIdx.x];
-    const int d = threadIdx.x, nb = ss_buckets(g.n);
+    const int d = threadIdx.x, nb = ss_buckets<true>(g.n);
     if (nb == 1 || d >= nb) return;
     uint32_t *c = counts + g.tile0 * RS_RADIX + (int64_t)d * g.nblk;
     uint32_t carry = 0;
@@ -841,7 +846,7 @@ ss_scatter(const void *__restrict__ src, const uint32_t *bucket, const K *__rest
     BucketSearch<K> *bucket_of = reinterpret_cast<BucketSearch<K> *>(stage);
     if (L.guard && *L.guard == 0) return;
     const TileRef T = tile_ref<VAR>(L, xcd_tile(blockIdx.x, gridDim.x));
-    const int nb = ss_buckets(T.n);
+    const int nb = ss_buckets<VAR>(T.n);
     if (nb == 1) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int64_t t0 = (int64_t)T.blk * TILE + wave * WAVE_KEYS;
@@ -1002,7 +1007,7 @@ __device__ __forceinline__ BucketRef bucket_ref(const SortLayout &L, const Bucke
     R.b = T.blk;
     R.sbase = T.base;
     R.sn = T.n;
-    R.nb = ss_buckets(T.n);
+    R.nb = ss_buckets<VAR>(T.n);
     if constexpr (VAR) R.qrow = L.segs[T.seg].qrow;
     else R.qrow = T.seg;
     R.start = 0;
@@ -1445,7 +1450,7 @@ __device__ __forceinline__ void ranks_of_tile(const uint32_t *slots, const uint3
     __shared__ uint32_t sr[TILE];
     __shared__ uint32_t gdelta[SS_B], wtot[SC_WAVES];
     const TileRef T = tile_ref<VAR>(L, tile);
-    const int nb = ss_buckets(T.n), tid = threadIdx.x;
+    const int nb = ss_buckets<VAR>(T.n), tid = threadIdx.x;
     if (nb == 1) return;
     const int64_t t0 = (int64_t)T.blk * TILE;
     const int tile_n = T.n - t0 < TILE ? (int)(T.n - t0) : TILE;
@@ -2182,10 +2187,10 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
     };
     constexpr int P = KeyTraits<K>::passes;
     const bool splitter = !L.radix && max_n > 0 && max_n <= SS_MAX_N;
-    const bool many = max_n > SS_BIG;  // some ensemble is more than one bucket
+    const bool many = max_n > (VAR ? SS_CAP : SS_BIG);  // some ensemble is more than one bucket
     if (splitter) {
         K *skeys = keys[1 - sorted_buffer<K>()], *out = keys[sorted_buffer<K>()];
-        const int nb = ss_buckets(max_n), runs = ss_runs(nb);
+        const int nb = ss_buckets<VAR>(max_n), runs = ss_runs(nb);
         if (many) {
             hipLaunchKernelGGL((ss_sample<K, VAR>), dim3((unsigned)(runs * L.nseg)), dim3(SS_RUN), 0, st, x, L, runs,
                                runq);
