@@ -169,6 +169,7 @@ __global__ void __launch_bounds__(256) m2k_units(const double *__restrict__ rho,
 // Serial chain of one instance per block: q_{k+1}^{n+1} = J(C_n(q_{k+1}^n),
 // q_f^{n+1}, q_c^{*,n+1}); without qf it is the plain coarse pass of the
 // zeroth iteration, q^{n+1} = C_n(q^n).  qn row 0 is copied from q.
+template <bool STREAM>
 __global__ void __launch_bounds__(CHAIN_THREADS) chain_kernel(const ChainInst *__restrict__ ci, int inst0,
                                                     const CoarseUnit *__restrict__ cu, const double *__restrict__ E,
                                                     const double *__restrict__ q, const double *__restrict__ qf,
@@ -183,10 +184,13 @@ __global__ void __launch_bounds__(CHAIN_THREADS) chain_kernel(const ChainInst *_
         qn[(int64_t)I.qrow0 * Q1 + j] = v;
     }
     __syncthreads();
+    auto E_of = [&](int s) { return E + (int64_t)cu[I.u0 + s].e_id * g.cells * g.cells; };
+    ChainStream stream;
+    if constexpr (STREAM) stream.start(E_of(0), g.cells);
     for (int s = 0; s < I.K; ++s) {
-        const CoarseUnit U = cu[I.u0 + s];
-        const int64_t orow = (int64_t)U.out_row * Q1;
-        chain_link(E + (int64_t)U.e_id * g.cells * g.cells, qf ? qf + orow : nullptr, qf ? qcs + orow : nullptr, g, sh);
+        const int64_t orow = (int64_t)cu[I.u0 + s].out_row * Q1;
+        chain_link<STREAM>(stream, E_of(s), E_of(min(s + 1, I.K - 1)), qf ? qf + orow : nullptr,
+                           qf ? qcs + orow : nullptr, g, sh);
         for (int j = threadIdx.x; j < Q1; j += blockDim.x) qn[orow + j] = sh[j];
         __syncthreads();
     }
@@ -387,6 +391,16 @@ static void build_units(Batch *b, int tile) {
     std::stable_sort(b->units_h.begin(), b->units_h.end(),
                      [&](const Unit &a, const Unit &c) { return cost(a) > cost(c); });
     b->n_units = (int)b->units_h.size();
+}
+
+// The chains of count instances from inst0 on.
+static int launch_chain(Batch *b, int inst0, int count, const double *qf, const double *qcs, double *qn,
+                        hipStream_t st) {
+    auto kernel = b->g.cells <= CHAIN_STREAM_CELLS ? chain_kernel<true> : chain_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(count), dim3(CHAIN_THREADS), chain_lds(b->g), st, (const ChainInst *)b->chain,
+                       inst0, (const CoarseUnit *)b->cu, (const double *)b->E, (const double *)b->q, qf, qcs, qn, b->g);
+    PR_LAUNCHED();
+    return PR_OK;
 }
 
 // Resident workgroups of the persistent fine kernel (queried outside any
@@ -598,10 +612,7 @@ static int iterate_once(Batch *b, int mode, hipStream_t st) {
         hipLaunchKernelGGL(m2k_units, dim3(b->total_slices), dim3(256), sizeof(double) * (2 * g.cells + 1), st,
                            (const double *)b->rho_b, (const CoarseUnit *)b->cu, b->qcs, g);
         PR_LAUNCHED();
-        hipLaunchKernelGGL(chain_kernel, dim3(b->B), dim3(CHAIN_THREADS), chain_lds(g), st, (const ChainInst *)b->chain, 0,
-                           (const CoarseUnit *)b->cu, (const double *)b->E, (const double *)b->q,
-                           (const double *)b->qf, (const double *)b->qcs, b->qn, g);
-        PR_LAUNCHED();
+        PR_CHECK(launch_chain(b, 0, b->B, b->qf, b->qcs, b->qn, st));
         hipLaunchKernelGGL(match_batch_kernel, dim3(b->n_mtiles), dim3(256), sizeof(double) * (Q + 1), st,
                            (const MatchSeg *)b->mseg, (const int *)b->mtile, 0, (const double *)b->qn,
                            (const double *)b->qf, Q, (const uint32_t *)b->rank, b->x[nx]);
@@ -640,10 +651,7 @@ static int iterate_once(Batch *b, int mode, hipStream_t st) {
             hipLaunchKernelGGL(m2k_units, dim3(K), dim3(256), sizeof(double) * (2 * g.cells + 1), st,
                                (const double *)b->rho_b, cu, b->qcs, g);
             PR_LAUNCHED();
-            hipLaunchKernelGGL(chain_kernel, dim3(1), dim3(CHAIN_THREADS), chain_lds(g), st, (const ChainInst *)b->chain, i,
-                               (const CoarseUnit *)b->cu, (const double *)b->E, (const double *)b->q,
-                               (const double *)b->qf, (const double *)b->qcs, b->qn, g);
-            PR_LAUNCHED();
+            PR_CHECK(launch_chain(b, i, 1, b->qf, b->qcs, b->qn, st));
             hipLaunchKernelGGL(match_batch_kernel, dim3(b->mtile_count[i]), dim3(256), sizeof(double) * (Q + 1), st,
                                (const MatchSeg *)b->mseg, (const int *)b->mtile, b->mtile_first[i],
                                (const double *)b->qn, (const double *)b->qf, Q, (const uint32_t *)b->rank, b->x[nx]);
@@ -763,7 +771,8 @@ static int batch_create(int B, const pr_sde *sde, const pr_schedule *sch, const 
     PR_CHECK(upload(b->chain, chain, st));
     b->n_e = (int)ereq.size();
     const int64_t nn = (int64_t)I * I;
-    PB_ALLOC(b->E, sizeof(double) * nn * b->n_e);
+    PB_ALLOC(b->E, sizeof(double) * (nn * b->n_e + 1));  // one element behind the last row (ChainStream reads pairs)
+    PR_HIP(hipMemsetAsync(b->E + nn * b->n_e, 0, sizeof(double), st));
     PR_CHECK(build_expms(gens, ereq, I, b->E, st));
     // sort layout of the states t = 1..K_i of every instance
     int64_t tiles = 0, keys = 0;
@@ -868,10 +877,7 @@ static int batch_create(int B, const pr_sde *sde, const pr_schedule *sch, const 
         PR_CHECK(init_ensemble(&sde[i], seed, b->inst_id[i], ni, b->x[0] + xo_i, b->y[0] + xo_i, st));
         PR_CHECK(restrict_quantiles(b->x[0] + xo_i, PR_F64, ni, 1, b->Q, nullptr, b->q + (int64_t)r0 * (b->Q + 1),
                                     b->rank + xo_i, nullptr, nullptr, nullptr, nullptr, b->ws, st));
-        hipLaunchKernelGGL(chain_kernel, dim3(1), dim3(CHAIN_THREADS), chain_lds(b->g), st, (const ChainInst *)b->chain, i,
-                           (const CoarseUnit *)b->cu, (const double *)b->E, (const double *)b->q, nullptr, nullptr,
-                           b->q, b->g);
-        PR_LAUNCHED();
+        PR_CHECK(launch_chain(b, i, 1, nullptr, nullptr, b->q, st));
         MatchArgs ma{b->q + (int64_t)(r0 + 1) * (b->Q + 1), b->Q + 1, b->q + (int64_t)r0 * (b->Q + 1), 0,
                      b->rank + xo_i, 0, b->x[0] + xo_i, 0, b->x[0] + xo_i + ni, ni};
         PR_CHECK(match_strided(ma, ni, K, b->Q, PR_F64, st));

@@ -134,9 +134,13 @@ __global__ void __launch_bounds__(CHAIN_THREADS) chain_block(const double *__res
         qn[j] = sh[j];
     }
     __syncthreads();
+    auto E_of = [&](int s) { return E + (int64_t)tau_id[s] * g.cells * g.cells; };
+    ChainStream stream;
+    stream.start(E_of(0), g.cells);
     for (int s = 0; s < K; ++s) {
         const int64_t row = (int64_t)(s + 1) * Q1;
-        chain_link(E + (int64_t)tau_id[s] * g.cells * g.cells, qf ? qf + row : nullptr, qf ? qcs + row : nullptr, g, sh);
+        chain_link<true>(stream, E_of(s), E_of(min(s + 1, K - 1)), qf ? qf + row : nullptr, qf ? qcs + row : nullptr, g,
+                         sh);
         for (int j = threadIdx.x; j < Q1; j += blockDim.x) qn[row + j] = sh[j];
         __syncthreads();
     }
@@ -253,7 +257,8 @@ int coarse_create_tridiag(const std::vector<double> &lo, const std::vector<doubl
         delete c;
         return code;
     };
-    if (hipMalloc(&c->E, sizeof(double) * nn * c->n_tau) != hipSuccess ||
+    // one element behind the last row (ChainStream reads pairs)
+    if (hipMalloc(&c->E, sizeof(double) * (nn * c->n_tau + 1)) != hipSuccess ||
         hipMalloc(&c->tau_id, sizeof(int) * sch->n_slices) != hipSuccess ||
         hipMalloc(&c->rho_a, sizeof(double) * (size_t)I * sch->n_slices * 2) != hipSuccess) {
         set_error("device allocation of the coarse propagator failed");
@@ -266,6 +271,10 @@ int coarse_create_tridiag(const std::vector<double> &lo, const std::vector<doubl
     }
     std::vector<ExpmReq> reqs;
     for (double tau : c->taus) reqs.push_back(ExpmReq{0, tau});
+    if (hipMemsetAsync(c->E + nn * c->n_tau, 0, sizeof(double), st) != hipSuccess) {
+        set_error("clearing the exponentials' last element failed");
+        return fail(PR_E_HIP);
+    }
     const int e = build_expms({Tridiag{lo, di, up}}, reqs, I, c->E, st);
     if (e != PR_OK) return fail(e);
     (void)hipGetDevice(&c->device);
@@ -299,10 +308,11 @@ int coarse_step(const Coarse *c, int first, int count, const double *q_in, int i
 // The serial chain of all slices: qn[0] = q, qn[s+1] = J(C_s(qn[s]), qf[s+1],
 // qcs[s+1]), or C_s(qn[s]) without qf (rows of n_q + 1 knots).  One block for
 // the whole chain while one CU reads E of a slice in about the time of two
-// launches: a link of 200 cells takes 12 us (7 of them the product, at 45 GB/s
-// from L2) against 18 us in two launches, one of 256 cells 13 us; 320 cells
-// take 18 us.  Beyond, two launches per link, the product spread over the chip.
+// launches: a link of 200 cells takes 8 us (4 of them the product) against 18
+// us in two launches; of 320 cells, too long to be streamed, 18 us as well.
+// Beyond, two launches per link, the product spread over the chip.
 constexpr int CHAIN_CELLS = 256;
+static_assert(CHAIN_CELLS <= CHAIN_STREAM_CELLS, "chain_block streams its rows");
 
 int coarse_chain(const Coarse *c, const double *q, const double *qf, const double *qcs, double *qn, hipStream_t st) {
     const GridDev &g = c->g;

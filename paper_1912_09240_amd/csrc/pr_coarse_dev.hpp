@@ -127,6 +127,9 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 // masses C_i (left to right); level p_j C_I.  A level hit on a flat stretch
 // gives its midpoint; the end knots are the grid ends.  Runs inside one
 // block; C must hold cells + 1 doubles of LDS.
+// MAX_PER: cells of a run at most, 16 for any grid, less where the caller knows
+// that it has no more than 64 MAX_PER cells.
+template <int MAX_PER = 16>
 __device__ inline void masses_to_knots_block(const double *rho, double *C, const GridDev &g, double *q) {
 #pragma clang fp contract(off)
     // Cumulative masses by one wave, in three nested levels: every lane sums its
@@ -143,14 +146,14 @@ __device__ inline void masses_to_knots_block(const double *rho, double *C, const
         double carry = 0.0;
         for (int base = 0; base < g.cells; base += 1024) {
             const int m = min(1024, g.cells - base), per = (m + 63) >> 6;
-            double v[16], run = 0.0;
+            double v[MAX_PER], run = 0.0;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
+            for (int i = 0; i < MAX_PER; ++i) {
                 const int idx = lane * per + i;
                 v[i] = (i < per && idx < m) ? rho[base + idx] : 0.0;
             }
 #pragma unroll
-            for (int i = 0; i < 16; ++i)
+            for (int i = 0; i < MAX_PER; ++i)
                 if (i < per) {
                     run = run + v[i];
                     v[i] = run;
@@ -172,7 +175,7 @@ __device__ inline void masses_to_knots_block(const double *rho, double *C, const
                 start = (lane >> 3) > w ? carry : start;
             }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
+            for (int i = 0; i < MAX_PER; ++i) {
                 const int idx = lane * per + i;
                 if (i < per && idx < m) C[base + idx + 1] = start + (in_group + v[i]);
             }
@@ -639,27 +642,27 @@ __device__ inline void pava_block_chunked(double *v, int L, const int *vio, int 
 // S [L] doubles, SC and vio [L] ints.  Every thread of the block calls it.
 __device__ inline void pava_block(double *v, int L, double *S, int *SC, int *vio) {
 #pragma clang fp contract(off)
-    __shared__ int wsum[16], nbad, npools;
-    const int nt = (int)blockDim.x;
-    const int per = (L + nt - 1) / nt;
-    const int j0 = (int)threadIdx.x * per, j1 = min(j0 + per, L - 1);
-    int cnt = 0;
-    for (int j = j0; j < j1; ++j) cnt += v[j] > v[j + 1] ? 1 : 0;
+    __shared__ int wsum[16], npools;
+    const int nt = (int)blockDim.x, nw = (nt + 63) / 64;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int inc = cnt;
-    for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(inc, off);
-        if (lane >= off) inc += t;
+    // the violations in order, nt indices at a time
+    int nbad = 0;
+    for (int j0 = 0; j0 < L - 1; j0 += nt) {
+        const int j = j0 + (int)threadIdx.x;
+        const bool bad = j < L - 1 && v[j] > v[j + 1];
+        const uint64_t all = __ballot(bad);
+        if (j0) __syncthreads();  // the last round's counts have been read
+        if (lane == 0) wsum[w] = __popcll(all);
+        __syncthreads();
+        int at = nbad + __popcll(all & ((1ull << lane) - 1ull));
+        for (int k = 0; k < nw; ++k) {
+            at += k < w ? wsum[k] : 0;
+            nbad += wsum[k];
+        }
+        if (bad) vio[at] = j;
     }
-    if (lane == 63) wsum[w] = inc;
-    __syncthreads();
-    int base = inc - cnt;
-    for (int k = 0; k < w; ++k) base += wsum[k];
-    for (int j = j0; j < j1; ++j)
-        if (v[j] > v[j + 1]) vio[base++] = j;
-    if ((int)threadIdx.x == nt - 1) nbad = base;
-    __syncthreads();
     if (nbad == 0) return;
+    __syncthreads();
     if (w == 0) {  // the whole first wave runs the pass
         double fm, lm;
         const int np = pava_sparse_range<true>(v, 0, L, vio, nbad, S, SC, &fm, &lm);
@@ -677,20 +680,126 @@ __device__ inline void pava_block(double *v, int L, double *S, int *SC, int *vio
 
 // ---------------------------------------------------------------------------
 // One link of a serial chain by one block: qc (LDS, the knots q^n) becomes
-// J(C_n(q^n), q_f, q_c^*), or C_n(q^n) without qf.  Es: E of the slice.  The
-// product E rho is spread over all the block's waves, each taking CHAIN_ROWS
-// rows at a time with their loads in flight together.  lds: chain_lds() bytes.  Every thread of the
-// block calls it; the result is complete when it returns.
+// J(C_n(q^n), q_f, q_c^*), or C_n(q^n) without qf.  Es: E of the slice, En: E of
+// the next link (any E behind the last).  lds: chain_lds() bytes.  Every thread
+// of the block calls it; the result is complete when it returns.
+//
+// The product E rho is spread over the block's 16 waves, row r on wave r mod
+// 16, in groups of CHAIN_ROWS rows per wave.  STREAM (rows of at most 256
+// cells): the next group of rows is always on its way in registers while one is
+// multiplied, behind the last of a link the first of the next one, which does
+// not depend on the knots and arrives while these are worked out.  What bounds
+// the product is the one CU's rate of loads, one per wave and 16 clocks: in
+// loads of 8 bytes per lane, a reduction per row, it took 17800 of a link's
+// 28000 clocks (200 cells, 100 knots), with the next rows on their way 17000, in
+// loads of 16 bytes 9400 of 18500.  The rest is latency: the knots' searches, the
+// masses' running sum and the monotone repair.  Longer rows are loaded four at
+// a time as they are needed.
 // ---------------------------------------------------------------------------
 constexpr int CHAIN_THREADS = 1024;
 constexpr int CHAIN_ROWS = 4;
+constexpr int CHAIN_STREAM_CELLS = 256;
+
+// Two groups of a wave's rows of E in registers (rows of at most 256 cells).
+// Half a wave holds a row: its lane l the elements 2 l + 64 u and 2 l + 1 + 64 u,
+// in loads of 16 bytes (a CU issues one load per wave and 16 clocks, of 8 or of
+// 16 bytes per lane).  The sums are those of lane_row_dot and wave_sum: lane c
+// there takes the elements c + 64 u.
+struct ChainStream {
+    typedef double Pair __attribute__((ext_vector_type(2)));
+    typedef double Pair8 __attribute__((ext_vector_type(2), aligned(8)));  // as it lies in E
+    Pair e[2][CHAIN_ROWS / 2][4];
+
+    // Rows k = 2 p + half of group grp: (grp CHAIN_ROWS + k) 16 + wave.  Rows past
+    // the end are read at the last one, elements past it at the pair from the last
+    // one on (E has one more element behind its last row): no load waits behind
+    // a condition.
+    __device__ __forceinline__ void load(int b, const double *E, int cells, int grp) {
+        // in scalar registers, and known to be global memory
+        using Global = const __attribute__((address_space(1))) char *;
+        const Global base = (Global)uniform_i64((int64_t)E);
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
+#pragma unroll
+        for (int p = 0; p < CHAIN_ROWS / 2; ++p) {
+            const int r = (grp * CHAIN_ROWS + 2 * p + (lane >> 5)) * (CHAIN_THREADS / 64) + wave;
+            const uint32_t row = (uint32_t)min(r, cells - 1) * (uint32_t)cells;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t off = 8u * (row + (uint32_t)min(2 * (lane & 31) + 64 * u, cells - 1));
+                e[b][p][u] = *(const __attribute__((address_space(1))) Pair8 *)(base + off);
+            }
+        }
+    }
+    // rho2 = max(E rho, 0) for group grp in slot b; v: the lane's elements of
+    // rho, 0 past the end.
+    __device__ __forceinline__ void apply(int b, const Pair *v, int cells, int grp, double *rho2) const {
+#pragma clang fp contract(off)
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
+        Pair acc[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            acc[p] = Pair{0.0, 0.0};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                acc[p].x = fma(e[b][p][u].x, v[u].x, acc[p].x);
+                acc[p].y = fma(e[b][p][u].y, v[u].y, acc[p].y);
+            }
+        }
+        // elements c ^ 32: the other row of 16 lanes, the two pairs' side by side
+        auto fold = [](double x, double y) {
+            const long long p = __double_as_longlong(x), q = __double_as_longlong(y);
+            const auto l = __builtin_amdgcn_permlane16_swap((unsigned)p, (unsigned)q, false, false);
+            const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(p >> 32), (unsigned)(q >> 32), false, false);
+            return __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+                   __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+        };
+        Pair w{fold(acc[0].x, acc[1].x), fold(acc[0].y, acc[1].y)};
+        w.x += dpp_f64<0x128>(w.x);  // c ^ 16: row_ror:8
+        w.y += dpp_f64<0x128>(w.y);
+        w.x += dpp_f64<0x124>(w.x);
+        w.y += dpp_f64<0x124>(w.y);
+        w.x += dpp_f64<0x122>(w.x);
+        w.y += dpp_f64<0x122>(w.y);
+        w.x += dpp_f64<0x121>(w.x);
+        w.y += dpp_f64<0x121>(w.y);
+        const double sum = w.x + w.y;  // c ^ 1
+        const int t = lane >> 4, k = ((t & 1) << 1) | (t >> 1);
+        const int r = (grp * CHAIN_ROWS + k) * (CHAIN_THREADS / 64) + wave;
+        if ((lane & 15) == 0 && r < cells) rho2[r] = sum > 0.0 ? sum : 0.0;
+    }
+    __device__ __forceinline__ void start(const double *E, int cells) { load(0, E, cells, 0); }
+    __device__ __forceinline__ void product(const double *Es, const double *En, const double *rho, int cells,
+                                            double *rho2) {
+        const int lane = (int)(threadIdx.x & 63);
+        Pair v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = 2 * (lane & 31) + 64 * u;
+            const double a = rho[min(j, cells - 1)], b = rho[min(j + 1, cells - 1)];
+            v[u] = Pair{j < cells ? a : 0.0, j + 1 < cells ? b : 0.0};
+        }
+        // groups in pairs: 2 for up to 128 rows, else 4
+        const int groups = cells <= 2 * CHAIN_ROWS * (CHAIN_THREADS / 64) ? 2 : 4;
+#pragma unroll 1
+        for (int grp = 0; grp < groups; grp += 2) {
+            const bool last = grp + 2 >= groups;
+            load(1, Es, cells, grp + 1);
+            apply(0, v, cells, grp, rho2);
+            load(0, last ? En : Es, cells, last ? 0 : grp + 2);
+            apply(1, v, cells, grp + 1, rho2);
+        }
+    }
+};
+static_assert(CHAIN_ROWS == 4, "the fold puts two pairs of rows side by side");
 
 inline size_t chain_lds(const GridDev &g) {
     return sizeof(double) * (2 * (g.nq + 1) + 4 * g.cells + 2) + 2 * sizeof(int) * (g.nq + 1);
 }
 
-__device__ inline void chain_link(const double *__restrict__ Es, const double *__restrict__ qf,
-                                  const double *__restrict__ qcs, const GridDev &g, double *lds) {
+template <bool STREAM>
+__device__ __forceinline__ void chain_link(ChainStream &stream, const double *__restrict__ Es,
+                                           const double *__restrict__ En, const double *__restrict__ qf,
+                                           const double *__restrict__ qcs, const GridDev &g, double *lds) {
 #pragma clang fp contract(off)
     const int Q1 = g.nq + 1;
     double *qc = lds;               // Q1: current knots
@@ -710,24 +819,28 @@ __device__ inline void chain_link(const double *__restrict__ Es, const double *_
     for (int i = threadIdx.x; i < g.cells; i += blockDim.x)
         rho[i] = (i == 0) ? c[1] : (i == g.cells - 1) ? 1.0 - c[g.cells - 1] : c[i + 1] - c[i];
     __syncthreads();
-    for (int r0 = wave; r0 < g.cells; r0 += nw * CHAIN_ROWS) {
-        const double *rows[CHAIN_ROWS];
-        double acc[CHAIN_ROWS];
+    if constexpr (STREAM) {
+        stream.product(Es, En, rho, g.cells, rho2);
+    } else {
+        for (int r0 = wave; r0 < g.cells; r0 += nw * CHAIN_ROWS) {
+            const double *rows[CHAIN_ROWS];
+            double acc[CHAIN_ROWS];
 #pragma unroll
-        for (int k = 0; k < CHAIN_ROWS; ++k) {
-            const int r = r0 + k * nw;
-            rows[k] = Es + (int64_t)(r < g.cells ? r : r0) * g.cells;
-        }
-        lane_rows_dot<CHAIN_ROWS, 4>(rows, rho, g.cells, lane, acc);
+            for (int k = 0; k < CHAIN_ROWS; ++k) {
+                const int r = r0 + k * nw;
+                rows[k] = Es + (int64_t)(r < g.cells ? r : r0) * g.cells;
+            }
+            lane_rows_dot<CHAIN_ROWS, 4>(rows, rho, g.cells, lane, acc);
 #pragma unroll
-        for (int k = 0; k < CHAIN_ROWS; ++k) {
-            const double a = wave_sum(acc[k]);
-            const int r = r0 + k * nw;
-            if (lane == 0 && r < g.cells) rho2[r] = a > 0.0 ? a : 0.0;
+            for (int k = 0; k < CHAIN_ROWS; ++k) {
+                const double a = wave_sum(acc[k]);
+                const int r = r0 + k * nw;
+                if (lane == 0 && r < g.cells) rho2[r] = a > 0.0 ? a : 0.0;
+            }
         }
     }
     __syncthreads();
-    masses_to_knots_block(rho2, C, g, qc);
+    masses_to_knots_block<STREAM ? CHAIN_STREAM_CELLS / 64 : 16>(rho2, C, g, qc);
     __syncthreads();
     if (qf) {
         if (j0 < Q1) qc[j0] = f0 + (qc[j0] - s0);
