@@ -253,22 +253,10 @@ __host__ __device__ inline bool mean_above(double a, int ca, double b, int cb) {
 // every merge that reaches lo): the values the serial pass over a longer
 // input would compare with the mean of the last pool before the stretch.
 // *lm receives the mean of the pool holding hi - 1.
-//
-// WAVE: called by a whole wave with the same arguments (every lane runs the
-// same scalar steps on the same values).  Where T holds more than one value
-// and the next value merges into it while B stays below, the wave takes the
-// run ahead at once: lane j adds v[i + j] to T's sum after the lanes before
-// it, in the serial order, and checks the two comparisons the serial pass
-// would make for that value; the longest prefix of lanes that pass is
-// committed (windows of 8 values, doubling up to 64 while whole windows
-// pass).  A decreasing run of L values then costs about L / 64 windows
-// instead of L serial steps.
-template <bool WAVE = false>
 __host__ __device__ inline int pava_sparse_range(const double *v, int lo, int hi, const int *vio, int nv,
                                                  double *S, int *SC, double *fm, double *lm) {
 #pragma clang fp contract(off)
     int nb = 0, vi = 0;
-    int win = 8;
     double fmin_ = v[lo];
     int i = vio[0];
     double tS = v[i], bS = 0.0;
@@ -280,20 +268,7 @@ __host__ __device__ inline int pava_sparse_range(const double *v, int lo, int hi
         if (tC == 1) {
             // first violation at or after i - 1 (a decreasing run leaves a
             // long stretch of consumed ones behind)
-            if constexpr (WAVE) {
-                // 64 entries per look, one per lane
-                const int lane = (int)(threadIdx.x & 63);
-                while (true) {
-                    const int idx = vi + lane;
-                    const uint64_t bm = __ballot(idx >= nv || vio[idx] >= i - 1);
-                    if (bm) {
-                        vi += __builtin_ctzll(bm);
-                        break;
-                    }
-                    vi += 64;
-                }
-                if (vi > nv) vi = nv;
-            } else {
+            {
                 int lo2 = vi, hi2 = nv;  // binary search
                 while (lo2 < hi2) {
                     const int mid = (lo2 + hi2) >> 1;
@@ -313,41 +288,6 @@ __host__ __device__ inline int pava_sparse_range(const double *v, int lo, int hi
                 i = jn + 1;
                 vcur = v[i];
             }
-        }
-        if constexpr (WAVE) {
-            if (tC > 1 && mean_above(tS, tC, vcur, 1) && (tSt == lo || !mean_above(bS, bC, vcur + tS, tC + 1))) {
-                const int lane = (int)(threadIdx.x & 63);
-                const int m = hi - i < win ? hi - i : win;
-                const double ve = lane < m ? v[i + lane] : 0.0;  // one load for the window
-                double acc = tS, prev = tS;  // T's sum before and after this lane's value
-                for (int k = 0; k < m; ++k) {
-                    const double vk = lane_value(ve, k);
-                    if (k <= lane) {
-                        prev = acc;
-                        acc = vk + acc;
-                    }
-                }
-                const int cb = tC + lane;
-                const bool ok = lane < m && mean_above(prev, cb, ve, 1) &&
-                                (tSt == lo || !mean_above(bS, bC, acc, cb + 1));
-                const uint64_t bad = __ballot(!ok);
-                const int f = bad ? __builtin_ctzll(bad) : 64;  // >= 1: lane 0 passes
-                if (tSt == lo) {
-                    double mm = lane < f ? acc / (double)(cb + 1) : INFINITY;
-                    for (int off = 32; off >= 1; off >>= 1) {
-                        const double o = __shfl_xor(mm, off);
-                        mm = o < mm ? o : mm;
-                    }
-                    if (mm < fmin_) fmin_ = mm;
-                }
-                tS = lane_value(acc, f - 1);
-                tC += f;
-                i += f;
-                win = f == m ? (win < 64 ? 2 * win : 64) : 8;
-                vcur = v[i < hi ? i : hi - 1];
-                continue;
-            }
-            win = 8;
         }
         double s = vcur;
         vcur = v[i + 1 < hi ? i + 1 : i];  // the next value, loaded ahead
@@ -411,6 +351,180 @@ __host__ __device__ inline int pava_sparse_range(const double *v, int lo, int hi
     return nb;
 }
 
+// pava_sparse_range by a whole wave, every lane with the same arguments and the
+// same scalar steps on the same values.  Bound by one wave's instructions and
+// branches, about 500 clocks a step; a step's two comparisons (T's mean against
+// the next value, B's against T's with that value) are taken together, and the
+// pool below B (A) is read from LDS as soon as it is known, not when B has been
+// merged.  Where values have merged into T alone PAVA_RUN times in a row, the
+// wave takes the run ahead at once: lane j adds v[i + j] to T's sum after the
+// lanes before it, in the serial order, and checks the two comparisons the
+// serial pass would make for that value; the longest prefix of lanes that pass
+// is committed (windows of 8 values, doubling up to 64 while whole windows
+// pass), so that a decreasing run of L values costs about L / 64 windows.  A
+// window costs as much as five steps: taken only for runs, a stretch of 432
+// noisy values takes 240,000 clocks (294,000 with a window tried at every such
+// value), one of 300 values with 50 violations 146,000 (170,000).
+constexpr int PAVA_RUN = 4;
+
+__device__ inline int pava_wave_range(const double *v, int lo, int hi, const int *vio, int nv, double *S, int *SC,
+                                      double *fm, double *lm) {
+#pragma clang fp contract(off)
+    const int lane = (int)(threadIdx.x & 63);
+    int nb = 0, vi = 0, win = 8, run = 0;
+    double fmin_ = v[lo];
+    int i = vio[0];
+    double tS = v[i], bS = 0.0;
+    int tC = 1, tSt = i, bC = 1, bSt = i - 1;
+    if (i > lo) bS = v[i - 1];
+    // the pool below B as loaded: the last stored one under B, and the value
+    // before B, which is a pool of its own unless that pool ends there
+    int aSC = 0, aN = 0;
+    double aS = 0.0, aV = 0.0;
+    auto load_a = [&]() {
+        aN = nb - (bC > 1 ? 1 : 0);  // stored pools under B
+        const int k = lo + (aN > 0 ? aN - 1 : 0);
+        aSC = SC[k];
+        aS = S[k];
+        aV = v[bSt > lo ? bSt - 1 : lo];
+    };
+    load_a();
+    ++i;
+    double vcur = v[i < hi ? i : hi - 1];
+    while (i < hi) {
+        if (tC == 1) {
+            // first violation at or after i - 1 (a decreasing run leaves a
+            // long stretch of consumed ones behind): 64 entries per look
+            int at = vi < nv ? vio[vi] : hi;
+            if (at < i - 1) {
+                while (true) {
+                    const int idx = vi + lane;
+                    const uint64_t bm = __ballot(idx >= nv || vio[idx] >= i - 1);
+                    if (bm) {
+                        vi += __builtin_ctzll(bm);
+                        break;
+                    }
+                    vi += 64;
+                }
+                if (vi > nv) vi = nv;
+                at = vi < nv ? vio[vi] : hi;
+            }
+            if (vi == nv) break;  // non-decreasing from v[i-1] on
+            if (at > i - 1) {
+                tSt = at;
+                tS = v[at];
+                bSt = at - 1;  // a single value: the values since i - 1 stay single
+                bS = v[at - 1];
+                bC = 1;
+                load_a();
+                i = at + 1;
+                vcur = v[i];
+            }
+        }
+        const bool into = mean_above(tS, tC, vcur, 1);
+        const double s1 = vcur + tS;
+        const bool onto = tSt != lo && mean_above(bS, bC, s1, tC + 1);
+        if (into && !onto) {
+            if (tC == 1 || run < PAVA_RUN) {
+                vcur = v[i + 1 < hi ? i + 1 : i];  // the next value
+                tS = s1;
+                ++tC;
+                ++i;
+                ++run;
+                win = 8;
+                if (tSt == lo) {
+                    const double m = tS / (double)tC;
+                    if (m < fmin_) fmin_ = m;
+                }
+                continue;
+            }
+            const int m = hi - i < win ? hi - i : win;
+            const double ve = lane < m ? v[i + lane] : 0.0;  // one load for the window
+            double acc = tS, prev = tS;  // T's sum before and after this lane's value
+            for (int k = 0; k < m; ++k) {
+                const double vk = lane_value(ve, k);
+                if (k <= lane) {
+                    prev = acc;
+                    acc = vk + acc;
+                }
+            }
+            const int cb = tC + lane;
+            const bool ok = lane < m && mean_above(prev, cb, ve, 1) &&
+                            (tSt == lo || !mean_above(bS, bC, acc, cb + 1));
+            const uint64_t bad = __ballot(!ok);
+            const int f = bad ? __builtin_ctzll(bad) : 64;  // >= 1: lane 0 passes
+            if (tSt == lo) {
+                double mm = lane < f ? acc / (double)(cb + 1) : INFINITY;
+                for (int off = 32; off >= 1; off >>= 1) {
+                    const double o = __shfl_xor(mm, off);
+                    mm = o < mm ? o : mm;
+                }
+                if (mm < fmin_) fmin_ = mm;
+            }
+            tS = lane_value(acc, f - 1);
+            tC += f;
+            i += f;
+            if (f < m) run = 0;
+            win = f == m ? (win < 64 ? 2 * win : 64) : 8;
+            vcur = v[i < hi ? i : hi - 1];
+            continue;
+        }
+        run = 0;
+        const double s0 = vcur;
+        vcur = v[i + 1 < hi ? i + 1 : i];
+        if (into) {
+            double s = s1;
+            int c = tC + 1, st = tSt;
+            do {  // B's mean is above
+                s = s + bS;
+                c = c + bC;
+                st = bSt;
+                if (bC > 1) --nb;  // B was the last stored pool
+                if (st == lo) {
+                    const double m = s / (double)c;
+                    if (m < fmin_) fmin_ = m;
+                    break;
+                }
+                if (aN > 0 && (aSC >> 16) + (aSC & 0xFFFF) == st) {
+                    bS = aS;
+                    bC = aSC & 0xFFFF;
+                    bSt = aSC >> 16;
+                } else {
+                    bS = aV;
+                    bC = 1;
+                    bSt = st - 1;
+                }
+                load_a();
+            } while (mean_above(bS, bC, s, c));
+            tS = s;
+            tC = c;
+            tSt = st;
+        } else {
+            if (tC > 1) {
+                S[lo + nb] = tS;
+                SC[lo + nb] = (tSt << 16) | tC;
+                ++nb;
+            }
+            bS = tS;
+            bC = tC;
+            bSt = tSt;
+            load_a();
+            tS = s0;
+            tC = 1;
+            tSt = i;
+        }
+        ++i;
+    }
+    *lm = (i - 1 == hi - 1) ? tS / (double)tC : v[hi - 1];
+    if (tC > 1) {
+        S[lo + nb] = tS;
+        SC[lo + nb] = (tSt << 16) | tC;
+        ++nb;
+    }
+    *fm = fmin_;
+    return nb;
+}
+
 // The same pass over the whole input v[0..L).
 __host__ __device__ inline void pava_sparse(const double *v, int L, const int *vio, int nv, double *S, int *SC,
                                             int *npools) {
@@ -422,7 +536,7 @@ __host__ __device__ inline void pava_sparse(const double *v, int L, const int *v
 // violations vio[0..nv) (increasing), with the arithmetic of the serial
 // stack form.  The input is cut where every value before is below every
 // value after (no pool can reach across such a cut); the stretches between
-// cuts that hold violations run pava_sparse_range, one wave each.  Where
+// cuts that hold violations run pava_wave_range, one wave each.  Where
 // the last pool of a stretch has a mean above a value the first pool of the
 // next one takes (rounding can put a pool's mean above its largest value),
 // the serial pass would have merged across the cut: those cuts are dropped
@@ -544,7 +658,7 @@ __device__ inline void pava_block_chunked(double *v, int L, const int *vio, int 
         const int nc = pc.nc;
         for (int k = w; k < nc; k += nt / 64) {  // one wave per stretch
             double fm, lm;
-            const int np = pava_sparse_range<true>(v, pc.cb[k], pc.cb[k + 1], vio + pc.fv[k],
+            const int np = pava_wave_range(v, pc.cb[k], pc.cb[k + 1], vio + pc.fv[k],
                                                    pc.fv[k + 1] - pc.fv[k], S, SC, &fm, &lm);
             if (lane == 0) {
                 pc.np[k] = np;
@@ -637,8 +751,8 @@ __device__ inline void pava_block_chunked(double *v, int L, const int *vio, int 
 
 // Pool-adjacent-violators over v[0..L) (L < 65536) by the whole block, with
 // the arithmetic of the serial stack form: the violations v[j] > v[j+1] are found
-// in parallel; without any, v is already the result; otherwise one thread
-// builds the pools with pava_sparse and the block writes their means.  LDS:
+// in parallel; without any, v is already the result; otherwise one wave
+// builds the pools and the block writes their means.  LDS:
 // S [L] doubles, SC and vio [L] ints.  Every thread of the block calls it.
 __device__ inline void pava_block(double *v, int L, double *S, int *SC, int *vio) {
 #pragma clang fp contract(off)
@@ -665,7 +779,7 @@ __device__ inline void pava_block(double *v, int L, double *S, int *SC, int *vio
     __syncthreads();
     if (w == 0) {  // the whole first wave runs the pass
         double fm, lm;
-        const int np = pava_sparse_range<true>(v, 0, L, vio, nbad, S, SC, &fm, &lm);
+        const int np = pava_wave_range(v, 0, L, vio, nbad, S, SC, &fm, &lm);
         if (lane == 0) npools = np;
     }
     __syncthreads();
