@@ -45,14 +45,14 @@ WORKLOAD = dict(lam=1.0, beta=2.0, eps=0.01, n=2 ** 20, dt=1e-4, T=10.0, K=64, c
 # isolated builds of each part.  The figure changes only with the method's
 # arithmetic, so that the fraction moves with speed alone.
 VALU_OPS_PER_STEP = 79
-# What the compiled kernel issues per particle-step by SQ_INSTS_VALU (154.06
-# per wave-step of two particles), valid while the sources hash to
+# What the compiled kernel issues per particle-step by SQ_INSTS_VALU, valid
+# while the sources hash to
 # FINE_SOURCES_SHA256: two fewer than the frozen figure, since the slow part's
 # cubic and linear terms are one polynomial in x (update 9) and the step loop,
 # unrolled twice with a 32-bit counter on the scalar unit, has no copies of
 # the state and no vector compare.  Its rate against the peak is the issue
 # utilisation.
-KERNEL_VALU_PER_STEP = 154.06 / 2
+KERNEL_VALU_PER_STEP = 77.06
 # MI355X: 256 CUs x 4 SIMDs x 16 lanes per clock x 2.4 GHz = VALU lane-ops/s
 VALU_PEAK = 256 * 64 * 2.4e9
 HBM_PEAK = 8.0e12  # B/s
@@ -70,8 +70,8 @@ FP64_FLOP_PER_STEP = 15
 # HBM bytes of one launch of the fine kernel (all 64 slices) from two
 # rocprofv3 counter passes, FETCH_SIZE x 2.0 (the factor a 1 GiB copy needs)
 # + WRITE_SIZE, valid while the kernel's sources hash to FINE_SOURCES_SHA256.
-FINE_TRAFFIC_BYTES = (524440 * 2 + 1048576) * 1024
-FINE_SOURCES_SHA256 = "ae8a2ccd719189505a28721d0c149e5f8e6851200a8ae949f78d752ad4ff2273"
+FINE_TRAFFIC_BYTES = (524485 * 2 + 1048576) * 1024
+FINE_SOURCES_SHA256 = "bfa2a87f9bfbb7603ba7abc8387d7f019566b051ff84dba14d95c1ea65de649c"
 FINE_SOURCES = ["pr_fine.hip", "pr_fine_dev.hpp", "pr_internal.hpp", "pr_normal.hpp", "pr_fastmath.hpp",
                 "pr_noise_tables.inc"]
 
@@ -152,10 +152,10 @@ ADJOINT = dict(lam=1.0, beta=2.0, eps=0.1, c3=1.0, n=2 ** 20, S=10_000, dt=1e-4,
 # VALU instructions of one particle-step of forward + reverse sweep with four
 # seed vectors and checkpoints every 256 steps: the forward step (79, as the
 # fine propagator), the reverse sweep's two replays of it (2 x 79) and the
-# reverse recursion (the step's Jacobian and parameter derivatives, 29, and
-# per seed vector four gradient updates and the 2 x 2 transposed Jacobian
-# product, 10, for four vectors 40: 69): 306
-ADJ_OPS_PER_STEP = 79 + 2 * 79 + 69
+# reverse recursion (the step's Jacobian and parameter derivatives, 14, and
+# per seed vector five gradient updates and the 2 x 2 transposed Jacobian
+# product, 9, for four vectors 36: 50): 287
+ADJ_OPS_PER_STEP = 79 + 2 * 79 + 50
 
 
 def adjoint_measure(torch, pr):
@@ -625,7 +625,7 @@ def main():
     roofline = dict(bound="alu", achieved=achieved / 1e12, peak=VALU_PEAK / 1e12, unit="Tops/s",
                     frac=achieved / VALU_PEAK, traffic=traffic,
                     traffic_algorithmic=n * K * 32,
-                    kernel="fine_kernel<1,double,2> (all 64 slices, one launch)",
+                    kernel="fine_kernel<1,double> (all 64 slices, one launch)",
                     fine_ms=phases["fine"], fine_particle_steps_per_s=fine_rate,
                     ops_per_particle_step=VALU_OPS_PER_STEP,
                     kernel_ops_per_particle_step=KERNEL_VALU_PER_STEP if traffic is not None else None,
