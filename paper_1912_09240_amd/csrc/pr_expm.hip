@@ -82,11 +82,16 @@ struct alignas(8) Pair {  // 16 bytes at a multiple of 8 (rows of an odd length)
 // waves per SIMD and block hide the LDS reads (four waves of 32x32 per block
 // took 58 us where eight of 32x16 took 44), pairs of elements per load keep
 // the address arithmetic off the matrix pipe (100 -> 90 us); stages twice as
-// deep gave nothing.  W = 1 keeps 4x as many blocks where W = 2 would leave
+// deep gave nothing.  Two stages on their way in registers: creation at 1024
+// cells 1.15 -> 1.12 ms, at 333 (rows at the edge read element by element) 202
+// -> 170 us, at 200 140 -> 126 us; four and six gave nothing more, nor did
+// reads of clamped pairs in place of the edge's branches (1.20 ms at 1024).  W = 1 keeps 4x as many blocks where W = 2 would leave
 // most CUs idle (200 cells: 49 blocks, 16 otherwise).
 template <int W, int NW>
 __global__ void __launch_bounds__(64 * NW) expm_gemm(const GemmJob *__restrict__ jobs, int n) {
     constexpr int T = 32 * W;
+    constexpr int AHEAD = 2;  // stages on their way in registers, even (a stage's buffer is its parity)
+    static_assert(AHEAD % 2 == 0, "buffers by parity");
     static_assert(T * EX_K == 2 * 64 * NW, "a stage is one pair of each factor per thread");
     constexpr int WC = 4 * W * W / NW / W;  // 16-column tiles per wave (W rows of them)
     // strides that put the two k of a half wave's operand reads on different
@@ -108,8 +113,8 @@ __global__ void __launch_bounds__(64 * NW) expm_gemm(const GemmJob *__restrict__
     const int ar = tid / (EX_K / 2), ac = tid % (EX_K / 2) * 2, br = tid / (T / 2), bc = tid % (T / 2) * 2;
     const bool inner = row0 + T <= n && col0 + T <= n;
     const double *pa = J.A + (int64_t)min(row0 + ar, n - 1) * n, *pb = J.B + col0 + bc;
-    Pair ra, rb;
-    auto fetch = [&](int k0) {
+    Pair fa[AHEAD], fb[AHEAD];
+    auto fetch = [&](Pair &ra, Pair &rb, int k0) {
         if (inner && k0 + EX_K <= n) {
             ra = *(const Pair *)(pa + k0 + ac);
             rb = *(const Pair *)(pb + (int64_t)(k0 + br) * n);
@@ -121,36 +126,41 @@ __global__ void __launch_bounds__(64 * NW) expm_gemm(const GemmJob *__restrict__
             rb.b = okk && col0 + bc + 1 < n ? pb[(int64_t)(k0 + br) * n + 1] : 0.0;
         }
     };
-    auto stage = [&](int b) {
+    auto step = [&](int b, const Pair &ra, const Pair &rb) {
         As[b][ar][ac] = ra.a;
         As[b][ar][ac + 1] = ra.b;
         Bs[b][br][bc] = rb.a;
         Bs[b][br][bc + 1] = rb.b;
     };
-    if (ka < kb) {
-        fetch(ka);
-        stage(0);
-        int b = 0;
-        for (int k0 = ka; k0 < kb; k0 += EX_K, b ^= 1) {
-            __syncthreads();  // stage b is filled, stage b ^ 1 has been read
-            const bool more = k0 + EX_K < kb;
-            if (more) fetch(k0 + EX_K);
+    auto multiply = [&](int b) {
 #pragma unroll
-            for (int kk = 0; kk < EX_K; kk += 4) {
-                double a[W], v[WC];
+        for (int kk = 0; kk < EX_K; kk += 4) {
+            double a[W], v[WC];
 #pragma unroll
-                for (int i = 0; i < W; ++i) a[i] = As[b][wr + 16 * i + li][kk + lk];
+            for (int i = 0; i < W; ++i) a[i] = As[b][wr + 16 * i + li][kk + lk];
 #pragma unroll
-                for (int j = 0; j < WC; ++j) v[j] = Bs[b][kk + lk][wc + 16 * j + li];
+            for (int j = 0; j < WC; ++j) v[j] = Bs[b][kk + lk][wc + 16 * j + li];
 #pragma unroll
-                for (int i = 0; i < W; ++i)
+            for (int i = 0; i < W; ++i)
 #pragma unroll
-                    for (int j = 0; j < WC; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], v[j], acc[i][j], 0, 0, 0);
-            }
-            if (more) stage(b ^ 1);
+                for (int j = 0; j < WC; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], v[j], acc[i][j], 0, 0, 0);
         }
-    }
+    };
+#pragma unroll
+    for (int d = 0; d < AHEAD; ++d) fetch(fa[d], fb[d], ka + d * EX_K);
+    // a stage goes to the buffer that was read two stages ago (its readers have
+    // passed the last stage's barrier)
+    for (int k0 = ka; k0 < kb; k0 += AHEAD * EX_K)
+#pragma unroll
+        for (int d = 0; d < AHEAD; ++d) {
+            const int k = k0 + d * EX_K;
+            if (k >= kb) break;
+            step(d & 1, fa[d], fb[d]);
+            fetch(fa[d], fb[d], k + AHEAD * EX_K);
+            __syncthreads();
+            multiply(d & 1);
+        }
 #pragma unroll
     for (int i = 0; i < W; ++i)
 #pragma unroll
