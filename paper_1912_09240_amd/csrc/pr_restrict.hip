@@ -448,6 +448,7 @@ rs_scatter(const void *__restrict__ src, const uint32_t *__restrict__ vals_in, K
 //                   leaves in order, with the rank of every slot;
 //   ss_left         the buckets of SS_CAP..SS_BIG keys the same way, one block
 //                   per CU, and those that do not fit that digit by digit;
+//   ss_whole        both for a few ensembles of one bucket each;
 //   ss_finish       the rank of every particle from that of its slot (a tile's
 //                   particles of one bucket hold neighbouring slots: the ranks
 //                   are read as runs and put in particle order in LDS, none is
@@ -464,7 +465,7 @@ rs_scatter(const void *__restrict__ src, const uint32_t *__restrict__ vals_in, K
 // staged by particle block, a complete guarded radix sort behind) took 1.37 ms
 // where every bucket fitted and 5.70 ms where one did not, as for ensembles in
 // two narrow wells.  33 FP32 ensembles of 99,991: 98 us (four radix passes:
-// 170 us).  10 FP64 ensembles of 10^4: two kernels, 32 us (about forty
+// 170 us).  10 FP64 ensembles of 10^4: one kernel, 29 us (about forty
 // launches of radix passes, fix-up and their guarded repetition: 160 us).
 // ---------------------------------------------------------------------------
 constexpr int SS_B = 256;
@@ -490,7 +491,7 @@ static_assert(SS_RUN == 4 * SS_KEEP && SS_RUN == 16 * SS_LIST, "a run's lists an
 
 // Buckets of an ensemble of n keys: one where it fits a block, else one per
 // tile of 4096, at most SS_B.  Equal ensembles are one bucket up to SS_BIG keys
-// (10 of 10^4 keys: two kernels instead of seven), those of a segment table up
+// (10 of 10^4 keys: one kernel instead of seven), those of a segment table up
 // to SS_CAP: the others' distribution is launched in any case, and above SS_CAP
 // they would wait for one of 256 blocks in ss_left (637 segments of 2^12 to
 // 2^15 keys: that took 156 us, now 10).
@@ -1050,8 +1051,10 @@ struct BucketLds {
     uint16_t spos[SS_BT * IT];     // slot of the key in the bucket's input
 };
 
+// Whether the bucket fits IT keys per thread but was left for the digits is
+// returned, equal in every thread.
 template <typename K, bool VAR, int IT>
-__device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const SortLayout &L, int64_t tile,
+__device__ __forceinline__ bool bucket_by_block(const BucketArgs<K> &A, const SortLayout &L, int64_t tile,
                                                 BucketLds<K, IT> &S) {
     using V = typename KeyTraits<K>::V;
     constexpr int CAP = SS_BT * IT, SUB = BucketLds<K, IT>::SUB, PER = SUB / 2 / SS_BT;
@@ -1061,7 +1064,7 @@ __device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const So
     const uint32_t size = R.size;
     if (size == 0 || size > (uint32_t)CAP) {
         if (tid == 0) A.left[tile] = size == 0 ? BL_NONE : (size <= (uint32_t)SS_BIG ? BL_BIG : BL_HARD);
-        return;
+        return false;
     }
     const int64_t base = R.sbase + R.start;
     for (int i = tid; i < SUB / 2; i += SS_BT) S.count[i] = 0;
@@ -1150,7 +1153,7 @@ __device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const So
         __syncthreads();
     }
     if (tid == 0) A.left[tile] = S.too_big ? BL_HARD : BL_NONE;
-    if (S.too_big) return;
+    if (S.too_big) return true;
 #pragma unroll
     for (int i = 0; i < IT; ++i)
         if (w[i] != NONE) {
@@ -1212,7 +1215,7 @@ __device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const So
     if (R.nb == 1)
         for (int j = tid; j <= A.nq; j += SS_BT)
             A.q[(int64_t)R.qrow * (A.nq + 1) + j] = knot_of<K>(S.sk, R.sn, j, A.nq);
-    if (!A.perm) return;
+    if (!A.perm) return false;
     // the particles, by way of LDS (in the keys' own array)
     uint32_t v[IT];
 #pragma unroll
@@ -1231,6 +1234,7 @@ __device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const So
         const uint32_t idx = (uint32_t)tid + (uint32_t)i * SS_BT;
         if (idx < size) A.perm[base + idx] = sv[idx];
     }
+    return false;
 }
 
 template <typename K, bool VAR, int IT>
@@ -1408,6 +1412,29 @@ __device__ __forceinline__ void bucket_by_digits(const BucketArgs<K> &A, const S
             if (R.nb == 1)
                 for (int64_t i = tid; i < size; i += SS_BT) A.rank[base + i] = pos[1][i];
         }
+    }
+}
+
+// Ensembles of one bucket each, all of which fit IT keys per thread: the block
+// that finds its bucket hard takes the digits itself, and nothing is left for
+// another launch.  The digits' registers leave room for one block per CU, so
+// up to SS_WHOLE ensembles (FP64, us, this / ss_bucket_sort and ss_left: 64 of 1000
+// keys 10.3 / 17.2, 10 of 10^4 28.6 / 33.1, 64 of 7000 22.7 / 30.5; 1000 of 7000
+// 187 / 131, 2048 of 4000 117 / 80, 300 of 14000 190 / 186).
+constexpr int SS_WHOLE = 256;
+
+template <typename K, bool VAR, int IT>
+__global__ void __launch_bounds__(SS_BT) ss_whole(BucketArgs<K> A, SortLayout L) {
+    union Lds {
+        BucketLds<K, IT> bucket;
+        DigitsLds<K> digits;
+    };
+    __shared__ Lds S;
+    if (L.guard && *L.guard == 0) return;
+    const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
+    if (bucket_by_block<K, VAR, IT>(A, L, tile, S.bucket)) {
+        __syncthreads();  // its LDS has been read
+        bucket_by_digits<K, VAR>(A, L, tile, S.digits);
     }
 }
 
@@ -2220,13 +2247,17 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
         // runs' since the splitters were taken
         const BucketArgs<K> A{x, skeys, totals, bstart, split, out, vals[1], rank, perm,
                               payload ? (rank ? rank : vals[0]) : nullptr, xs, q, (uint32_t *)runq, nq};
-        if (!VAR && !many && max_n > SS_CAP)
-            hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT_BIG>), grid, dim3(SS_BT), 0, st, A, L);
-        else
-            hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT>), grid, dim3(SS_BT), 0, st, A, L);
-        PR_LAUNCHED();
-        hipLaunchKernelGGL((ss_left<K, VAR>), dim3((unsigned)std::min<int64_t>(total_tiles, 256)), dim3(SS_BT), 0, st, A,
-                           L, total_tiles);
+        const bool big = !VAR && !many && max_n > SS_CAP;  // ensembles of one bucket above SS_CAP
+        if (!many && L.nseg <= SS_WHOLE) {
+            if (big) hipLaunchKernelGGL((ss_whole<K, VAR, SS_IT_BIG>), grid, dim3(SS_BT), 0, st, A, L);
+            else hipLaunchKernelGGL((ss_whole<K, VAR, SS_IT>), grid, dim3(SS_BT), 0, st, A, L);
+        } else {
+            if (big) hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT_BIG>), grid, dim3(SS_BT), 0, st, A, L);
+            else hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT>), grid, dim3(SS_BT), 0, st, A, L);
+            PR_LAUNCHED();
+            hipLaunchKernelGGL((ss_left<K, VAR>), dim3((unsigned)std::min<int64_t>(total_tiles, 256)), dim3(SS_BT), 0,
+                               st, A, L, total_tiles);
+        }
         PR_LAUNCHED();
         if (many || mom) {
             const int64_t blocks = L.nseg + (many && rank ? total_tiles : 0);
