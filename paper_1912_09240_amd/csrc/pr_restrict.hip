@@ -445,10 +445,13 @@ rs_scatter(const void *__restrict__ src, const uint32_t *__restrict__ vals_in, K
 //                   (linear in the value between the bucket's bounds, which
 //                   keeps the order), every key counts the keys of its
 //                   sub-bucket that precede it by (key, slot), and the bucket
-//                   leaves in order, with the rank of every slot;
+//                   leaves in order, with the rank of every slot; where a
+//                   sub-bucket is crowded (ties, outliers, values of many
+//                   magnitudes), the bucket goes by the digits of its keys
+//                   instead, in LDS as well;
 //   ss_left         the buckets of SS_CAP..SS_BIG keys the same way, one block
-//                   per CU, and those that do not fit that digit by digit;
-//   ss_whole        both for a few ensembles of one bucket each;
+//                   per CU, and longer ones by digits in global memory (not
+//                   launched for ensembles of one bucket, which fit a block);
 //   ss_finish       the rank of every particle from that of its slot (a tile's
 //                   particles of one bucket hold neighbouring slots: the ranks
 //                   are read as runs and put in particle order in LDS, none is
@@ -478,7 +481,14 @@ constexpr int SS_IT = 7;                    // keys per thread of a bucket block
 constexpr int SS_CAP = SS_BT * SS_IT;       // 7168: two bucket blocks share a CU's LDS
 constexpr int SS_IT_BIG = 14;
 constexpr int SS_BIG = SS_BT * SS_IT_BIG;   // 14336: one block takes 148 KiB of it
-constexpr int SS_SUBMAX = 512;
+// Keys of a value sub-bucket above which the bucket goes by digits: the
+// counting's time grows with them and with the keys per thread, that of the
+// digits only with the latter.  FP32, 8 ensembles of 2^20 of 20,000 values (52 keys
+// each): 396 us counted, 359 by digits; FP64, 64 of them: 2.63 and 3.48 ms.
+template <typename K>
+constexpr uint32_t ss_crowded(uint32_t size) {
+    return (sizeof(K) == 8 ? 160u : 42u) << (size <= 1024 ? 2 : size <= 2048 ? 1 : 0);
+}
 // Above this the SS_B buckets average more than 4352 keys.  A bucket spans 64
 // samples and its two splitters are each a few samples off (thinned runs): its
 // size has a standard deviation of about 16 %, so one bucket in tens of
@@ -962,7 +972,7 @@ __device__ __forceinline__ double knot_of(const K *s, int64_t n, int j, int nq) 
     return v < b ? v : b;
 }
 
-enum BucketLeft : uint32_t { BL_NONE = 0, BL_BIG = 1, BL_HARD = 2 };
+enum BucketLeft : uint32_t { BL_NONE = 0, BL_BIG = 1, BL_CROWDED = 2, BL_LONG = 3 };
 
 // Moments of an ensemble from its tiles' sums, by the block's first wave.
 __device__ __forceinline__ void moments_of(const double *part, int64_t tile0, int nblk, int64_t n, double *mom) {
@@ -1049,12 +1059,177 @@ struct BucketLds {
     uint32_t red32[SS_BT / 64];
     int too_big;
     uint16_t spos[SS_BT * IT];     // slot of the key in the bucket's input
+    // by digits: a word of every key in slot order, the slots in the order so far
+    // and the next, a place per slot; 64-bit keys' own array has room for more
+    // than the words
+    uint16_t more[sizeof(K) == 4 ? 2 * SS_BT * IT : 2];
+    __device__ __forceinline__ uint32_t *words() { return reinterpret_cast<uint32_t *>(sk); }
+    __device__ __forceinline__ uint16_t *slots(int b) {
+        if constexpr (sizeof(K) == 4) return b ? more : spos;
+        else return reinterpret_cast<uint16_t *>(words() + SS_BT * IT) + b * (SS_BT * IT);
+    }
+    __device__ __forceinline__ uint16_t *places() {
+        if constexpr (sizeof(K) == 4) return more + SS_BT * IT;
+        else return spos;
+    }
 };
 
-// Whether the bucket fits IT keys per thread but was left for the digits is
-// returned, equal in every thread.
-template <typename K, bool VAR, int IT>
-__device__ __forceinline__ bool bucket_by_block(const BucketArgs<K> &A, const SortLayout &L, int64_t tile,
+// The slots in S.slots(cur) into the order of their words, by the bytes in
+// which the words differ at all (diff), least significant first: every wave ranks
+// its consecutive slots in order with ballot-built peer masks, so every pass is
+// stable.  Returns the buffer that holds the result.  Bound by the ranking's
+// vector operations, about 60 per key and pass, and the LDS reads before them;
+// held in loops, not unrolled, which leaves the kernels around it their registers.
+// Called by the whole block, behind a barrier; ends with one.
+template <typename Lds>
+__device__ __forceinline__ int slots_by_digits(Lds &S, int tid, int cur, uint32_t size, uint32_t diff) {
+    constexpr int NW = SS_BT / 64;
+    static_assert(NW * RS_RADIX <= Lds::SUB, "the counts take the sub-buckets' place");
+    uint16_t(*wcnt)[RS_RADIX] = reinterpret_cast<uint16_t(*)[RS_RADIX]>(S.count);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    const uint32_t per = (size + SS_BT - 1) / SS_BT, p0 = wave * per * 64 + lane, p1 = min(size, (wave + 1) * per * 64);
+    const uint32_t *word = S.words();
+    uint16_t *place = S.places();
+#pragma unroll 1
+    for (int shift = 0; shift < 32; shift += 8) {
+        if (((diff >> shift) & 0xFFu) == 0) continue;
+        const uint16_t *in = S.slots(cur);
+        uint16_t *out = S.slots(cur ^ 1);
+        cur ^= 1;
+        for (int i = lane; i < RS_RADIX / 2; i += 64) reinterpret_cast<uint32_t *>(wcnt[wave])[i] = 0;
+        wave_sync();
+        uint32_t next = p0 < p1 ? word[in[p0]] : 0u;  // read ahead of the ranking
+#pragma unroll 1
+        for (uint32_t i = 0, p = p0; i < per; ++i, p += 64) {
+            const bool valid = p < p1;
+            const uint32_t d = (next >> shift) & 0xFFu;
+            next = word[in[min(p + 64, size - 1)]];
+            const uint64_t peers = digit_peers(d, valid);
+            const uint32_t before = wcnt[wave][d];
+            if (valid) place[p] = (uint16_t)(before + (uint32_t)__popcll(peers & lt));
+            wave_sync();
+            if (valid && lane == 63 - __clzll(peers)) wcnt[wave][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
+            wave_sync();
+        }
+        __syncthreads();
+        uint32_t tot = 0;
+        if (tid < RS_RADIX)
+            for (int v = 0; v < NW; ++v) tot += wcnt[v][tid];
+        uint32_t at = block_exclusive<SS_BT>(tot, S.red32);
+        if (tid < RS_RADIX)
+            for (int v = 0; v < NW; ++v) {
+                const uint32_t c = wcnt[v][tid];
+                wcnt[v][tid] = (uint16_t)at;
+                at += c;
+            }
+        __syncthreads();
+#pragma unroll 4
+        for (uint32_t p = p0; p < p1; p += 64) {
+            const uint16_t slot = in[p];
+            out[wcnt[wave][(word[slot] >> shift) & 0xFFu] + place[p]] = slot;
+        }
+        __syncthreads();
+    }
+    return cur;
+}
+
+// The slots of a bucket in key order, whatever the values (ties, far outliers,
+// values of many magnitudes or not finite).  64-bit keys are sorted by 32 bits
+// from the highest in which any two differ on; what is left are short runs of
+// equal words, put in order by one thread each.  Only where a longer run is out of
+// order do the passes over both halves run.  diff: the bits in which keys differ;
+// key(slot) reads one.  Returns the buffer that holds the slots.
+template <typename K, int IT, typename Key>
+__device__ __forceinline__ int bucket_digits(BucketLds<K, IT> &S, int tid, uint32_t size, K diff, Key key) {
+    constexpr uint32_t RUN = 32;
+    uint32_t *word = S.words();
+    const int top = sizeof(K) == 8 && (uint64_t)diff >> 32 ? 32 - __builtin_clzll((unsigned long long)diff) : 0;
+    int cur = 0;
+#pragma unroll 1
+    for (int round = 0; round < 3; ++round) {
+        const int shift = round == 0 ? top : (round == 1 ? 0 : 32);
+        for (uint32_t i = tid; i < size; i += SS_BT) {
+            word[i] = (uint32_t)((uint64_t)key(i) >> shift);
+            if (round < 2) S.slots(cur)[i] = (uint16_t)i;
+        }
+        __syncthreads();
+        cur = slots_by_digits(S, tid, cur, size, (uint32_t)((uint64_t)diff >> shift));
+        if (round == 1) continue;
+        if (round == 2 || (diff & (((K)1 << top) - 1)) == 0) break;  // the words tell the keys apart
+        uint16_t *slot = S.slots(cur);
+        for (uint32_t p = tid; p + 1 < size; p += SS_BT) {
+            const uint32_t v = word[slot[p]];
+            if (word[slot[p + 1]] != v || (p > 0 && word[slot[p - 1]] == v)) continue;
+            uint32_t e = p + 2;  // the run [p, e)
+            while (e < size && e - p <= RUN && word[slot[e]] == v) ++e;
+            if (e - p > RUN) continue;
+            for (uint32_t i = p + 1; i < e; ++i) {
+                const uint16_t s = slot[i];
+                const K k = key(s);
+                uint32_t j = i;
+                for (; j > p && key(slot[j - 1]) > k; --j) slot[j] = slot[j - 1];
+                slot[j] = s;
+            }
+        }
+        __syncthreads();
+        for (uint32_t p = tid; p + 1 < size; p += SS_BT)
+            if (word[slot[p]] == word[slot[p + 1]] && key(slot[p]) > key(slot[p + 1])) S.too_big = 2;
+        __syncthreads();
+        if (S.too_big != 2) break;
+    }
+    return cur;
+}
+
+// The bucket by digits, with its outputs.
+template <typename K, int IT>
+__device__ __forceinline__ void bucket_by_digits_in_lds(const BucketArgs<K> &A, const BucketRef &R,
+                                                        BucketLds<K, IT> &S) {
+    using V = typename KeyTraits<K>::V;
+    int tid = threadIdx.x;
+    int64_t base = uniform_i64(R.sbase + R.start);
+    uint32_t size = (uint32_t)__builtin_amdgcn_readfirstlane((int)R.size);
+    // no address or bound is kept from the code before, whose registers it would take
+    asm volatile("" : "+v"(tid), "+s"(base), "+s"(size));
+    auto key = [&](uint32_t i) { return R.nb == 1 ? key_of(((const V *)A.x)[base + i]) : A.skeys[base + i]; };
+    K diff = 0;  // the bits in which any two keys differ
+    const K k0 = key(0);
+    for (uint32_t i0 = tid; i0 < size; i0 += 4 * SS_BT) {
+        K k[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) k[u] = key(i0 + u * SS_BT < size ? i0 + u * SS_BT : i0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) diff |= k[u] ^ k0;
+    }
+    diff = (K)uniform_i64((int64_t)ss_block_reduce<K>(diff, S.redk, [](K a, K c) { return (K)(a | c); }));
+    const uint16_t *slot = S.slots(bucket_digits<K, IT>(S, tid, size, diff, key));
+#pragma unroll 4
+    for (uint32_t i = tid; i < size; i += SS_BT) {
+        const K ok = key(slot[i]);
+        A.keys_out[base + i] = ok;
+        if (A.xs) A.xs[base + i] = value_of(ok);
+    }
+    uint16_t *place = S.places();
+    if (A.rank) {
+        uint32_t *rank = R.nb == 1 ? A.rank : A.frank;
+        for (uint32_t i = tid; i < size; i += SS_BT) place[slot[i]] = (uint16_t)i;
+        __syncthreads();
+        for (uint32_t i = tid; i < size; i += SS_BT) rank[base + i] = R.start + place[i];
+    }
+    __syncthreads();  // the sorted keys are written, the words are free
+    if (R.nb == 1)
+        for (int j = tid; j <= A.nq; j += SS_BT)
+            A.q[(int64_t)R.qrow * (A.nq + 1) + j] = knot_of<K>(A.keys_out + base, R.sn, j, A.nq);
+    if (!A.perm) return;
+    uint32_t *sv = S.words();
+    for (uint32_t i = tid; i < size; i += SS_BT) sv[i] = R.nb == 1 ? (uint32_t)slot[i] : A.perm[base + slot[i]];
+    __syncthreads();
+    for (uint32_t i = tid; i < size; i += SS_BT) A.perm[base + i] = sv[i];
+}
+
+// HERE: also where a sub-bucket is crowded (else left).
+template <typename K, bool VAR, int IT, bool HERE>
+__device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const SortLayout &L, int64_t tile,
                                                 BucketLds<K, IT> &S) {
     using V = typename KeyTraits<K>::V;
     constexpr int CAP = SS_BT * IT, SUB = BucketLds<K, IT>::SUB, PER = SUB / 2 / SS_BT;
@@ -1063,9 +1238,10 @@ __device__ __forceinline__ bool bucket_by_block(const BucketArgs<K> &A, const So
     const int tid = threadIdx.x;
     const uint32_t size = R.size;
     if (size == 0 || size > (uint32_t)CAP) {
-        if (tid == 0) A.left[tile] = size == 0 ? BL_NONE : (size <= (uint32_t)SS_BIG ? BL_BIG : BL_HARD);
-        return false;
+        if (tid == 0) A.left[tile] = size == 0 ? BL_NONE : (size <= (uint32_t)SS_BIG ? BL_BIG : BL_LONG);
+        return;
     }
+    if (HERE && tid == 0) A.left[tile] = BL_NONE;
     const int64_t base = R.sbase + R.start;
     for (int i = tid; i < SUB / 2; i += SS_BT) S.count[i] = 0;
     if (tid == 0) S.too_big = 0;
@@ -1132,7 +1308,7 @@ __device__ __forceinline__ bool bucket_by_block(const BucketArgs<K> &A, const So
             c[2 * i] = two & 0xFFFFu;
             c[2 * i + 1] = two >> 16;
             sum += c[2 * i] + c[2 * i + 1];
-            if (c[2 * i] > (uint32_t)SS_SUBMAX || c[2 * i + 1] > (uint32_t)SS_SUBMAX) S.too_big = 1;
+            if (max(c[2 * i], c[2 * i + 1]) > ss_crowded<K>(size)) S.too_big = 1;
         }
         const int lane = tid & 63, wave = tid >> 6;
         uint32_t inc = sum;
@@ -1152,8 +1328,11 @@ __device__ __forceinline__ bool bucket_by_block(const BucketArgs<K> &A, const So
         if (tid == SS_BT - 1) S.start[SUB] = (uint16_t)size;
         __syncthreads();
     }
-    if (tid == 0) A.left[tile] = S.too_big ? BL_HARD : BL_NONE;
-    if (S.too_big) return true;
+    if (!HERE && tid == 0) A.left[tile] = S.too_big ? BL_CROWDED : BL_NONE;
+    if (S.too_big) {
+        if constexpr (HERE) bucket_by_digits_in_lds<K, IT>(A, R, S);
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < IT; ++i)
         if (w[i] != NONE) {
@@ -1215,7 +1394,7 @@ __device__ __forceinline__ bool bucket_by_block(const BucketArgs<K> &A, const So
     if (R.nb == 1)
         for (int j = tid; j <= A.nq; j += SS_BT)
             A.q[(int64_t)R.qrow * (A.nq + 1) + j] = knot_of<K>(S.sk, R.sn, j, A.nq);
-    if (!A.perm) return false;
+    if (!A.perm) return;
     // the particles, by way of LDS (in the keys' own array)
     uint32_t v[IT];
 #pragma unroll
@@ -1234,14 +1413,21 @@ __device__ __forceinline__ bool bucket_by_block(const BucketArgs<K> &A, const So
         const uint32_t idx = (uint32_t)tid + (uint32_t)i * SS_BT;
         if (idx < size) A.perm[base + idx] = sv[idx];
     }
-    return false;
 }
 
-template <typename K, bool VAR, int IT>
-__global__ void __launch_bounds__(SS_BT) ss_bucket_sort(BucketArgs<K> A, SortLayout L) {
+// With SS_IT keys per thread two blocks share a CU, which leaves FP64 no registers
+// for the digits in the same kernel (64 ensembles of 2^20: 1.26 ms, 1.41 with
+// them); up to SS_WHOLE ensembles of one such bucket each one block per CU is
+// enough, and nothing is left for another launch (64 of 1000 keys 17.7 us, 23.0 in
+// two launches).
+constexpr int SS_WHOLE = 256;
+
+template <typename K, bool VAR, int IT, bool HERE>
+__global__ void __launch_bounds__(SS_BT, IT <= SS_IT && (!HERE || sizeof(K) == 4) ? 8 : 4)
+ss_bucket_sort(BucketArgs<K> A, SortLayout L) {
     if (L.guard && *L.guard == 0) return;
     __shared__ BucketLds<K, IT> S;
-    bucket_by_block<K, VAR, IT>(A, L, xcd_tile(blockIdx.x, gridDim.x), S);
+    bucket_by_block<K, VAR, IT, HERE>(A, L, xcd_tile(blockIdx.x, gridDim.x), S);
 }
 
 // Tile j of this block's share.  Neighbouring ensembles mostly leave the same
@@ -1263,14 +1449,12 @@ __device__ __forceinline__ int tiles_left(const uint32_t *left, int64_t tiles, i
     return *count;
 }
 
-// A bucket of more than SS_BIG keys (mostly one value taken by many particles)
-// or with a sub-bucket above SS_SUBMAX (ties, far outliers, values that are
-// not finite).  One block orders such a bucket in
-// global memory by the digits in which its keys differ at all, least
-// significant first; every pass is stable, so equal keys stay in slot order.
-// The keys alternate between the scattered and the sorted keys' stretches
-// (the first pass reads the scattered ones, or the values), their slots
-// between tmp and frank.
+// A bucket of more than SS_BIG keys, one of several of its ensemble.  One block
+// orders it in global memory by the digits in which its keys differ at all,
+// least significant first; every pass is stable, so equal keys stay in slot
+// order.  The keys alternate between the scattered and the sorted keys'
+// stretches (the first pass reads the scattered ones), their slots between tmp
+// and frank.
 template <typename K>
 struct DigitsLds {
     K redk[SS_BT / 64];
@@ -1282,7 +1466,6 @@ struct DigitsLds {
 template <typename K, bool VAR>
 __device__ __forceinline__ void bucket_by_digits(const BucketArgs<K> &A, const SortLayout &L, int64_t tile,
                                                  DigitsLds<K> &S) {
-    using V = typename KeyTraits<K>::V;
     constexpr int NW = SS_BT / 64, IT = 4, STEP = SS_BT * IT;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const uint64_t lt = (1ull << lane) - 1ull;
@@ -1294,32 +1477,24 @@ __device__ __forceinline__ void bucket_by_digits(const BucketArgs<K> &A, const S
     // the first buffer holds the keys; the digits in which they differ (eight
     // loads in flight per thread: one block reads the whole bucket)
     K diff = 0;
-    const K k0 = R.nb == 1 ? key_of(((const V *)A.x)[base]) : buf[0][0];
+    const K k0 = buf[0][0];
     for (int64_t i0 = tid; i0 < size; i0 += 8 * SS_BT) {
         K k[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int64_t i = i0 + u * SS_BT < size ? i0 + u * SS_BT : i0;
-            if (R.nb == 1) k[u] = key_of(((const V *)A.x)[base + i]);
-            else k[u] = buf[0][i];
+            k[u] = buf[0][i];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            diff |= k[u] ^ k0;
-            if (R.nb == 1 && i0 + u * SS_BT < size) buf[0][i0 + u * SS_BT] = k[u];
-        }
+        for (int u = 0; u < 8; ++u) diff |= k[u] ^ k0;
     }
     diff = ss_block_reduce<K>(diff, S.redk, [](K a, K c) { return (K)(a | c); });
     if (diff == 0) {  // one value: already in order, slot by slot
-        uint32_t *rank = R.nb == 1 ? A.rank : A.frank;
         for (int64_t i = tid; i < size; i += SS_BT) {
             buf[1][i] = k0;
-            if (A.rank) rank[base + i] = R.start + (uint32_t)i;
-            if (A.perm && R.nb == 1) A.perm[base + i] = (uint32_t)i;
+            if (A.rank) A.frank[base + i] = R.start + (uint32_t)i;
             if (A.xs) A.xs[base + i] = value_of(k0);
         }
-        if (R.nb == 1)
-            for (int j = tid; j <= A.nq; j += SS_BT) A.q[(int64_t)R.qrow * (A.nq + 1) + j] = value_of(k0);
         return;
     }
     if (payload)
@@ -1390,56 +1565,22 @@ __device__ __forceinline__ void bucket_by_digits(const BucketArgs<K> &A, const S
     __syncthreads();
     if (A.xs)
         for (int64_t i = tid; i < size; i += SS_BT) A.xs[base + i] = value_of(buf[1][i]);
-    if (R.nb == 1)
-        for (int j = tid; j <= A.nq; j += SS_BT)
-            A.q[(int64_t)R.qrow * (A.nq + 1) + j] = knot_of<K>(buf[1], R.sn, j, A.nq);
     if (payload) {
         // pos[0] holds the slots in key order (in the rank array, where
         // ranks are asked for)
         if (A.perm) {
-            if (R.nb == 1) {
-                for (int64_t i = tid; i < size; i += SS_BT) A.perm[base + i] = pos[0][i];
-            } else {
-                for (int64_t i = tid; i < size; i += SS_BT) pos[1][i] = A.perm[base + pos[0][i]];
-                __syncthreads();
-                for (int64_t i = tid; i < size; i += SS_BT) A.perm[base + i] = pos[1][i];
-            }
+            for (int64_t i = tid; i < size; i += SS_BT) pos[1][i] = A.perm[base + pos[0][i]];
+            __syncthreads();
+            for (int64_t i = tid; i < size; i += SS_BT) A.perm[base + i] = pos[1][i];
             __syncthreads();
         }
-        if (A.rank) {
+        if (A.rank)
             for (int64_t i = tid; i < size; i += SS_BT) pos[1][pos[0][i]] = R.start + (uint32_t)i;
-            __syncthreads();
-            if (R.nb == 1)
-                for (int64_t i = tid; i < size; i += SS_BT) A.rank[base + i] = pos[1][i];
-        }
-    }
-}
-
-// Ensembles of one bucket each, all of which fit IT keys per thread: the block
-// that finds its bucket hard takes the digits itself, and nothing is left for
-// another launch.  The digits' registers leave room for one block per CU, so
-// up to SS_WHOLE ensembles (FP64, us, this / ss_bucket_sort and ss_left: 64 of 1000
-// keys 10.3 / 17.2, 10 of 10^4 28.6 / 33.1, 64 of 7000 22.7 / 30.5; 1000 of 7000
-// 187 / 131, 2048 of 4000 117 / 80, 300 of 14000 190 / 186).
-constexpr int SS_WHOLE = 256;
-
-template <typename K, bool VAR, int IT>
-__global__ void __launch_bounds__(SS_BT) ss_whole(BucketArgs<K> A, SortLayout L) {
-    union Lds {
-        BucketLds<K, IT> bucket;
-        DigitsLds<K> digits;
-    };
-    __shared__ Lds S;
-    if (L.guard && *L.guard == 0) return;
-    const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
-    if (bucket_by_block<K, VAR, IT>(A, L, tile, S.bucket)) {
-        __syncthreads();  // its LDS has been read
-        bucket_by_digits<K, VAR>(A, L, tile, S.digits);
     }
 }
 
 // What ss_bucket_sort left: the buckets of SS_CAP..SS_BIG keys by one block
-// with most of a CU's LDS, then the ones for the digits.
+// with most of a CU's LDS, then the longer ones.
 template <typename K, bool VAR>
 __global__ void __launch_bounds__(SS_BT) ss_left(BucketArgs<K> A, SortLayout L, int64_t tiles) {
     union Lds {
@@ -1453,11 +1594,16 @@ __global__ void __launch_bounds__(SS_BT) ss_left(BucketArgs<K> A, SortLayout L, 
     for (int64_t c = 0; c * SS_BT * gridDim.x < tiles; ++c) {
         const int big = tiles_left(A.left, tiles, c, BL_BIG, list, &count);
         for (int i = 0; i < big; ++i) {
-            bucket_by_block<K, VAR, SS_IT_BIG>(A, L, shared_tile(c * SS_BT + list[i]), S.bucket);
+            bucket_by_block<K, VAR, SS_IT_BIG, true>(A, L, shared_tile(c * SS_BT + list[i]), S.bucket);
             __syncthreads();
         }
-        const int hard = tiles_left(A.left, tiles, c, BL_HARD, list, &count);
-        for (int i = 0; i < hard; ++i) {
+        const int crowded = tiles_left(A.left, tiles, c, BL_CROWDED, list, &count);
+        for (int i = 0; i < crowded; ++i) {
+            bucket_by_digits_in_lds<K, SS_IT_BIG>(A, bucket_ref<K, VAR>(L, A, shared_tile(c * SS_BT + list[i])), S.bucket);
+            __syncthreads();
+        }
+        const int longer = tiles_left(A.left, tiles, c, BL_LONG, list, &count);
+        for (int i = 0; i < longer; ++i) {
             bucket_by_digits<K, VAR>(A, L, shared_tile(c * SS_BT + list[i]), S.digits);
             __syncthreads();
         }
@@ -2248,17 +2394,19 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
         const BucketArgs<K> A{x, skeys, totals, bstart, split, out, vals[1], rank, perm,
                               payload ? (rank ? rank : vals[0]) : nullptr, xs, q, (uint32_t *)runq, nq};
         const bool big = !VAR && !many && max_n > SS_CAP;  // ensembles of one bucket above SS_CAP
-        if (!many && L.nseg <= SS_WHOLE) {
-            if (big) hipLaunchKernelGGL((ss_whole<K, VAR, SS_IT_BIG>), grid, dim3(SS_BT), 0, st, A, L);
-            else hipLaunchKernelGGL((ss_whole<K, VAR, SS_IT>), grid, dim3(SS_BT), 0, st, A, L);
-        } else {
-            if (big) hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT_BIG>), grid, dim3(SS_BT), 0, st, A, L);
-            else hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT>), grid, dim3(SS_BT), 0, st, A, L);
-            PR_LAUNCHED();
+        const bool here = sizeof(K) == 4 || big || (!many && L.nseg <= SS_WHOLE);
+        if (big)
+            hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT_BIG, true>), grid, dim3(SS_BT), 0, st, A, L);
+        else if (here)
+            hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT, true>), grid, dim3(SS_BT), 0, st, A, L);
+        else
+            hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT, sizeof(K) == 4>), grid, dim3(SS_BT), 0, st, A, L);
+        PR_LAUNCHED();
+        if (many || !here) {
             hipLaunchKernelGGL((ss_left<K, VAR>), dim3((unsigned)std::min<int64_t>(total_tiles, 256)), dim3(SS_BT), 0,
                                st, A, L, total_tiles);
+            PR_LAUNCHED();
         }
-        PR_LAUNCHED();
         if (many || mom) {
             const int64_t blocks = L.nseg + (many && rank ? total_tiles : 0);
             hipLaunchKernelGGL((ss_finish<K, VAR>), dim3((unsigned)blocks), dim3(SC_THREADS), 0, st,
