@@ -575,6 +575,15 @@ struct BucketSearch {
     }
 };
 
+// Whether bucket d of nb holds copies of one value only, by their splitters.  The
+// scatter then writes it where the sorted keys go, and the rank of every slot
+// is the slot's own number: nothing is left of it for a block of its own, however
+// long it is (2^20 + 2^16 equal FP32 keys: 272 -> 89 us, FP64 399 -> 110).
+template <typename K>
+__device__ __forceinline__ bool one_value(const K *split, int d, int nb) {
+    return d > 0 && d + 1 < nb && split[d] == split[d + 1];
+}
+
 // Merge of the sorted lists of len keys in a[0..m) (m / len a power of two)
 // into out, pairs of neighbouring lists: a key's place is its index plus the
 // number of the partner list's keys before it, equal keys of the first list
@@ -844,12 +853,14 @@ __device__ __forceinline__ uint64_t digit_peers(uint32_t d, bool valid) {
 template <typename K, bool VAR>
 __global__ void __launch_bounds__(SC_THREADS)
 ss_scatter(const void *__restrict__ src, const uint32_t *bucket, const K *__restrict__ split,
-           K *__restrict__ keys_out, uint32_t *slots, uint32_t *__restrict__ pv, const uint32_t *__restrict__ counts,
-           const uint32_t *__restrict__ totals, SortLayout L, uint32_t *__restrict__ bstart) {
+           K *__restrict__ keys_out, K *__restrict__ sorted, double *__restrict__ xs, uint32_t *slots,
+           uint32_t *__restrict__ pv, const uint32_t *__restrict__ counts, const uint32_t *__restrict__ totals,
+           SortLayout L, uint32_t *__restrict__ bstart) {
     using V = typename KeyTraits<K>::V;
     constexpr int TILE = RS_THREADS * RS_ITEMS, ITEMS = TILE / SC_THREADS, WAVE_KEYS = 64 * ITEMS;
     __shared__ uint32_t wcnt[SC_WAVES][RS_RADIX];  // keys of a wave's bucket, then its first place in the tile
     __shared__ uint32_t gdelta[RS_RADIX];
+    __shared__ bool same[RS_RADIX];
     __shared__ uint32_t wtot[SC_WAVES];
     __shared__ alignas(16) K stage[TILE];
     __shared__ uint8_t sdig[TILE];
@@ -914,6 +925,7 @@ ss_scatter(const void *__restrict__ src, const uint32_t *bucket, const K *__rest
                 acc += c;
             }
             gdelta[d] = dbase + counts[T.tile0 * RS_RADIX + (int64_t)d * T.nblk + T.blk] - ls;
+            same[d] = one_value(split + (int64_t)T.seg * SS_B, d, nb);
             if (T.blk == 0) bstart[(int64_t)T.seg * RS_RADIX + d] = dbase;
         }
     }
@@ -937,10 +949,12 @@ ss_scatter(const void *__restrict__ src, const uint32_t *bucket, const K *__rest
         const int j = tid + r * SC_THREADS;
         gpos[r] = 0xFFFFFFFFu;
         if (j < tile_n) {
-            const uint32_t g = (uint32_t)j + gdelta[sdig[j]];
+            const uint32_t d = sdig[j], g = (uint32_t)j + gdelta[d];
             if ((int64_t)g < T.n) {  // always true for a consistent scan
                 gpos[r] = g;
-                keys_out[T.base + g] = stage[j];
+                K *to = same[d] ? sorted : keys_out;
+                to[T.base + g] = stage[j];
+                if (xs && same[d]) xs[T.base + g] = value_of(stage[j]);
             }
         }
     }
@@ -1237,8 +1251,9 @@ __device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const So
     const BucketRef R = bucket_ref<K, VAR>(L, A, tile);
     const int tid = threadIdx.x;
     const uint32_t size = R.size;
-    if (size == 0 || size > (uint32_t)CAP) {
-        if (tid == 0) A.left[tile] = size == 0 ? BL_NONE : (size <= (uint32_t)SS_BIG ? BL_BIG : BL_LONG);
+    const bool done = size == 0 || one_value(A.split + (int64_t)R.seg * SS_B, R.b, R.nb);
+    if (done || size > (uint32_t)CAP) {
+        if (tid == 0) A.left[tile] = done ? BL_NONE : (size <= (uint32_t)SS_BIG ? BL_BIG : BL_LONG);
         return;
     }
     if (HERE && tid == 0) A.left[tile] = BL_NONE;
@@ -1614,14 +1629,15 @@ __global__ void __launch_bounds__(SS_BT) ss_left(BucketArgs<K> A, SortLayout L, 
 // bucket of every place of its tile, reads the ranks of those places' slots
 // (runs of neighbouring slots, one per bucket) into LDS and writes them in
 // particle order.
-template <bool VAR>
+template <typename K, bool VAR>
 __device__ __forceinline__ void ranks_of_tile(const uint32_t *slots, const uint32_t *frank, const uint32_t *counts,
-                                              const uint32_t *totals, const uint32_t *bstart, const SortLayout &L,
-                                              int64_t tile, uint32_t *rank) {
+                                              const uint32_t *totals, const uint32_t *bstart, const K *split,
+                                              const SortLayout &L, int64_t tile, uint32_t *rank) {
     constexpr int TILE = RS_THREADS * RS_ITEMS, ITEMS = TILE / SC_THREADS;
     __shared__ uint8_t sdig[TILE];
     __shared__ uint32_t sr[TILE];
     __shared__ uint32_t gdelta[SS_B], wtot[SC_WAVES];
+    __shared__ bool same[SS_B];
     const TileRef T = tile_ref<VAR>(L, tile);
     const int nb = ss_buckets<VAR>(T.n), tid = threadIdx.x;
     if (nb == 1) return;
@@ -1641,7 +1657,10 @@ __device__ __forceinline__ void ranks_of_tile(const uint32_t *slots, const uint3
         at = bstart[(int64_t)T.seg * SS_B + tid] + c[0];
     }
     const uint32_t ls = block_exclusive<SC_THREADS>(mine, wtot);
-    if (tid < nb) gdelta[tid] = at - ls;
+    if (tid < nb) {
+        gdelta[tid] = at - ls;
+        same[tid] = one_value(split + (int64_t)T.seg * SS_B, tid, nb);
+    }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i)
         if (s[i] != ~0u) sdig[s[i] & (TILE - 1)] = (uint8_t)(s[i] >> RK_SHIFT);
@@ -1651,7 +1670,8 @@ __device__ __forceinline__ void ranks_of_tile(const uint32_t *slots, const uint3
     for (int i = 0; i < ITEMS; ++i) {
         const int j = tid + i * SC_THREADS;
         const uint32_t g = j < tile_n ? (uint32_t)j + gdelta[sdig[j]] : ~0u;
-        r[i] = (int64_t)g < T.n ? frank[T.base + g] : 0u;
+        r[i] = g;
+        if ((int64_t)g < T.n && !same[sdig[j]]) r[i] = frank[T.base + g];
     }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) sr[tid + i * SC_THREADS] = r[i];
@@ -1668,11 +1688,12 @@ __global__ void __launch_bounds__(SC_THREADS)
 ss_finish(const K *__restrict__ sorted, int nq, double *__restrict__ q, const double *__restrict__ part,
           double *__restrict__ mom, const uint32_t *__restrict__ slots, const uint32_t *__restrict__ frank,
           const uint32_t *__restrict__ counts, const uint32_t *__restrict__ totals,
-          const uint32_t *__restrict__ bstart, SortLayout L, uint32_t *__restrict__ rank) {
+          const uint32_t *__restrict__ bstart, const K *__restrict__ split, SortLayout L,
+          uint32_t *__restrict__ rank) {
     if (L.guard && *L.guard == 0) return;
     if ((int64_t)blockIdx.x >= L.nseg) {
-        ranks_of_tile<VAR>(slots, frank, counts, totals, bstart, L,
-                           xcd_tile((int64_t)blockIdx.x - L.nseg, (int64_t)gridDim.x - L.nseg), rank);
+        ranks_of_tile<K, VAR>(slots, frank, counts, totals, bstart, split, L,
+                              xcd_tile((int64_t)blockIdx.x - L.nseg, (int64_t)gridDim.x - L.nseg), rank);
         return;
     }
     int64_t base, n, tile0;
@@ -2385,8 +2406,8 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
                                    counts, totals, L);
             PR_LAUNCHED();
             hipLaunchKernelGGL((ss_scatter<K, VAR>), grid, dim3(SC_THREADS), 0, st, x, (const uint32_t *)vals[0],
-                               (const K *)split, skeys, rank ? vals[0] : nullptr, perm, (const uint32_t *)counts,
-                               (const uint32_t *)totals, L, bstart);
+                               (const K *)split, skeys, out, xs, rank ? vals[0] : nullptr, perm,
+                               (const uint32_t *)counts, (const uint32_t *)totals, L, bstart);
             PR_LAUNCHED();
         }
         // the ranks' final array is free until ss_finish writes it, the
@@ -2412,7 +2433,7 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
             hipLaunchKernelGGL((ss_finish<K, VAR>), dim3((unsigned)blocks), dim3(SC_THREADS), 0, st,
                                many ? (const K *)out : nullptr, nq, q, mom ? (const double *)mom_part : nullptr, mom,
                                (const uint32_t *)vals[0], (const uint32_t *)vals[1], (const uint32_t *)counts,
-                               (const uint32_t *)totals, (const uint32_t *)bstart, L, rank);
+                               (const uint32_t *)totals, (const uint32_t *)bstart, (const K *)split, L, rank);
             PR_LAUNCHED();
         }
     } else if constexpr (std::is_same<K, uint64_t>::value) {

@@ -82,3 +82,52 @@ def test_time_of_crowded_values(n, k, prec):
             best = min(best, e0.elapsed_time(e1) * 1e3)
         us.append(best)
     assert max(us) < 5.0 * us[0], us
+
+
+@pytest.mark.parametrize("prec", [pr.PR_F64, pr.PR_F32])
+def test_time_of_one_value(prec):
+    """A bucket of copies of one value leaves with the scatter: equal values do
+    not take longer than smooth ones (by more than a quarter, the shortest of
+    several passes; one block that read and wrote them all took 2.9 to 3.9 times
+    as long)."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    n = 2 ** 20 + 2 ** 16
+    ws = torch.empty(pr.pr_restrict_workspace_size(n, 1, prec), dtype=torch.uint8, device="cuda")
+    q = torch.empty((1, 101), dtype=torch.float64, device="cuda")
+    rank = torch.empty((1, n), dtype=torch.int32, device="cuda")
+    smooth = np.random.default_rng(23).normal(0.0, 1.0, n)
+    us = []
+    for name, v in (("smooth", smooth), ("equal", np.full(n, 0.3)), ("half", np.where(smooth > 0, smooth, 0.0))):
+        print(f"one value time {name} precision={prec}", flush=True)
+        x = torch.from_numpy(v.astype(np.float64 if prec == pr.PR_F64 else np.float32)).cuda()
+        best = np.inf
+        for _ in range(20):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            pr.pr_restrict_quantiles(x, prec, n, 1, 100, q, ws, rank=rank)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1) * 1e3)
+        us.append(best)
+    assert max(us) < 1.25 * us[0], us
+
+
+@pytest.mark.parametrize("prec", [pr.PR_F64, pr.PR_F32])
+@pytest.mark.parametrize("n", [14_337, 20_000, 70_001])
+def test_buckets_of_one_value(n, prec):
+    """Values with buckets of their own beside others: the smallest, the
+    largest and one between, and all values equal."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"one value n={n} precision={prec}", flush=True)
+    rng = np.random.default_rng(24)
+    x = rng.normal(0.0, 1.0, (5, n))
+    part = rng.random((5, n)) < 0.6
+    for row, v in enumerate((-9.0, 9.0, 0.125, -0.0)):
+        x[row, part[row]] = v
+    x[3, ::3] = 0.0
+    x[4] = 2.5
+    _check(torch, np.ascontiguousarray(x.astype(np.float64 if prec == pr.PR_F64 else np.float32)), prec, 7)
