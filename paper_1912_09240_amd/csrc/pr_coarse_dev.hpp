@@ -253,124 +253,76 @@ __host__ __device__ inline bool mean_above(double a, int ca, double b, int cb) {
 // every merge that reaches lo): the values the serial pass over a longer
 // input would compare with the mean of the last pool before the stretch.
 // *lm receives the mean of the pool holding hi - 1.
-__host__ __device__ inline int pava_sparse_range(const double *v, int lo, int hi, const int *vio, int nv,
-                                                 double *S, int *SC, double *fm, double *lm) {
-#pragma clang fp contract(off)
-    int nb = 0, vi = 0;
-    double fmin_ = v[lo];
-    int i = vio[0];
-    double tS = v[i], bS = 0.0;
-    int tC = 1, tSt = i, bC = 1, bSt = i - 1;
-    if (i > lo) bS = v[i - 1];
-    ++i;
-    double vcur = v[i < hi ? i : hi - 1];
-    while (i < hi) {
-        if (tC == 1) {
-            // first violation at or after i - 1 (a decreasing run leaves a
-            // long stretch of consumed ones behind)
-            {
-                int lo2 = vi, hi2 = nv;  // binary search
-                while (lo2 < hi2) {
-                    const int mid = (lo2 + hi2) >> 1;
-                    if (vio[mid] < i - 1) lo2 = mid + 1;
-                    else hi2 = mid;
-                }
-                vi = lo2;
-            }
-            if (vi == nv) break;  // non-decreasing from v[i-1] on
-            const int jn = vio[vi];
-            if (jn > i - 1) {
-                tSt = jn;
-                tS = v[jn];
-                bSt = jn - 1;  // a single value: the values since i - 1 stay single
-                bS = v[jn - 1];
-                bC = 1;
-                i = jn + 1;
-                vcur = v[i];
-            }
-        }
-        double s = vcur;
-        vcur = v[i + 1 < hi ? i + 1 : i];  // the next value, loaded ahead
-        int c = 1, st = i;
-        if (mean_above(tS, tC, s, c)) {
-            s = s + tS;
-            c = c + tC;
-            st = tSt;
-            if (st == lo) {
-                const double m = s / (double)c;
-                if (m < fmin_) fmin_ = m;
-            }
-            while (st != lo && mean_above(bS, bC, s, c)) {
-                s = s + bS;
-                c = c + bC;
-                st = bSt;
-                if (bC > 1) --nb;  // B was the last stored pool
-                if (st == lo) {
-                    const double m = s / (double)c;
-                    if (m < fmin_) fmin_ = m;
-                } else {
-                    const int k = lo + (nb > 0 ? nb - 1 : 0);
-                    const int sc = SC[k];
-                    const double sv = S[k], vv = v[st - 1];
-                    if (nb > 0 && (sc >> 16) + (sc & 0xFFFF) == st) {
-                        bS = sv;
-                        bC = sc & 0xFFFF;
-                        bSt = sc >> 16;
-                    } else {
-                        bS = vv;
-                        bC = 1;
-                        bSt = st - 1;
-                    }
-                }
-            }
-            tS = s;
-            tC = c;
-            tSt = st;
-        } else {
-            if (tC > 1) {
-                S[lo + nb] = tS;
-                SC[lo + nb] = (tSt << 16) | tC;
-                ++nb;
-            }
-            bS = tS;
-            bC = tC;
-            bSt = tSt;
-            tS = s;
-            tC = 1;
-            tSt = i;
-        }
-        ++i;
-    }
-    *lm = (i - 1 == hi - 1) ? tS / (double)tC : v[hi - 1];
-    if (tC > 1) {
-        S[lo + nb] = tS;
-        SC[lo + nb] = (tSt << 16) | tC;
-        ++nb;
-    }
-    *fm = fmin_;
-    return nb;
-}
-
-// pava_sparse_range by a whole wave, every lane with the same arguments and the
-// same scalar steps on the same values.  Bound by one wave's instructions and
-// branches, about 500 clocks a step; a step's two comparisons (T's mean against
-// the next value, B's against T's with that value) are taken together, and the
-// pool below B (A) is read from LDS as soon as it is known, not when B has been
-// merged.  Where values have merged into T alone PAVA_RUN times in a row, the
-// wave takes the run ahead at once: lane j adds v[i + j] to T's sum after the
-// lanes before it, in the serial order, and checks the two comparisons the
-// serial pass would make for that value; the longest prefix of lanes that pass
-// is committed (windows of 8 values, doubling up to 64 while whole windows
-// pass), so that a decreasing run of L values costs about L / 64 windows.  A
-// window costs as much as five steps: taken only for runs, a stretch of 432
-// noisy values takes 240,000 clocks (294,000 with a window tried at every such
-// value), one of 300 values with 50 violations 146,000 (170,000).
+//
+// Run by a whole wave, every lane with the same arguments and the same scalar
+// steps on the same values.  Bound by one wave's instructions and branches, about
+// 500 clocks a step; a step's two comparisons (T's mean against the next value,
+// B's against T's with that value) are taken together, and the pool below B (A) is
+// read from LDS as soon as it is known, not when B has been merged.  Where values
+// have merged into T alone PAVA_RUN times in a row, the wave takes the run ahead
+// at once: lane j adds v[i + j] to T's sum after the lanes before it, in the
+// serial order, and checks the two comparisons the serial pass would make for that
+// value; the longest prefix of lanes that pass is committed (windows of 8 values,
+// doubling up to 64 while whole windows pass), so that a decreasing run of L
+// values costs about L / 64 windows.  A window costs as much as five steps: taken
+// only for runs, a stretch of 432 noisy values takes 240,000 clocks (294,000 with a
+// window tried at every such value), one of 300 values with 50 violations 146,000
+// (170,000).
+//
+// Lanes: the wave's own lanes, or 64 lanes in one host thread (PavaHostLanes), so
+// that the host runs every step the kernels run.
 constexpr int PAVA_RUN = 4;
 
-__device__ inline int pava_wave_range(const double *v, int lo, int hi, const int *vio, int nv, double *S, int *SC,
-                                      double *fm, double *lm) {
+struct PavaWaveLanes {
+    using Value = double;  // one per lane
+    static __device__ __forceinline__ int lane() { return (int)(threadIdx.x & 63); }
+    // f(lane) for every lane; lanes' values through of(x, lane)
+    template <class F>
+    static __device__ __forceinline__ void each(F f) {
+        f(lane());
+    }
+    static __device__ __forceinline__ double &of(Value &x, int) { return x; }
+    template <class F>
+    static __device__ __forceinline__ uint64_t ballot(F f) {
+        return __ballot(f(lane()));
+    }
+    static __device__ __forceinline__ double value(const Value &x, int l) { return lane_value(x, l); }
+    static __device__ __forceinline__ double smallest(Value x) {
+        for (int off = 32; off >= 1; off >>= 1) {
+            const double o = __shfl_xor(x, off);
+            x = o < x ? o : x;
+        }
+        return x;
+    }
+};
+
+struct PavaHostLanes {
+    struct Value {
+        double x[64];
+    };
+    template <class F>
+    static inline void each(F f) {
+        for (int l = 0; l < 64; ++l) f(l);
+    }
+    static inline double &of(Value &x, int l) { return x.x[l]; }
+    template <class F>
+    static inline uint64_t ballot(F f) {
+        uint64_t m = 0;
+        for (int l = 0; l < 64; ++l) m |= (uint64_t)(f(l) ? 1 : 0) << l;
+        return m;
+    }
+    static inline double value(const Value &x, int l) { return x.x[l]; }
+    static inline double smallest(const Value &x) {
+        double m = x.x[0];
+        for (double o : x.x) m = o < m ? o : m;
+        return m;
+    }
+};
+
+template <class Lanes>
+__host__ __device__ inline int pava_range(const double *v, int lo, int hi, const int *vio, int nv, double *S, int *SC,
+                                          double *fm, double *lm) {
 #pragma clang fp contract(off)
-    const int lane = (int)(threadIdx.x & 63);
     int nb = 0, vi = 0, win = 8, run = 0;
     double fmin_ = v[lo];
     int i = vio[0];
@@ -398,8 +350,8 @@ __device__ inline int pava_wave_range(const double *v, int lo, int hi, const int
             int at = vi < nv ? vio[vi] : hi;
             if (at < i - 1) {
                 while (true) {
-                    const int idx = vi + lane;
-                    const uint64_t bm = __ballot(idx >= nv || vio[idx] >= i - 1);
+                    const uint64_t bm =
+                        Lanes::ballot([&](int lane) { return vi + lane >= nv || vio[vi + lane] >= i - 1; });
                     if (bm) {
                         vi += __builtin_ctzll(bm);
                         break;
@@ -439,29 +391,35 @@ __device__ inline int pava_wave_range(const double *v, int lo, int hi, const int
                 continue;
             }
             const int m = hi - i < win ? hi - i : win;
-            const double ve = lane < m ? v[i + lane] : 0.0;  // one load for the window
-            double acc = tS, prev = tS;  // T's sum before and after this lane's value
+            typename Lanes::Value ve, acc, prev;  // T's sum before and after each lane's value
+            Lanes::each([&](int lane) {
+                Lanes::of(ve, lane) = lane < m ? v[i + lane] : 0.0;  // one load for the window
+                Lanes::of(acc, lane) = Lanes::of(prev, lane) = tS;
+            });
             for (int k = 0; k < m; ++k) {
-                const double vk = lane_value(ve, k);
-                if (k <= lane) {
-                    prev = acc;
-                    acc = vk + acc;
-                }
+                const double vk = Lanes::value(ve, k);
+                Lanes::each([&](int lane) {
+                    if (k <= lane) {
+                        Lanes::of(prev, lane) = Lanes::of(acc, lane);
+                        Lanes::of(acc, lane) = vk + Lanes::of(acc, lane);
+                    }
+                });
             }
-            const int cb = tC + lane;
-            const bool ok = lane < m && mean_above(prev, cb, ve, 1) &&
-                            (tSt == lo || !mean_above(bS, bC, acc, cb + 1));
-            const uint64_t bad = __ballot(!ok);
+            const uint64_t bad = Lanes::ballot([&](int lane) {
+                const int cb = tC + lane;
+                return !(lane < m && mean_above(Lanes::of(prev, lane), cb, Lanes::of(ve, lane), 1) &&
+                         (tSt == lo || !mean_above(bS, bC, Lanes::of(acc, lane), cb + 1)));
+            });
             const int f = bad ? __builtin_ctzll(bad) : 64;  // >= 1: lane 0 passes
             if (tSt == lo) {
-                double mm = lane < f ? acc / (double)(cb + 1) : INFINITY;
-                for (int off = 32; off >= 1; off >>= 1) {
-                    const double o = __shfl_xor(mm, off);
-                    mm = o < mm ? o : mm;
-                }
+                typename Lanes::Value mean;
+                Lanes::each([&](int lane) {
+                    Lanes::of(mean, lane) = lane < f ? Lanes::of(acc, lane) / (double)(tC + lane + 1) : INFINITY;
+                });
+                const double mm = Lanes::smallest(mean);
                 if (mm < fmin_) fmin_ = mm;
             }
-            tS = lane_value(acc, f - 1);
+            tS = Lanes::value(acc, f - 1);
             tC += f;
             i += f;
             if (f < m) run = 0;
@@ -525,9 +483,19 @@ __device__ inline int pava_wave_range(const double *v, int lo, int hi, const int
     return nb;
 }
 
-// The same pass over the whole input v[0..L).
-__host__ __device__ inline void pava_sparse(const double *v, int L, const int *vio, int nv, double *S, int *SC,
-                                            int *npools) {
+__device__ inline int pava_wave_range(const double *v, int lo, int hi, const int *vio, int nv, double *S, int *SC,
+                                      double *fm, double *lm) {
+    return pava_range<PavaWaveLanes>(v, lo, hi, vio, nv, S, SC, fm, lm);
+}
+
+// The same on the host.
+inline int pava_sparse_range(const double *v, int lo, int hi, const int *vio, int nv, double *S, int *SC, double *fm,
+                             double *lm) {
+    return pava_range<PavaHostLanes>(v, lo, hi, vio, nv, S, SC, fm, lm);
+}
+
+// The same over the whole input v[0..L).
+inline void pava_sparse(const double *v, int L, const int *vio, int nv, double *S, int *SC, int *npools) {
     double fm, lm;
     *npools = pava_sparse_range(v, 0, L, vio, nv, S, SC, &fm, &lm);
 }
