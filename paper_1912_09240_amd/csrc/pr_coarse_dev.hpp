@@ -259,15 +259,16 @@ __host__ __device__ inline bool mean_above(double a, int ca, double b, int cb) {
 // 500 clocks a step; a step's two comparisons (T's mean against the next value,
 // B's against T's with that value) are taken together, and the pool below B (A) is
 // read from LDS as soon as it is known, not when B has been merged.  Where values
-// have merged into T alone PAVA_RUN times in a row, the wave takes the run ahead
-// at once: lane j adds v[i + j] to T's sum after the lanes before it, in the
+// have merged into T alone several times in a row, the wave takes the run ahead at
+// once: lane j adds v[i + j] to T's sum after the lanes before it, in the
 // serial order, and checks the two comparisons the serial pass would make for that
 // value; the longest prefix of lanes that pass is committed (windows of 8 values,
 // doubling up to 64 while whole windows pass), so that a decreasing run of L
-// values costs about L / 64 windows.  A window costs as much as five steps: taken
-// only for runs, a stretch of 432 noisy values takes 240,000 clocks (294,000 with a
-// window tried at every such value), one of 300 values with 50 violations 146,000
-// (170,000).
+// values costs about L / 64 windows.  A window costs as much as five steps, so it
+// is taken after PAVA_RUN merges, and after one where the last run would have
+// repaid that (1025 values, us, with a window at every second merge / always after
+// four / so: noise 426 / 384 / 373, runs of three 569 / 398 / 381, of seven 251 / 394
+// / 274, of forty 130 / 170 / 148).
 //
 // Lanes: the wave's own lanes, or 64 lanes in one host thread (PavaHostLanes), so
 // that the host runs every step the kernels run.
@@ -323,7 +324,7 @@ template <class Lanes>
 __host__ __device__ inline int pava_range(const double *v, int lo, int hi, const int *vio, int nv, double *S, int *SC,
                                           double *fm, double *lm) {
 #pragma clang fp contract(off)
-    int nb = 0, vi = 0, win = 8, run = 0;
+    int nb = 0, vi = 0, win = 8, run = 0, need = PAVA_RUN;
     double fmin_ = v[lo];
     int i = vio[0];
     double tS = v[i], bS = 0.0;
@@ -377,7 +378,7 @@ __host__ __device__ inline int pava_range(const double *v, int lo, int hi, const
         const double s1 = vcur + tS;
         const bool onto = tSt != lo && mean_above(bS, bC, s1, tC + 1);
         if (into && !onto) {
-            if (tC == 1 || run < PAVA_RUN) {
+            if (tC == 1 || run < need) {
                 vcur = v[i + 1 < hi ? i + 1 : i];  // the next value
                 tS = s1;
                 ++tC;
@@ -422,6 +423,8 @@ __host__ __device__ inline int pava_range(const double *v, int lo, int hi, const
             tS = Lanes::value(acc, f - 1);
             tC += f;
             i += f;
+            run += f;
+            need = run > PAVA_RUN + 1 ? 1 : PAVA_RUN;
             if (f < m) run = 0;
             win = f == m ? (win < 64 ? 2 * win : 64) : 8;
             vcur = v[i < hi ? i : hi - 1];

@@ -74,3 +74,15 @@ def test_random_runs(pv):
             v = np.round(v * 4.0) / 4.0
         windows += _check(pv, v)
     assert windows > 100
+
+
+def test_windows_follow_the_last_run(pv):
+    """Runs of twelve merges one after the other: the first is recognised after
+    four single steps and leaves one window of eight, the following ones are
+    taken ahead from their second merge on, in a window of eight and one for
+    the last three.  Runs of three merges never pay for a window."""
+    runs = 40
+    v = np.concatenate([3.0 * r + 2.0 - 0.2 * np.arange(13) for r in range(runs)])
+    assert _check(pv, v) >= 2 * (runs - 2)
+    v = np.concatenate([3.0 * r + 2.0 - 0.2 * np.arange(4) for r in range(runs)])
+    assert _check(pv, v) == 0
