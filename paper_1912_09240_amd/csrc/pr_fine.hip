@@ -29,17 +29,20 @@ __global__ void __launch_bounds__(256, (D >= 32 ? (sizeof(T) == 4 ? 4 : 3) : 1))
 #pragma unroll
     for (int i = 0; i < D; ++i) a[i] = a_dev ? (T)a_dev[i] : (T)1;
 
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    T x = xin[(int64_t)s * n + p], y[D];
+    // threads past the last particle step the first one: behind a return for
+    // them the compiler no longer overlaps two unrolled steps (d = 2, 5 x 10^4
+    // particles, 100 steps: 49 us, 56 with the return)
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, pc = p < n ? p : 0;
+    T x = xin[(int64_t)s * n + pc], y[D];
 #pragma unroll
-    for (int i = 0; i < D; ++i) y[i] = yin[((int64_t)s * D + i) * n + p];
+    for (int i = 0; i < D; ++i) y[i] = yin[((int64_t)s * D + i) * n + pc];
     // 32-bit step counter (the generator's counter word is 32 bits wide);
     // unrolled twice where the registers allow (a large fast part would spill)
     constexpr int UNROLL = D <= 4 ? 2 : 1;
     const uint32_t mb = (uint32_t)m0, steps = (uint32_t)(m1 - m0);
 #pragma unroll UNROLL
     for (uint32_t i = 0; i < steps; ++i) em_step<D, T>(x, y, a, c, tab, key, inst, mb + i, (uint32_t)p);
+    if (p >= n) return;
     xout[(int64_t)s * n + p] = x;
 #pragma unroll
     for (int i = 0; i < D; ++i) yout[((int64_t)s * D + i) * n + p] = y[i];
