@@ -105,12 +105,15 @@ __global__ void coupling_kernel(double *a, int d, Key key, uint32_t inst) {
 // particles find room on the chip at once (three per CU, 49152 particles), and
 // beyond one block per CU only for slices long enough to repay the blocks'
 // start (the tables are filled per 64 instead of per 256 particles).
-// Measured in us with / without, 100 steps: 10^4 particles 9.6 / 25, 40,000
+// Blocks of fewer than 64 particles (short ensembles in many slices) count as
+// full ones.  Measured in us with / without, 100 steps: 10^4 particles 9.6 / 25, 40,000
 // 20.7 / 25.1, 48,000 21.8 / 25.2, 60,000 25.9 / 25.5, 100,000 41.8 / 37.7;
 // 20 steps: 10^4 7.4 / 8.8, 20,000 8.8 / 8.7, 40,000 11.5 / 8.5; 40 steps:
-// 40,000 13.1 / 12.6; 1000 steps: 10^4 58 / 208.
-static bool normals_ahead(int64_t particles, int64_t steps) {
-    return particles <= 16384 || (particles <= 49152 && steps >= 48);
+// 40,000 13.1 / 12.6; 1000 steps: 10^4 58 / 208; one step: 10^4 11.8 / 11.0; 16384
+// slices of one particle, one step: 288 / 137.
+static bool normals_ahead(int64_t n, int64_t slices, int64_t steps) {
+    const int64_t particles = (n + 63) / 64 * 64 * slices;
+    return steps >= 4 && (particles <= 16384 || (particles <= 49152 && steps >= 48));
 }
 
 template <int D, typename T>
@@ -118,7 +121,7 @@ static int launch_fine(const pr_sde *sde, const pr_schedule *sch, uint64_t seed,
                        int64_t n, int slice_first, int slice_count, const void *xi, const void *yi, void *x,
                        void *y, hipStream_t st) {
     if constexpr (D == 1 && sizeof(T) == 8) {
-        if (normals_ahead(n * slice_count, sch->total_steps / sch->n_slices)) {
+        if (normals_ahead(n, slice_count, sch->total_steps / sch->n_slices)) {
             const dim3 grid((unsigned)((n + 63) / 64), (unsigned)slice_count);
             hipLaunchKernelGGL(fine_split_kernel, grid, dim3(SPLIT_THREADS), 0, st, (const double *)xi,
                                (const double *)yi, (double *)x, (double *)y, n, slice_first, sch->total_steps,
