@@ -52,27 +52,32 @@ __device__ __forceinline__ void em_step_d1(double &x, double &y, const EmCoef<do
 }
 
 // Forward over all steps [0, S) with checkpoints, one particle per thread
-// (as the fine propagator).
+// (as the fine propagator).  MANY: groups of 256 particles per block, one after
+// the other.
+template <bool MANY>
 __global__ void __launch_bounds__(256) fwd_ckpt_kernel(double *__restrict__ x, double *__restrict__ y, int64_t n,
                                                        int64_t S, int every, double *__restrict__ ckpt,
-                                                       EmCoef<double> ec, Key key, uint32_t inst) {
+                                                       EmCoef<double> ec, Key key, uint32_t inst, int groups) {
     __shared__ NoiseTab tab;
     load_noise_tab(tab);
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    double xv = x[p], yv = y[p];
-    int64_t cidx = 0;
-    for (int64_t m0 = 0; m0 < S; m0 += every, ++cidx) {
-        ckpt[(cidx * 2) * n + p] = xv;
-        ckpt[(cidx * 2 + 1) * n + p] = yv;
-        const int64_t m1 = m0 + every < S ? m0 + every : S;
-        // 32-bit step counter (the generator's counter word is 32 bits wide)
-        const uint32_t mb = (uint32_t)m0, steps = (uint32_t)(m1 - m0);
+#pragma unroll 1
+    for (int g = 0; g < (MANY ? groups : 1); ++g) {
+        const int64_t p = ((int64_t)blockIdx.x * (MANY ? groups : 1) + g) * blockDim.x + threadIdx.x;
+        if (p >= n) return;
+        double xv = x[p], yv = y[p];
+        int64_t cidx = 0;
+        for (int64_t m0 = 0; m0 < S; m0 += every, ++cidx) {
+            ckpt[(cidx * 2) * n + p] = xv;
+            ckpt[(cidx * 2 + 1) * n + p] = yv;
+            const int64_t m1 = m0 + every < S ? m0 + every : S;
+            // 32-bit step counter (the generator's counter word is 32 bits wide)
+            const uint32_t mb = (uint32_t)m0, steps = (uint32_t)(m1 - m0);
 #pragma unroll 2
-        for (uint32_t i = 0; i < steps; ++i) em_step_d1(xv, yv, ec, tab, key, inst, mb + i, (uint32_t)p);
+            for (uint32_t i = 0; i < steps; ++i) em_step_d1(xv, yv, ec, tab, key, inst, mb + i, (uint32_t)p);
+        }
+        x[p] = xv;
+        y[p] = yv;
     }
-    x[p] = xv;
-    y[p] = yv;
 }
 
 // One sub-segment of the reverse sweep: the L <= AD_SUB steps from ms are
@@ -362,10 +367,11 @@ extern "C" int pr_fine_checkpoint(const pr_sde *sde, const pr_schedule *sched, u
     PR_REQUIRE(n >= 1 && n <= 0xFFFFFFFFll, "n must be in [1, 2^32)");
     PR_REQUIRE(ckpt_every >= 1 && ckpt_every <= 1 << 20, "ckpt_every must be in [1, 2^20]");
     PR_REQUIRE(x && y && ckpt, "x, y and ckpt must be non-NULL");
-    hipLaunchKernelGGL(fwd_ckpt_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       as_stream(stream),
-                       (double *)x, (double *)y, n, sched->total_steps, ckpt_every, ckpt,
-                       make_coef<double>(sde, sched->dt), make_key(seed), instance);
+    const int64_t groups = groups_per_block((n + 255) / 256, 1, sched->total_steps);
+    auto kernel = groups > 1 ? fwd_ckpt_kernel<true> : fwd_ckpt_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(((n + 255) / 256 + groups - 1) / groups)), dim3(256), 0,
+                       as_stream(stream), (double *)x, (double *)y, n, sched->total_steps, ckpt_every, ckpt,
+                       make_coef<double>(sde, sched->dt), make_key(seed), instance, (int)groups);
     PR_LAUNCHED();
     return PR_OK;
 }

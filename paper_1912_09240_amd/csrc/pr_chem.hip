@@ -69,24 +69,29 @@ __device__ __forceinline__ void chem_step(double &x, double &y, const ChemCoef &
 // per thread gain nothing where the chip is full and lose where it is not
 // (20 slices of 100,000 particles x 2000 steps: 12.8 -> 12.4 ms; 8 slices of
 // 10,000 x 500 steps, with the states around it: 358 -> 328 us).
+// MANY: groups of 256 particles per block, one after the other.
+template <bool MANY>
 __global__ void __launch_bounds__(256) chem_fine_kernel(const double *xin, const double *yin, double *xout,
                                                         double *yout, int64_t n, int slice_first, int64_t S, int N,
-                                                        ChemCoef c, Key key, uint32_t inst) {
+                                                        ChemCoef c, Key key, uint32_t inst, int groups) {
     __shared__ NoiseTab tab;
     load_noise_tab(tab);
     const int s = blockIdx.y;
     const int sl = slice_first + s;
     const int64_t m0 = uniform_i64(slice_begin(S, N, sl));
     const int64_t m1 = uniform_i64(slice_begin(S, N, sl + 1));
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    double xv = xin[(int64_t)s * n + p], yv = yin[(int64_t)s * n + p];
     // 32-bit step counter (the generator's counter word is 32 bits wide)
     const uint32_t mb = (uint32_t)m0, steps = (uint32_t)(m1 - m0);
+#pragma unroll 1
+    for (int g = 0; g < (MANY ? groups : 1); ++g) {
+        const int64_t p = ((int64_t)blockIdx.x * (MANY ? groups : 1) + g) * blockDim.x + threadIdx.x;
+        if (p >= n) return;
+        double xv = xin[(int64_t)s * n + p], yv = yin[(int64_t)s * n + p];
 #pragma unroll 2
-    for (uint32_t i = 0; i < steps; ++i) chem_step(xv, yv, c, tab, key, inst, mb + i, (uint32_t)p);
-    xout[(int64_t)s * n + p] = xv;
-    yout[(int64_t)s * n + p] = yv;
+        for (uint32_t i = 0; i < steps; ++i) chem_step(xv, yv, c, tab, key, inst, mb + i, (uint32_t)p);
+        xout[(int64_t)s * n + p] = xv;
+        yout[(int64_t)s * n + p] = yv;
+    }
 }
 
 __global__ void __launch_bounds__(256) chem_init_kernel(double *__restrict__ x, double *__restrict__ y, int64_t n,
@@ -128,9 +133,11 @@ int chem_fine_propagate(const pr_chem *c, const pr_schedule *sch, uint64_t seed,
                         int slice_first, int slice_count, const double *xi, const double *yi, double *x, double *y,
                         hipStream_t st) {
     if (slice_count == 0 || n == 0) return PR_OK;
-    const dim3 grid((unsigned)((n + 255) / 256), (unsigned)slice_count);
-    hipLaunchKernelGGL(chem_fine_kernel, grid, dim3(256), 0, st, xi, yi, x, y, n, slice_first, sch->total_steps,
-                       sch->n_slices, make_chem_coef(c, sch->dt), make_key(seed), inst);
+    const int64_t groups = groups_per_block((n + 255) / 256, slice_count, sch->total_steps / sch->n_slices);
+    const dim3 grid((unsigned)(((n + 255) / 256 + groups - 1) / groups), (unsigned)slice_count);
+    auto kernel = groups > 1 ? chem_fine_kernel<true> : chem_fine_kernel<false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, xi, yi, x, y, n, slice_first, sch->total_steps, sch->n_slices,
+                       make_chem_coef(c, sch->dt), make_key(seed), inst, (int)groups);
     PR_LAUNCHED();
     return PR_OK;
 }

@@ -12,11 +12,11 @@ namespace pr {
 // (one wave per SIMD); asking for 3 blocks per CU makes the compiler fit it
 // in 168 with a few spilled values, which runs 1.5x faster (FP32: 4 blocks,
 // 128 VGPRs, 2 % faster than its own 142).
-template <int D, typename T>
-__global__ void __launch_bounds__(256, (D >= 32 ? (sizeof(T) == 4 ? 4 : 3) : 1)) fine_kernel(const T *xin, const T *yin, T *xout, T *yout, int64_t n,
-                                                   int slice_first, int64_t S, int N,
-                                                   EmCoef<T> c, const double *__restrict__ a_dev,
-                                                   Key key, uint32_t inst) {
+// MANY: groups of 256 particles per block, one after the other.
+template <int D, typename T, bool MANY>
+__global__ void __launch_bounds__(256, (D >= 32 ? (sizeof(T) == 4 ? 4 : 3) : 1))
+fine_kernel(const T *xin, const T *yin, T *xout, T *yout, int64_t n, int slice_first, int64_t S, int N, EmCoef<T> c,
+            const double *__restrict__ a_dev, Key key, uint32_t inst, int groups) {
     __shared__ typename TabOf<T>::type tab;
     load_noise_tab(tab);
     const int s = blockIdx.y;
@@ -29,23 +29,26 @@ __global__ void __launch_bounds__(256, (D >= 32 ? (sizeof(T) == 4 ? 4 : 3) : 1))
 #pragma unroll
     for (int i = 0; i < D; ++i) a[i] = a_dev ? (T)a_dev[i] : (T)1;
 
-    // threads past the last particle step the first one: behind a return for
-    // them the compiler no longer overlaps two unrolled steps (d = 2, 5 x 10^4
-    // particles, 100 steps: 49 us, 56 with the return)
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, pc = p < n ? p : 0;
-    T x = xin[(int64_t)s * n + pc], y[D];
-#pragma unroll
-    for (int i = 0; i < D; ++i) y[i] = yin[((int64_t)s * D + i) * n + pc];
     // 32-bit step counter (the generator's counter word is 32 bits wide);
     // unrolled twice where the registers allow (a large fast part would spill)
     constexpr int UNROLL = D <= 4 ? 2 : 1;
     const uint32_t mb = (uint32_t)m0, steps = (uint32_t)(m1 - m0);
-#pragma unroll UNROLL
-    for (uint32_t i = 0; i < steps; ++i) em_step<D, T>(x, y, a, c, tab, key, inst, mb + i, (uint32_t)p);
-    if (p >= n) return;
-    xout[(int64_t)s * n + p] = x;
+#pragma unroll 1
+    for (int g = 0; g < (MANY ? groups : 1); ++g) {
+        // threads past the last particle step the first one: behind a return for
+        // them the compiler no longer overlaps two unrolled steps (d = 2, 5 x
+        // 10^4 particles, 100 steps: 49 us, 56 with the return)
+        const int64_t p = ((int64_t)blockIdx.x * (MANY ? groups : 1) + g) * blockDim.x + threadIdx.x, pc = p < n ? p : 0;
+        T x = xin[(int64_t)s * n + pc], y[D];
 #pragma unroll
-    for (int i = 0; i < D; ++i) yout[((int64_t)s * D + i) * n + p] = y[i];
+        for (int i = 0; i < D; ++i) y[i] = yin[((int64_t)s * D + i) * n + pc];
+#pragma unroll UNROLL
+        for (uint32_t i = 0; i < steps; ++i) em_step<D, T>(x, y, a, c, tab, key, inst, mb + i, (uint32_t)p);
+        if (p >= n) return;
+        xout[(int64_t)s * n + p] = x;
+#pragma unroll
+        for (int i = 0; i < D; ++i) yout[((int64_t)s * D + i) * n + p] = y[i];
+    }
 }
 
 // Few particles (d = 1, FP64): 64 per block, their normals generated ahead by
@@ -133,11 +136,19 @@ static int launch_fine(const pr_sde *sde, const pr_schedule *sch, uint64_t seed,
     // One particle per thread: two take the same time where the chip is full
     // (64 x 2^20 particles: 221.8 ms both) and up to 1.8 times as long where it
     // is not (40,000 particles: 45 us, one 25 us; 100,000: 45.5 and 37.7).
-    dim3 grid((unsigned)((n + 255) / 256), (unsigned)slice_count);
-    hipLaunchKernelGGL((fine_kernel<D, T>), grid, dim3(256), 0, st, (const T *)xi, (const T *)yi, (T *)x,
-                       (T *)y, n, slice_first,
-                       sch->total_steps, sch->n_slices, make_coef<T>(sde, sch->dt), sde->a,
-                       make_key(seed), inst);
+    const int64_t groups = D == 1 ? groups_per_block((n + 255) / 256, slice_count, sch->total_steps / sch->n_slices) : 1;
+    dim3 grid((unsigned)(((n + 255) / 256 + groups - 1) / groups), (unsigned)slice_count);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, (const T *)xi, (const T *)yi, (T *)x, (T *)y, n,
+                           slice_first, sch->total_steps, sch->n_slices, make_coef<T>(sde, sch->dt), sde->a,
+                           make_key(seed), inst, (int)groups);
+    };
+    if constexpr (D == 1) {
+        if (groups > 1) launch(fine_kernel<D, T, true>);
+        else launch(fine_kernel<D, T, false>);
+    } else {
+        launch(fine_kernel<D, T, false>);
+    }
     PR_LAUNCHED();
     return PR_OK;
 }

@@ -2,6 +2,7 @@
 // device-side counter-based noise (Philox4x32-10 + Box-Muller).
 #pragma once
 
+#include <algorithm>
 #include <hip/hip_runtime.h>
 
 #include <cstdarg>
@@ -146,6 +147,21 @@ __device__ __forceinline__ void box_muller(const Block &b, const NoiseTab &tab, 
 
 __device__ __forceinline__ void box_muller(const Block &b, const NoiseTabF &tab, float &z0, float &z1) {
     normal_pair_of_words_f32(b.w0, b.w2, tab, z0, z1);
+}
+
+// Groups of 256 particles that a block of a kernel with one particle per thread
+// takes one after the other (blocks: of one group each, per slice).  A block's start (the tables filled, the first
+// loads) weighs more than a few steps: slices shorter than 16 steps, where one group
+// per block makes more blocks than the chip holds at once (eight per CU; four, where
+// the start is most of the time), take as many groups as bring the blocks down to
+// that, at most eight.  FP64, us with one / several: 8 x 2^20 particles, one step 136 /
+// 55, ten 301 / 258; 3 x 2^18, one step 21.9 / 17.2, ten 36.6 / 36.7.
+inline int64_t groups_per_block(int64_t blocks, int64_t slices, int64_t steps) {
+    const int64_t at_once = (steps < 8 ? 4 : 8) * 256;
+    if (steps >= 16 || blocks * slices <= at_once) return 1;
+    const int64_t groups = std::min<int64_t>(8, (blocks * slices + at_once - 1) / at_once);
+    const int64_t left = (blocks + groups - 1) / groups;  // blocks per slice, evenly loaded
+    return (blocks + left - 1) / left;
 }
 
 // Orderable 64-bit key of a double: unsigned order == numeric order,
