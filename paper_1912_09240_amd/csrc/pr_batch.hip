@@ -511,12 +511,12 @@ static int autotune(Batch *b, hipStream_t st) {
 static int restrict_fine(Batch *b, int nx, hipStream_t st) {
     if (!b->split_sort && b->tuned_sizes) {
         const SortLayout L{0, 0, (int)b->seg_f_h.size(), b->seg_f, b->tile_f, nullptr, b->seg_max_n, true};
-        return restrict_segments(b->x[nx], PR_F64, L, b->total_x, b->tiles_f, b->Q, b->qf, b->rank, b->ws, st);
+        return restrict_segments(b->x[nx], L, b->total_x, b->tiles_f, b->Q, b->qf, b->rank, b->ws, st);
     }
     for (const Batch::Part &P : b->part) {
         if (P.nseg == 0) continue;
         const SortLayout LP{0, 0, P.nseg, P.seg, P.tile, nullptr, P.max_n};
-        PR_CHECK(restrict_segments(b->x[nx], PR_F64, LP, b->total_x, P.tiles, b->Q, b->qf, b->rank, b->ws, st));
+        PR_CHECK(restrict_segments(b->x[nx], LP, b->total_x, P.tiles, b->Q, b->qf, b->rank, b->ws, st));
     }
     return PR_OK;
 }
@@ -587,7 +587,7 @@ static int sort_new_if_flagged(Batch *b, int nx, hipStream_t st) {
     PR_HIP(hipMemcpyAsync(b->seg_sub, b->seg_sub_h, sizeof(SortSeg) * nsub, hipMemcpyHostToDevice, st));
     PR_HIP(hipMemcpyAsync(b->tile_sub, b->tile_sub_h, sizeof(int) * tiles, hipMemcpyHostToDevice, st));
     SortLayout L{0, 0, nsub, b->seg_sub, b->tile_sub, nullptr, max_n};
-    PR_CHECK(restrict_segments(b->x[nx], PR_F64, L, b->total_x, tiles, b->Q, b->qR, nullptr, b->ws, st));
+    PR_CHECK(restrict_segments(b->x[nx], L, b->total_x, tiles, b->Q, b->qR, nullptr, b->ws, st));
     b->knot_sorts += 1;
     b->knot_sort_segs += nsub;
     return PR_OK;
@@ -626,7 +626,7 @@ static int iterate_once(Batch *b, int mode, hipStream_t st) {
         if (mk != PR_OK && mk != PR_E_UNSUPPORTED) return mk;
         b->mk_ok = mk == PR_OK;
         if (!b->mk_ok)
-            PR_CHECK(restrict_segments(b->x[nx], PR_F64, L, b->total_x, b->tiles_f, Q, b->qR, nullptr, b->ws, st));
+            PR_CHECK(restrict_segments(b->x[nx], L, b->total_x, b->tiles_f, Q, b->qR, nullptr, b->ws, st));
         hipLaunchKernelGGL(copy_f64, dim3(64), dim3(256), 0, st, (const double *)b->qn, b->q,
                            (int64_t)b->total_rows * (Q + 1));
         PR_LAUNCHED();

@@ -280,8 +280,8 @@ int64_t sort_tiles(int64_t n);
 bool splitter_sorts(int64_t n);
 bool splitter_tuned(int64_t n);
 size_t sort_ws_bytes(int64_t total_keys, int64_t total_tiles, int nseg, int precision, bool payload);
-int restrict_segments(const void *x, int precision, const SortLayout &L, int64_t total_keys, int64_t total_tiles,
-                      int nq, double *q, uint32_t *rank, void *ws, hipStream_t st);
+int restrict_segments(const double *x, const SortLayout &L, int64_t total_keys, int64_t total_tiles, int nq,
+                      double *q, uint32_t *rank, void *ws, hipStream_t st);
 // restrict_quantiles of k equal segments for knots only, every kernel
 // returning at once while *guard reads 0 (a sort that runs only where the
 // device decides it is needed, launched unconditionally).

@@ -24,9 +24,10 @@
 // sort that only needs knots carries no payload.  64-bit keys run only the
 // four passes over their high halves, then a fix-up pass (rs_fixup) that
 // orders every run of equal high halves and writes the last pass's outputs
-// (the ranks through a staging buffer instead of stores to random addresses,
-// rs_rank_bucket and rs_rank_place); the complete sort follows, guarded by a
-// flag that the fix-up raises only for a run longer than it handles.
+// (the ranks of a segment table through a staging buffer instead of stores to
+// random addresses, rs_rank_bucket and rs_rank_place); the complete sort
+// follows, guarded by a flag that the fix-up raises only for a run longer than
+// it handles.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -480,7 +481,7 @@ constexpr int SS_BT = 1024;                 // threads of a bucket block
 constexpr int SS_IT = 7;                    // keys per thread of a bucket block
 constexpr int SS_CAP = SS_BT * SS_IT;       // 7168: two bucket blocks share a CU's LDS
 constexpr int SS_IT_BIG = 14;
-constexpr int SS_BIG = SS_BT * SS_IT_BIG;   // 14336: one block takes 148 KiB of it
+constexpr int SS_BIG = SS_BT * SS_IT_BIG;   // 14336: one block takes 156 KiB of it
 // Keys of a value sub-bucket above which the bucket goes by digits: the
 // counting's time grows with them and with the keys per thread, that of the
 // digits only with the latter.  FP32, 8 ensembles of 2^20 of 20,000 values (52 keys
@@ -1087,6 +1088,13 @@ struct BucketLds {
         else return spos;
     }
 };
+// two bucket blocks per CU, and the largest alone (with ss_left's list) in one
+constexpr size_t CU_LDS = 160 << 10;
+static_assert(2 * sizeof(BucketLds<uint64_t, SS_IT>) <= CU_LDS && 2 * sizeof(BucketLds<uint32_t, SS_IT>) <= CU_LDS,
+              "two blocks of SS_CAP keys share a CU");
+static_assert(sizeof(BucketLds<uint64_t, SS_IT_BIG>) + 2 * SS_BT + 64 <= CU_LDS &&
+                  sizeof(BucketLds<uint32_t, SS_IT_BIG>) + 2 * SS_BT + 64 <= CU_LDS,
+              "a block of SS_BIG keys and its list of tiles fit a CU");
 
 // The slots in S.slots(cur) into the order of their words, by the bytes in
 // which the words differ at all (diff), least significant first: every wave ranks
@@ -1814,15 +1822,15 @@ rs_fixup(const uint64_t *__restrict__ keys_in, const uint32_t *__restrict__ vals
 //   rs_rank_place   every block of TILE particles takes its region, places
 //                   the ranks in LDS and writes them out in particle order.
 // A pair packs the position (below 2^20) and the particle's offset in its
-// block (below 2^12) into 32 bits, so segments of up to 2^20 keys take this
-// path.  Both kernels return at once where the fix-up raised its flag (the
-// complete sort then writes the ranks).
+// block (below 2^12) into 32 bits, so segment tables of up to 2^20 keys per
+// segment take this path (ensembles of equal lengths come to the radix passes
+// only with more).  Both kernels return at once where the fix-up raised its
+// flag (the complete sort then writes the ranks).
 // ---------------------------------------------------------------------------
 constexpr int64_t RK_MAX_N = (int64_t)1 << 20;
 static_assert((1 << RK_SHIFT) == RS_THREADS * RS_ITEMS, "a block of particles is one tile");
 static_assert(RS_THREADS == RS_RADIX, "one thread per particle block of a segment");
 
-template <bool VAR>
 __global__ void __launch_bounds__(RS_THREADS)
 rs_rank_bucket(const uint32_t *__restrict__ perm, SortLayout L, uint32_t *__restrict__ cursor,
                uint32_t *__restrict__ staged, const int *__restrict__ flag) {
@@ -1831,7 +1839,7 @@ rs_rank_bucket(const uint32_t *__restrict__ perm, SortLayout L, uint32_t *__rest
     __shared__ uint32_t stage[TILE];
     __shared__ uint8_t sblk[TILE];
     if ((L.guard && *L.guard == 0) || *flag != 0) return;
-    const TileRef T = tile_ref<VAR>(L, xcd_tile(blockIdx.x, gridDim.x));
+    const TileRef T = tile_ref<true>(L, xcd_tile(blockIdx.x, gridDim.x));
     const int tid = threadIdx.x;
     cnt[tid] = 0;
     __syncthreads();
@@ -1871,14 +1879,13 @@ rs_rank_bucket(const uint32_t *__restrict__ perm, SortLayout L, uint32_t *__rest
     }
 }
 
-template <bool VAR>
 __global__ void __launch_bounds__(RS_THREADS)
 rs_rank_place(const uint32_t *__restrict__ staged, SortLayout L, uint32_t *__restrict__ rank_out,
               const int *__restrict__ flag) {
     constexpr int TILE = RS_THREADS * RS_ITEMS;
     __shared__ uint32_t r[TILE];
     if ((L.guard && *L.guard == 0) || *flag != 0) return;
-    const TileRef T = tile_ref<VAR>(L, xcd_tile(blockIdx.x, gridDim.x));
+    const TileRef T = tile_ref<true>(L, xcd_tile(blockIdx.x, gridDim.x));
     const int64_t b0 = (int64_t)T.blk * TILE;
     const int bn = (int)(T.n - b0 < TILE ? T.n - b0 : TILE);
     uint32_t e[RS_ITEMS];
@@ -2326,24 +2333,7 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
     K *runq = (K *)(bstart + (size_t)L.nseg * SS_B);                    // thinned runs, [nseg][SS_MAX_RUNS SS_KEEP]
     const dim3 grid((unsigned)total_tiles);
     const dim3 rows((unsigned)(((int64_t)L.nseg * RS_RADIX + 3) / 4));
-    // outputs of the last pass (the ranks move to the staging kernels below
-    // where they take over)
-    uint32_t *rank_last = rank, *perm_last = perm;
     const int64_t max_n = VAR ? L.max_n : L.n;
-    const bool staged_ranks = rank != nullptr && max_n > 0 && max_n <= RK_MAX_N;
-    // ranks from the permutation in order, through the staging buffer
-    auto stage_ranks = [&](const uint32_t *perm_in, uint32_t *staging) -> int {
-        const int64_t zb = (total_tiles + 255) / 256 < 1024 ? (total_tiles + 255) / 256 : 1024;
-        hipLaunchKernelGGL(zero_u32, dim3((unsigned)zb), dim3(256), 0, st, counts, total_tiles);
-        PR_LAUNCHED();
-        hipLaunchKernelGGL((rs_rank_bucket<VAR>), grid, dim3(RS_THREADS), 0, st, perm_in, L, counts, staging,
-                           (const int *)flag);
-        PR_LAUNCHED();
-        hipLaunchKernelGGL((rs_rank_place<VAR>), grid, dim3(RS_THREADS), 0, st, (const uint32_t *)staging, L, rank,
-                           (const int *)flag);
-        PR_LAUNCHED();
-        return PR_OK;
-    };
     // One LSD pass over the byte at shift: keys[in] -> keys[out] (pass 0
     // reads the values), with the statistics on the first read and the rank,
     // perm and sorted-value outputs on the last pass.
@@ -2365,7 +2355,7 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
 #define PR_SCATTER(FIRST, LAST, PAY, SRC, VIN, VOUT)                                                            \
     hipLaunchKernelGGL((rs_scatter<K, ITEMS, FIRST, LAST, PAY, VAR>), grid, dim3(RS_THREADS), 0, st, SRC, VIN,     \
                        keys[out], VOUT, (const uint32_t *)counts, (const uint32_t *)totals, shift, LL,         \
-                       LAST ? rank_last : nullptr, LAST ? perm_last : nullptr, LAST ? xs : nullptr)
+                       LAST ? rank : nullptr, LAST ? perm : nullptr, LAST ? xs : nullptr)
         if (payload) {
             if (first) PR_SCATTER(true, false, true, x, nullptr, vals[out]);
             else if (!last) PR_SCATTER(false, false, true, (const void *)keys[in], vals[in], vals[out]);
@@ -2416,9 +2406,10 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
                               payload ? (rank ? rank : vals[0]) : nullptr, xs, q, (uint32_t *)runq, nq};
         const bool big = !VAR && !many && max_n > SS_CAP;  // ensembles of one bucket above SS_CAP
         const bool here = sizeof(K) == 4 || big || (!many && L.nseg <= SS_WHOLE);
-        if (big)
-            hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT_BIG, true>), grid, dim3(SS_BT), 0, st, A, L);
-        else if (here)
+        if (big) {
+            if constexpr (!VAR)
+                hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT_BIG, true>), grid, dim3(SS_BT), 0, st, A, L);
+        } else if (here)
             hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT, true>), grid, dim3(SS_BT), 0, st, A, L);
         else
             hipLaunchKernelGGL((ss_bucket_sort<K, VAR, SS_IT, sizeof(K) == 4>), grid, dim3(SS_BT), 0, st, A, L);
@@ -2443,11 +2434,12 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
         for (int j = 0; j < 4; ++j) PR_CHECK(pass(L, 32 + 8 * j, j == 0, false, (j + 1) & 1, j & 1, true));
         hipLaunchKernelGGL(zero_u32, dim3(1), dim3(64), 0, st, (uint32_t *)flag, (int64_t)1);
         PR_LAUNCHED();
-        // ranks through the staging buffer (vals[1], free once the fix-up
-        // has read it) where every segment fits the packing, the fix-up
-        // then writing the permutation in order (into vals[0] unless asked
-        // for) instead of the ranks; the complete sort behind it keeps
-        // storing the ranks itself
+        // a segment table's ranks through the staging buffer (vals[1], free
+        // once the fix-up has read it) where every segment fits the packing,
+        // the fix-up then writing the permutation in order (into vals[0]
+        // unless asked for) instead of the ranks; the complete sort behind it
+        // keeps storing the ranks itself
+        const bool staged_ranks = VAR && rank != nullptr && max_n > 0 && max_n <= RK_MAX_N;
         uint32_t *perm_fix = perm ? perm : (staged_ranks ? vals[0] : nullptr);
         if (payload)
             hipLaunchKernelGGL((rs_fixup<VAR, true>), grid, dim3(RS_THREADS), 0, st, (const uint64_t *)keys[1],
@@ -2457,23 +2449,24 @@ static int sort_impl(const void *x, const SortLayout &L, int64_t total_keys, int
             hipLaunchKernelGGL((rs_fixup<VAR, false>), grid, dim3(RS_THREADS), 0, st, (const uint64_t *)keys[1],
                                (const uint32_t *)nullptr, (uint64_t *)keys[0], L, rank, perm, xs, flag);
         PR_LAUNCHED();
-        if (staged_ranks) PR_CHECK(stage_ranks(perm_fix, vals[1]));
+        if constexpr (VAR) {
+            if (staged_ranks) {
+                const int64_t zb = (total_tiles + 255) / 256 < 1024 ? (total_tiles + 255) / 256 : 1024;
+                hipLaunchKernelGGL(zero_u32, dim3((unsigned)zb), dim3(256), 0, st, counts, total_tiles);
+                PR_LAUNCHED();
+                hipLaunchKernelGGL(rs_rank_bucket, grid, dim3(RS_THREADS), 0, st, (const uint32_t *)perm_fix, L, counts,
+                                   vals[1], (const int *)flag);
+                PR_LAUNCHED();
+                hipLaunchKernelGGL(rs_rank_place, grid, dim3(RS_THREADS), 0, st, (const uint32_t *)vals[1], L, rank,
+                                   (const int *)flag);
+                PR_LAUNCHED();
+            }
+        }
         SortLayout LG = L;
         LG.guard = flag;
         for (int j = 0; j < P; ++j) PR_CHECK(pass(LG, 8 * j, j == 0, j == P - 1, j & 1, (j + 1) & 1, false));
     } else {
-        // the last pass reads vals[0] and writes the permutation into vals[1]
-        // (unless asked for); vals[0] then stages the ranks
-        if (staged_ranks) {
-            rank_last = nullptr;
-            perm_last = perm ? perm : vals[1];
-        }
         for (int j = 0; j < P; ++j) PR_CHECK(pass(L, 8 * j, j == 0, j == P - 1, (j + 1) & 1, j & 1, true));
-        if (staged_ranks) {
-            hipLaunchKernelGGL(zero_u32, dim3(1), dim3(64), 0, st, (uint32_t *)flag, (int64_t)1);
-            PR_LAUNCHED();
-            PR_CHECK(stage_ranks(perm_last, vals[0]));
-        }
     }
     if (splitter) return PR_OK;
     hipLaunchKernelGGL((rs_knots<K, VAR>), dim3(L.nseg), dim3(128), 0, st, (const K *)keys[sorted_buffer<K>()], L, nq,
@@ -2507,12 +2500,9 @@ int restrict_knots_guarded(const void *x, int precision, int64_t n, int k, int n
                                       nullptr, ws, st);
 }
 
-int restrict_segments(const void *x, int precision, const SortLayout &L, int64_t total_keys, int64_t total_tiles,
-                      int nq, double *q, uint32_t *rank, void *ws, hipStream_t st) {
-    if (precision == PR_F64)
-        return sort_impl<uint64_t, true>(x, L, total_keys, total_tiles, nq, nullptr, q, rank, nullptr, nullptr,
-                                         nullptr, nullptr, ws, st);
-    return sort_impl<uint32_t, true>(x, L, total_keys, total_tiles, nq, nullptr, q, rank, nullptr, nullptr, nullptr,
+int restrict_segments(const double *x, const SortLayout &L, int64_t total_keys, int64_t total_tiles, int nq,
+                      double *q, uint32_t *rank, void *ws, hipStream_t st) {
+    return sort_impl<uint64_t, true>(x, L, total_keys, total_tiles, nq, nullptr, q, rank, nullptr, nullptr, nullptr,
                                      nullptr, ws, st);
 }
 
