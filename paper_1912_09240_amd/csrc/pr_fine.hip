@@ -35,10 +35,12 @@ fine_kernel(const T *xin, const T *yin, T *xout, T *yout, int64_t n, int slice_f
     const uint32_t mb = (uint32_t)m0, steps = (uint32_t)(m1 - m0);
 #pragma unroll 1
     for (int g = 0; g < (MANY ? groups : 1); ++g) {
-        // threads past the last particle step the first one: behind a return for
-        // them the compiler no longer overlaps two unrolled steps (d = 2, 5 x
-        // 10^4 particles, 100 steps: 49 us, 56 with the return)
+        // waves past the last particle end here; single threads past it step the
+        // first one: behind a return for them the compiler no longer overlaps two
+        // unrolled steps (d = 2, 5 x 10^4 particles, 100 steps: 49 us, 56 with
+        // such a return)
         const int64_t p = ((int64_t)blockIdx.x * (MANY ? groups : 1) + g) * blockDim.x + threadIdx.x, pc = p < n ? p : 0;
+        if (uniform_i64(p - (int64_t)(threadIdx.x & 63)) >= n) return;
         T x = xin[(int64_t)s * n + pc], y[D];
 #pragma unroll
         for (int i = 0; i < D; ++i) y[i] = yin[((int64_t)s * D + i) * n + pc];

@@ -118,3 +118,31 @@ def test_groups_of_the_chemical_and_checkpointed_steps(n, steps):
     torch.cuda.synchronize()
     assert torch.equal(x[:m], xs) and torch.equal(y[:m], ys) and torch.equal(ck[:, :, :m], cks)
     assert not torch.isnan(x).any() and (ck[:, :, -1] != 0).all()
+
+
+@pytest.mark.parametrize("prec", [pr.PR_F64, pr.PR_F32])
+def test_time_of_waves_without_particles(prec):
+    """Slices of fewer particles than a block has threads: a wave without a
+    particle takes no steps (5000 slices of 64 particles, d = 32: one wave of
+    each block's four; with all four stepping, the time of 256 particles)."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"fine waves without particles precision={prec}", flush=True)
+    k, d, dt = 5000, 32, torch.float64 if prec == pr.PR_F64 else torch.float32
+    sde, sched = pr.Sde(eps=0.05, precision=prec, d=d), pr.Schedule(4 * k, k, 1e-3)
+    us = {}
+    for n in (64, 256):
+        x = torch.zeros((k, n), device="cuda", dtype=dt)
+        y = torch.zeros((k, d, n), device="cuda", dtype=dt)
+        best = float("inf")
+        for _ in range(10):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            pr.pr_fine_propagate(sde, sched, 3, 1, n, 0, k, x, y)
+            e1.record()
+            e1.synchronize()
+            best = min(best, 1e3 * e0.elapsed_time(e1))
+        us[n] = best
+    print(us, flush=True)
+    assert us[64] < 0.7 * us[256], us
