@@ -1726,6 +1726,7 @@ ss_finish(const K *__restrict__ sorted, int nq, double *__restrict__ q, const do
 // ---------------------------------------------------------------------------
 constexpr int FIX_MAX = 64;
 constexpr int FIX_HALO = FIX_MAX + 1;
+constexpr int FIX_NEAR = 4;
 
 template <bool VAR, bool PAYLOAD>
 __global__ void __launch_bounds__(RS_THREADS)
@@ -1767,10 +1768,20 @@ rs_fixup(const uint64_t *__restrict__ keys_in, const uint32_t *__restrict__ vals
             const int j = (int)(p - t0) + FIX_HALO;  // p in sk
             const uint64_t kp = sk[j];
             const uint32_t hp = (uint32_t)(kp >> 32);
-            // the run [p - back, p + fwd] of equal high halves, at most FIX_MAX long
+            // the run [p - back, p + fwd] of equal high halves, up to FIX_MAX keys on
+            // either side: the first few key by key, the rest in halving steps (the
+            // high halves are in order; all of a long run key by key took more
+            // than a quarter of the whole sort)
+            const int bmax = (int)min((int64_t)FIX_MAX, p), fmax = (int)min((int64_t)FIX_MAX, n - 1 - p);
             int back = 0, fwd = 0;
-            while (back < FIX_MAX && p - back > 0 && (uint32_t)(sk[j - back - 1] >> 32) == hp) ++back;
-            while (fwd < FIX_MAX && p + fwd + 1 < n && (uint32_t)(sk[j + fwd + 1] >> 32) == hp) ++fwd;
+            while (back < FIX_NEAR && back < bmax && (uint32_t)(sk[j - back - 1] >> 32) == hp) ++back;
+            if (back == FIX_NEAR)
+                for (int step = FIX_MAX / 2; step > 0; step >>= 1)
+                    if (back + step <= bmax && (uint32_t)(sk[j - back - step] >> 32) == hp) back += step;
+            while (fwd < FIX_NEAR && fwd < fmax && (uint32_t)(sk[j + fwd + 1] >> 32) == hp) ++fwd;
+            if (fwd == FIX_NEAR)
+                for (int step = FIX_MAX / 2; step > 0; step >>= 1)
+                    if (fwd + step <= fmax && (uint32_t)(sk[j + fwd + step] >> 32) == hp) fwd += step;
             key[i] = kp;
             if (back + fwd + 1 > FIX_MAX) {
                 too_long = true;

@@ -122,3 +122,29 @@ def test_batch_of_short_and_longest_ensembles():
                     assert all(torch.equal(a, b) for a, b in zip(got, ref[j])), (n, mode)
             finally:
                 pr.pr_parareal_batch_destroy(h)
+
+
+@pytest.mark.parametrize("longest", [64, 65])
+def test_runs_of_equal_high_halves(longest):
+    """Radix-sorted FP64 keys in runs that agree in their high halves, of 1, 2
+    and the fix-up's longest run (64) and one key more (the complete sort), over
+    tile edges and the ends, with repeated keys in them."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    n, rng = LONGEST + 4096 + 7, np.random.default_rng(5)
+    lengths = np.resize([longest, 1, 2, 63, 64, 5], n)
+    run = np.repeat(np.arange(n), lengths)[:n]
+    x = 1.0 + run * 2.0 ** -20 + rng.integers(0, 40, n) * 2.0 ** -52
+    x = x[rng.permutation(n)]
+    print(f"runs of equal high halves up to {longest}", flush=True)
+    d = torch.from_numpy(x).cuda()
+    ws = torch.empty(pr.pr_restrict_workspace_size(n, 1, pr.PR_F64), dtype=torch.uint8, device="cuda")
+    q = torch.zeros((1, 51), dtype=torch.float64, device="cuda")
+    rank, perm = (torch.zeros(n, dtype=torch.int32, device="cuda") for _ in range(2))
+    pr.pr_restrict_quantiles(d, pr.PR_F64, n, 1, 50, q, ws, rank=rank, perm=perm)
+    torch.cuda.synchronize()
+    p, r, v = OR.sort_ranks(x)
+    assert np.array_equal(rank.cpu().numpy().view(np.uint32), r)
+    assert np.array_equal(perm.cpu().numpy().view(np.uint32), p)
+    assert np.array_equal(q[0].cpu().numpy(), OR.hazen_knots(v, 50))
