@@ -1352,7 +1352,7 @@ __device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const So
         __syncthreads();
     }
     if (!HERE && tid == 0) A.left[tile] = S.too_big ? BL_CROWDED : BL_NONE;
-    if (S.too_big) {
+    if (__builtin_expect(S.too_big, 0)) {  // and no register of the code below is spilled for it
         if constexpr (HERE) bucket_by_digits_in_lds<K, IT>(A, R, S);
         return;
     }
