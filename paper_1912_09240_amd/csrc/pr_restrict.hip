@@ -648,7 +648,8 @@ ss_sample(const void *__restrict__ x, SortLayout L, int most_runs, K *__restrict
 }
 
 // The kept keys of the runs merged, then the splitters.  Splitters past the
-// last bucket are the largest key.
+// last bucket are the largest key; the place of splitter 0, which bounds
+// nothing, says whether any bucket holds one value (see one_value).
 template <typename K, bool VAR>
 __global__ void __launch_bounds__(1024)
 ss_splitters(const K *__restrict__ runq, SortLayout L, K *__restrict__ split) {
@@ -668,8 +669,10 @@ ss_splitters(const K *__restrict__ runq, SortLayout L, K *__restrict__ split) {
         merge_pairs(buf[cur], buf[cur ^ 1], M, len);
         __syncthreads();
     }
-    for (int b = t; b < SS_B; b += 1024)
-        split[(int64_t)s * SS_B + b] = b == 0 ? (K)0 : (b < nb ? buf[cur][(int)((int64_t)b * M / nb)] : ~(K)0);
+    auto at = [&](int b) { return b < nb ? buf[cur][(int)((int64_t)b * M / nb)] : ~(K)0; };
+    const bool twice = t > 0 && t + 1 < nb && at(t) == at(t + 1);
+    const int any = __syncthreads_or(twice);
+    if (t < SS_B) split[(int64_t)s * SS_B + t] = t == 0 ? (K)(any ? 1 : 0) : at(t);
 }
 
 // The tiles of the radix passes (RS_THREADS x RS_ITEMS keys) are taken by
@@ -875,6 +878,7 @@ ss_scatter(const void *__restrict__ src, const uint32_t *bucket, const K *__rest
     const int64_t t0 = (int64_t)T.blk * TILE + wave * WAVE_KEYS;
     const uint64_t lt = (1ull << lane) - 1ull;
     for (int i = lane; i < RS_RADIX; i += 64) wcnt[wave][i] = 0;
+    const bool any_same = split[(int64_t)T.seg * SS_B] != 0;
     const bool stored = bucket != nullptr;
     if (!stored) {  // no stored buckets: searched again, from the staging area
         bucket_of->load(split + (int64_t)T.seg * SS_B, nb);
@@ -926,7 +930,7 @@ ss_scatter(const void *__restrict__ src, const uint32_t *bucket, const K *__rest
                 acc += c;
             }
             gdelta[d] = dbase + counts[T.tile0 * RS_RADIX + (int64_t)d * T.nblk + T.blk] - ls;
-            same[d] = one_value(split + (int64_t)T.seg * SS_B, d, nb);
+            if (any_same) same[d] = one_value(split + (int64_t)T.seg * SS_B, d, nb);
             if (T.blk == 0) bstart[(int64_t)T.seg * RS_RADIX + d] = dbase;
         }
     }
@@ -945,20 +949,29 @@ ss_scatter(const void *__restrict__ src, const uint32_t *bucket, const K *__rest
     const int64_t rem = T.n - (int64_t)T.blk * TILE;
     const int tile_n = rem < TILE ? (int)rem : TILE;
     uint32_t gpos[ITEMS];
+    auto leave = [&](auto mixed) {  // mixed: some bucket's keys go where the sorted ones do
 #pragma unroll
-    for (int r = 0; r < ITEMS; ++r) {
-        const int j = tid + r * SC_THREADS;
-        gpos[r] = 0xFFFFFFFFu;
-        if (j < tile_n) {
-            const uint32_t d = sdig[j], g = (uint32_t)j + gdelta[d];
-            if ((int64_t)g < T.n) {  // always true for a consistent scan
-                gpos[r] = g;
-                K *to = same[d] ? sorted : keys_out;
-                to[T.base + g] = stage[j];
-                if (xs && same[d]) xs[T.base + g] = value_of(stage[j]);
+        for (int r = 0; r < ITEMS; ++r) {
+            const int j = tid + r * SC_THREADS;
+            gpos[r] = 0xFFFFFFFFu;
+            if (j < tile_n) {
+                const uint32_t d = sdig[j], g = (uint32_t)j + gdelta[d];
+                if ((int64_t)g < T.n) {  // always true for a consistent scan
+                    gpos[r] = g;
+                    K *to = keys_out;
+                    if constexpr (mixed) {
+                        if (same[d]) {
+                            to = sorted;
+                            if (xs) xs[T.base + g] = value_of(stage[j]);
+                        }
+                    }
+                    to[T.base + g] = stage[j];
+                }
             }
         }
-    }
+    };
+    if (any_same) leave(std::true_type{});
+    else leave(std::false_type{});
     if (!pv) return;
     __syncthreads();
     uint32_t *sv = (uint32_t *)stage;
@@ -1259,11 +1272,15 @@ __device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const So
     const BucketRef R = bucket_ref<K, VAR>(L, A, tile);
     const int tid = threadIdx.x;
     const uint32_t size = R.size;
-    const bool done = size == 0 || one_value(A.split + (int64_t)R.seg * SS_B, R.b, R.nb);
-    if (done || size > (uint32_t)CAP) {
+    if (size == 0 || size > (uint32_t)CAP) {
+        const bool done = size == 0 || one_value(A.split + (int64_t)R.seg * SS_B, R.b, R.nb);
         if (tid == 0) A.left[tile] = done ? BL_NONE : (size <= (uint32_t)SS_BIG ? BL_BIG : BL_LONG);
         return;
     }
+    // the splitters on either side, on their way with the keys
+    const bool inside = R.b > 0 && R.b < R.nb - 1;
+    K kmin = inside ? A.split[(int64_t)R.seg * SS_B + R.b] : ~(K)0;
+    K kmax = inside ? A.split[(int64_t)R.seg * SS_B + R.b + 1] : (K)0;
     if (HERE && tid == 0) A.left[tile] = BL_NONE;
     const int64_t base = R.sbase + R.start;
     for (int i = tid; i < SUB / 2; i += SS_BT) S.count[i] = 0;
@@ -1281,13 +1298,11 @@ __device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const So
     }
     // bounds of the bucket's values: its splitters inside, its extremes at
     // the two ends of the ensemble
-    K kmin, kmax;
-    if (R.b > 0 && R.b < R.nb - 1) {
-        kmin = A.split[(int64_t)R.seg * SS_B + R.b];
-        kmax = A.split[(int64_t)R.seg * SS_B + R.b + 1];
-    } else {
-        kmin = ~(K)0;
-        kmax = (K)0;
+    if (inside && kmin == kmax) {  // one value: the scatter has written it
+        if (!HERE && tid == 0) A.left[tile] = BL_NONE;
+        return;
+    }
+    if (!inside) {
 #pragma unroll
         for (int i = 0; i < IT; ++i)
             if ((uint32_t)tid + (uint32_t)i * SS_BT < size) {
@@ -1649,6 +1664,7 @@ __device__ __forceinline__ void ranks_of_tile(const uint32_t *slots, const uint3
     const TileRef T = tile_ref<VAR>(L, tile);
     const int nb = ss_buckets<VAR>(T.n), tid = threadIdx.x;
     if (nb == 1) return;
+    const bool any_same = split[(int64_t)T.seg * SS_B] != 0;
     const int64_t t0 = (int64_t)T.blk * TILE;
     const int tile_n = T.n - t0 < TILE ? (int)(T.n - t0) : TILE;
     uint32_t s[ITEMS];
@@ -1667,20 +1683,28 @@ __device__ __forceinline__ void ranks_of_tile(const uint32_t *slots, const uint3
     const uint32_t ls = block_exclusive<SC_THREADS>(mine, wtot);
     if (tid < nb) {
         gdelta[tid] = at - ls;
-        same[tid] = one_value(split + (int64_t)T.seg * SS_B, tid, nb);
+        if (any_same) same[tid] = one_value(split + (int64_t)T.seg * SS_B, tid, nb);
     }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i)
         if (s[i] != ~0u) sdig[s[i] & (TILE - 1)] = (uint8_t)(s[i] >> RK_SHIFT);
     __syncthreads();
     uint32_t r[ITEMS];
+    auto ranks = [&](auto mixed) {  // mixed: some bucket's slots are their own ranks
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        const int j = tid + i * SC_THREADS;
-        const uint32_t g = j < tile_n ? (uint32_t)j + gdelta[sdig[j]] : ~0u;
-        r[i] = g;
-        if ((int64_t)g < T.n && !same[sdig[j]]) r[i] = frank[T.base + g];
-    }
+        for (int i = 0; i < ITEMS; ++i) {
+            const int j = tid + i * SC_THREADS;
+            const uint32_t g = j < tile_n ? (uint32_t)j + gdelta[sdig[j]] : ~0u;
+            r[i] = g;
+            if constexpr (mixed) {
+                if ((int64_t)g < T.n && !same[sdig[j]]) r[i] = frank[T.base + g];
+            } else {
+                r[i] = (int64_t)g < T.n ? frank[T.base + g] : 0u;
+            }
+        }
+    };
+    if (any_same) ranks(std::true_type{});
+    else ranks(std::false_type{});
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) sr[tid + i * SC_THREADS] = r[i];
     __syncthreads();
