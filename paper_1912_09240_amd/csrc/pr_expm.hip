@@ -13,7 +13,7 @@
 // sum, so the entries do not depend on the tile sizes or the bands.
 //
 // 1024 cells, 64 slices of T = 10 (two slice lengths, 14 squarings each),
-// with one coarse pass: 1.16 ms; 37 products per length in 64x64 VALU tiles at
+// with one coarse pass: 1.14 ms; 37 products per length in 64x64 VALU tiles at
 // 9 TFLOP/s took 17.8 ms.
 #include <algorithm>
 #include <cmath>
