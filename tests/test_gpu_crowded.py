@@ -131,3 +131,37 @@ def test_buckets_of_one_value(n, prec):
     x[3, ::3] = 0.0
     x[4] = 2.5
     _check(torch, np.ascontiguousarray(x.astype(np.float64 if prec == pr.PR_F64 else np.float32)), prec, 7)
+
+
+@pytest.mark.parametrize("prec", [pr.PR_F64, pr.PR_F32])
+@pytest.mark.parametrize("case", ["values", "zeros", "mixed", "outliers", "short_runs"])
+def test_crowded_buckets_without_ranks(case, prec):
+    """Knots and sorted values alone, where a crowded sub-bucket of one value is
+    left as it was counted: ties, zeros of both signs (one sub-bucket, two keys),
+    crowded sub-buckets of several values beside ones of one."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(23)
+    dt = np.float64 if prec == pr.PR_F64 else np.float32
+    for n, k in [(n, 3) for n in SIZES] + [(500, 300), (7168, 257), (14_337, 20), (200_000, 2)]:
+        print(f"crowded without ranks {case} precision={prec} n={n} k={k}", flush=True)
+        if case == "zeros":
+            xs = np.where(rng.random((k, n)) < 0.5, -0.0, 0.0)
+            xs[:, ::7] = np.round(rng.normal(0.0, 1.0, (k, len(range(0, n, 7)))) * 4.0) / 4.0
+        elif case == "mixed":  # 64 values, those of the upper half with a few ulp around them
+            xs = 1.0 + np.floor(rng.random((k, n)) * 64.0) / 64.0
+            xs += np.where(xs > 1.5, rng.integers(0, 5, (k, n)) * np.spacing(dt(1.0)), 0.0)
+        else:
+            xs = _crowded(case, k, n, rng)
+        xs = np.ascontiguousarray(xs.astype(dt))
+        x = torch.from_numpy(xs).cuda()
+        ws = torch.empty(pr.pr_restrict_workspace_size(n, k, prec), dtype=torch.uint8, device="cuda")
+        q = torch.zeros((k, 101), dtype=torch.float64, device="cuda")
+        srt = torch.zeros((k, n), dtype=torch.float64, device="cuda")
+        pr.pr_restrict_quantiles(x, prec, n, k, 100, q, ws, x_sorted=srt)
+        torch.cuda.synchronize()
+        for s in range(0, k, max(1, k // 5)):
+            v = OR.sort_ranks(xs[s].astype(np.float64))[2]
+            assert np.array_equal(srt[s].cpu().numpy().view(np.uint64), v.view(np.uint64)), (n, s)
+            assert np.array_equal(q[s].cpu().numpy(), OR.hazen_knots(v, 100)), (n, s)
