@@ -485,10 +485,13 @@ constexpr int SS_BIG = SS_BT * SS_IT_BIG;   // 14336: one block takes 156 KiB of
 // Keys of a value sub-bucket above which the bucket goes by digits: the
 // counting's time grows with them and with the keys per thread, that of the
 // digits only with the latter.  FP32, 8 ensembles of 2^20 of 20,000 values (52 keys
-// each): 396 us counted, 359 by digits; FP64, 64 of them: 2.63 and 3.48 ms.
-template <typename K>
+// each): 396 us counted, 359 by digits; FP64, 64 of them: 2.63 and 3.48 ms.  HERE, FP64
+// ensembles of one bucket, which wait for one block and not for the chip: with
+// the line of the others 7168 keys of 140 values take 144 us instead of 90, 1000
+// half of which are zero 69 instead of 25.
+template <typename K, bool HERE>
 constexpr uint32_t ss_crowded(uint32_t size) {
-    return (sizeof(K) == 8 ? 160u : 42u) << (size <= 1024 ? 2 : size <= 2048 ? 1 : 0);
+    return (sizeof(K) == 8 && !HERE ? 160u : 42u) << (size <= 1024 ? 2 : size <= 2048 ? 1 : 0);
 }
 // Above this the SS_B buckets average more than 4352 keys.  A bucket spans 64
 // samples and its two splitters are each a few samples off (thinned runs): its
@@ -1351,7 +1354,7 @@ __device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const So
             c[2 * i] = two & 0xFFFFu;
             c[2 * i + 1] = two >> 16;
             sum += c[2 * i] + c[2 * i + 1];
-            if (max(c[2 * i], c[2 * i + 1]) > ss_crowded<K>(size)) S.too_big = 1;
+            if (max(c[2 * i], c[2 * i + 1]) > ss_crowded<K, HERE>(size)) S.too_big = 1;
         }
         const int lane = tid & 63, wave = tid >> 6;
         uint32_t inc = sum;
@@ -1406,7 +1409,7 @@ __device__ __forceinline__ void bucket_by_block(const BucketArgs<K> &A, const So
                 if (w[i] != NONE) {
                     const uint32_t a = S.start[w[i] & 0xFFFFu], e = S.start[(w[i] & 0xFFFFu) + 1];
                     if (!(S.spos[a] & MIXED)) alike |= 1u << i;
-                    else if (e - a > ss_crowded<uint32_t>(SS_CAP)) S.too_big = 4;
+                    else if (e - a > ss_crowded<uint32_t, HERE>(SS_CAP)) S.too_big = 4;
                 }
             __syncthreads();
             if (S.too_big == 4) {
